@@ -8,14 +8,55 @@
 //   dQ[u][v] = <A[u,:], pi_hat[v,:]>
 //   g(u->v)  = (1-alpha)/d_u (dQ[u][v] - sum_b P_ub dQ[u][b]) + sum_t G[u][t] pi_hat[u][t]
 //   dLoss/dw_{u,v} = g(u->v) + g(v->u)   (one weight shared by both arcs)
-// The adjoint gathers over the same neighbours with the same coefficients as
-// the forward push, so it reuses the streaming step with a dense forcing term.
+// Two ways to A, chosen by adjoint_dense:
+//  - the sum over j is the transposed forward result, (sum_{j<T} Q^j)^T =
+//    pi_hat^T / alpha, and pi_hat is at hand: A = pi_hat^T D G / alpha is one
+//    dense product, whose cost does not depend on T;
+//  - T - 1 streaming steps with a dense forcing term (the adjoint gathers over
+//    the same neighbours with the same coefficients as the forward push).
+#include "dense.hpp"
 #include "internal.hpp"
 
 namespace pprviz {
 
-// One wave per arc: dq[e] = <A[u, :], pi[v, :]>, A in the slab layout of
-// the streaming iterate, pi row-major n x n.
+// A = pi_hat^T D G / alpha, row-major n x n, one BT x BT tile per block.
+// Blocks go to the XCDs round-robin, so block b takes tile (b % 8) of every
+// eighth part of the list: each XCD works through one contiguous part, in
+// bands of 8 tile rows, whose operand rows its L2 keeps.
+// Bound: the matrix cores (2 n^3 FLOP): 116 TFLOP/s at n = 8192, 75% of the
+// FP32 matrix peak.
+constexpr int kAdjBand = 8;
+// 128-wide tiles from this size on, where they fill the 256 CUs twice over
+// (two blocks per CU); below it 64-wide ones, which need twice the operand
+// traffic but leave four times the blocks.
+constexpr int kAdjWideN = 3000;
+
+template <int BT>
+__global__ __launch_bounds__(kDenseThreads, 2) void adjoint_dense_kernel(const float* __restrict__ pi,
+                                                                       const float* __restrict__ G,
+                                                                       const float* __restrict__ deg, int32_t n,
+                                                                       float alpha, float* __restrict__ A) {
+    __shared__ DenseLds<BT> L;
+    const int nt = (n + BT - 1) / BT;
+    const int64_t total = (int64_t)nt * nt;
+    const int64_t part = (total + kXcds - 1) / kXcds;
+    const int64_t item = (blockIdx.x % kXcds) * part + blockIdx.x / kXcds;
+    if (blockIdx.x / kXcds >= part || item >= total) return;  // block-uniform
+    const int64_t band = item / ((int64_t)kAdjBand * nt);
+    const int rows = (int)min((int64_t)kAdjBand, nt - band * kAdjBand);
+    const int64_t in = item - band * kAdjBand * nt;
+    const int i0 = (int)(band * kAdjBand + in % rows) * BT, j0 = (int)(in / rows) * BT;
+    DenseTile<BT> t;
+    dense_tile<BT, 256 / dense_k(BT)>(pi, n, G, n, deg, 1.0f / alpha, n, i0, j0, L, t);
+    dense_each<BT>(t, i0, j0, [&](int i, int j, float v) {
+        if (i < n && j < n) A[(int64_t)i * n + j] = v;
+    });
+}
+
+// One wave per arc: dq[e] = <A[u, :], pi[v, :]>, pi row-major n x n; A
+// row-major as well (SLAB = false), or in the slab layout of the streaming
+// iterate.
+template <bool SLAB>
 __global__ __launch_bounds__(256) void arc_dot_kernel(const int32_t* __restrict__ row_of_arc,
                                                       const int32_t* __restrict__ col_idx, int64_t nnz,
                                                       const float* __restrict__ A,
@@ -28,7 +69,7 @@ __global__ __launch_bounds__(256) void arc_dot_kernel(const int32_t* __restrict_
     const int64_t v = col_idx[e];
     const float* p = pi + v * (int64_t)n;
     double s = 0.0;
-    for (int t = lane; t < n; t += 64) s = fma((double)A[sidx(u, t, n)], (double)p[t], s);
+    for (int t = lane; t < n; t += 64) s = fma((double)A[SLAB ? sidx(u, t, n) : u * n + t], (double)p[t], s);
     s = wave_sum(s);
     if (lane == 0) dq[e] = s;
 }
@@ -89,6 +130,29 @@ __global__ void edge_sum_kernel(const int32_t* __restrict__ row_ptr, const int32
     out[e] = (float)(g[e] + (rev >= 0 ? g[rev] : 0.0));
 }
 
+// Whether the adjoint is taken as the dense product: by the time each takes.
+// Measured: the product runs at 116 TFLOP/s (n = 8192: 9.5 ms; n = 1000: 41
+// us), a streaming step moves nnz n 4-byte values at 11-12 TB/s and takes 6 us
+// at least (T - 1 = 99 steps: 53.9 ms for n = 8192 and 1.97e5 arcs, 1.0 ms for
+// n = 1000).  For short series of sparse graphs the steps win.
+static bool adjoint_dense(int n, int64_t nnz, int T) {
+    const double dense = 2.0 * n * n * n / 110e12 + 10e-6;
+    const double stream = (double)(T - 1) * (4.0 * nnz * n / 11e12 + 6e-6);
+    return dense < stream;
+}
+
+static void adjoint_launch(const float* pi, const float* G, const float* deg, int n, float alpha, float* A,
+                           hipStream_t s) {
+    auto blocks = [&](int bt) {
+        const int64_t nt = (n + bt - 1) / bt;
+        return dim3((unsigned)((nt * nt + kXcds - 1) / kXcds * kXcds));
+    };
+    if (n >= kAdjWideN)
+        hipLaunchKernelGGL(adjoint_dense_kernel<128>, blocks(128), dim3(kDenseThreads), 0, s, pi, G, deg, n, alpha, A);
+    else
+        hipLaunchKernelGGL(adjoint_dense_kernel<64>, blocks(64), dim3(kDenseThreads), 0, s, pi, G, deg, n, alpha, A);
+}
+
 struct BwdWs {
     PprWs f;  // forward recompute (any kernel) plus the streaming buffers of the adjoint
     float* pi;
@@ -147,25 +211,32 @@ ppr_status ppr_matrix_backward(const ppr_csr* g, float alpha, int32_t T, const f
         ppr_forward(g, nullptr, n, nullptr, n, alpha, T, w.pi, nullptr, f.deg, f.invd, nullptr, f, s);
         pi = w.pi;
     }
-    stream_row_order(g->row_ptr, n, f.hist, f.rows, s);
-    StreamArgs sa;
-    sa.rows = f.rows;
-    sa.row_ptr = g->row_ptr;
-    sa.col_idx = g->col_idx;
-    sa.weight = g->weight;
-    sa.invd = f.invd;
-    sa.deg = f.deg;
-    sa.n = n;
-    sa.ncols = n;
-    sa.ld = stream_ld(n);
-    sa.alpha = alpha;
-    sa.src = nullptr;
-    sa.forcing = grad_dppr;
-    sa.ld_forcing = n;
-    const float* A = stream_power_iteration(sa, T, f.ya, f.yb, s);
     hipLaunchKernelGGL(row_of_arc_kernel, dim3((n + 255) / 256), dim3(256), 0, s, g->row_ptr, n, w.row_of_arc);
-    hipLaunchKernelGGL(arc_dot_kernel, dim3((unsigned)((g->nnz + 3) / 4)), dim3(256), 0, s, w.row_of_arc, g->col_idx,
-                       g->nnz, A, pi, n, w.dq);
+    const dim3 dots((unsigned)((g->nnz + 3) / 4));
+    if (adjoint_dense(n, g->nnz, T)) {
+        adjoint_launch(pi, grad_dppr, f.deg, n, alpha, f.ya, s);
+        hipLaunchKernelGGL(arc_dot_kernel<false>, dots, dim3(256), 0, s, w.row_of_arc, g->col_idx, g->nnz, f.ya, pi,
+                           n, w.dq);
+    } else {
+        stream_row_order(g->row_ptr, n, f.hist, f.rows, s);
+        StreamArgs sa;
+        sa.rows = f.rows;
+        sa.row_ptr = g->row_ptr;
+        sa.col_idx = g->col_idx;
+        sa.weight = g->weight;
+        sa.invd = f.invd;
+        sa.deg = f.deg;
+        sa.n = n;
+        sa.ncols = n;
+        sa.ld = stream_ld(n);
+        sa.alpha = alpha;
+        sa.src = nullptr;
+        sa.forcing = grad_dppr;
+        sa.ld_forcing = n;
+        const float* A = stream_power_iteration(sa, T, f.ya, f.yb, s);
+        hipLaunchKernelGGL(arc_dot_kernel<true>, dots, dim3(256), 0, s, w.row_of_arc, g->col_idx, g->nnz, A, pi, n,
+                           w.dq);
+    }
     hipLaunchKernelGGL(row_dot_kernel, dim3((n + 3) / 4), dim3(256), 0, s, grad_dppr, pi, n, w.dd);
     hipLaunchKernelGGL(arc_grad_kernel, dim3((n + 255) / 256), dim3(256), 0, s, g->row_ptr, g->weight, f.deg, w.dq,
                        w.dd, n, alpha, w.g);
