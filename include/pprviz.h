@@ -86,6 +86,13 @@ ppr_status pprviz_pushes_for_tolerance(float alpha, double tol, int32_t max_iter
 /* Workspace bytes needed by ppr_matrix for this graph and source count. */
 size_t ppr_matrix_workspace(const ppr_csr* g, int32_t n_src, int32_t n_tgt);
 
+/* Workspace bytes with which ppr_matrix takes its fastest route: at least
+ * ppr_matrix_workspace(), and 16 n^2 bytes more for all pairs (n_src == n) of
+ * a graph of 192 <= n <= 2304 nodes, whose push series is then cut into a
+ * shorter one and dense products where that is faster.  The two routes agree
+ * to FP32 rounding. */
+size_t ppr_matrix_workspace_fast(const ppr_csr* g, int32_t n_src, int32_t n_tgt);
+
 /*
  * pi_hat(s, t) after T pushes from every source s in src[0..n_src), for the
  * targets t in tgt[0..n_tgt) (tgt == NULL: all nodes, n_tgt must equal n).
@@ -120,15 +127,17 @@ ppr_status ppr_matrix(const ppr_csr* g, const int32_t* src, int32_t n_src,
 /*
  * ppr_matrix for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same computation, kernels and results as ppr_matrix, with the workspace
- * taken from a fixed scratch array inside the library instead of a caller
+ * same computation, kernels and results as ppr_matrix with the workspace of
+ * ppr_matrix_workspace_fast(), taken from a fixed scratch array inside the library instead of a caller
  * buffer.  Inputs and outputs are still the caller's.  The call allocates
  * nothing (no hipMalloc/hipFree, no allocating library routine).
  *
  * Limit: the workspace ppr_matrix_workspace(g, n_src, n_tgt) would ask for
  * must fit ppr_matrix_noalloc_max_scratch() bytes (8 MiB), else the call
  * returns PPR_EUNSUPPORTED before any launch.  That covers, for example, the
- * LDS-resident path (n <= 2304) up to about 1 million arcs unweighted.
+ * LDS-resident path (n <= 2304) up to about 1 million arcs unweighted.  The
+ * 16 n^2 bytes that the fastest route of all pairs adds have room of their
+ * own (85 MB) and do not count.
  *
  * The scratch is one array per GPU, held from the first call on that GPU
  * until the process ends (its device address is looked up once per device).
@@ -401,7 +410,10 @@ typedef struct {
 /* Largest subgraph the batched path accepts (all-pairs PPR kept on chip). */
 int32_t pprviz_batch_max_n(void);
 
-/* Workspace bytes for pprviz_batch / pprviz_batch_plan_create. */
+/* Workspace bytes for pprviz_batch / pprviz_batch_plan_create.  Where max_n is
+ * at least 192 this holds a pool of pool_size floats for the dense products of
+ * the all-pairs PPR; a workspace without it (4 pool_size bytes less) is
+ * accepted as well and takes all pushes, which is slower. */
 size_t pprviz_batch_workspace(const ppr_batch* b);
 
 /*

@@ -40,6 +40,7 @@ _SIGS = {
     "pprviz_status_string": (C.c_char_p, [C.c_int]),
     "pprviz_pushes_for_tolerance": (C.c_int, [f32, f64, i32, C.POINTER(i32), C.POINTER(i32)]),
     "ppr_matrix_workspace": (sz, [C.POINTER(ppr_csr), i32, i32]),
+    "ppr_matrix_workspace_fast": (sz, [C.POINTER(ppr_csr), i32, i32]),
     "ppr_matrix": (C.c_int, [C.POINTER(ppr_csr), vp, i32, vp, i32, f32, f64, i32, vp, vp,
                              C.POINTER(f64), C.POINTER(i32), vp, sz, vp]),
     "ppr_matrix_noalloc_max_scratch": (sz, []),

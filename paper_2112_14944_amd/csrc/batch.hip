@@ -22,6 +22,7 @@
 #include "internal.hpp"
 #include "layout_core.hpp"
 #include "ppr_core.hpp"
+#include "ppr_dense.hpp"
 
 namespace pprviz {
 
@@ -52,7 +53,8 @@ struct BatchPlan {
     int32_t* rt_graph;   // subgraph of each 64-row tile
     int64_t* pb_pre;     // [G+1] prefix of the partial blocks, T*T*64 floats per subgraph
     int64_t* iv_pre;     // [G+1] prefix of the 1/Delta pool, k rows of inv_ld(k) floats per subgraph
-    int32_t* counter;    // [4] PPR task queue heads, one per tile width; layout task queue head
+    int64_t* dn_pre[kDenseMaxK];  // [G+1] prefix of the p-th product's tiles, LPT order
+    int32_t* counter;    // [4 + kDenseMaxK] queue heads: PPR tasks per tile width, layout tasks, product tiles
     int32_t* cls_pos;    // [4] first LPT position of the 16-, 32- and 64-column classes, then G
 };
 
@@ -77,7 +79,7 @@ __device__ __forceinline__ int64_t tiles_of(int n) {
     return cols == 0 ? 0 : (n + cols - 1) / cols;
 }
 
-constexpr int kPlanPrefixes = 7;
+constexpr int kPlanPrefixes = 7 + kDenseMaxK;
 
 // Row stride of a subgraph's block in the 1/Delta pool: rows start on a
 // 128-byte boundary, so the 256-byte row segments a pair tile reads span two
@@ -92,12 +94,16 @@ __device__ __forceinline__ int64_t* plan_prefix(const BatchPlan& p, int which) {
         case 3: return p.pt_pre;
         case 4: return p.rt_pre;
         case 5: return p.pb_pre;
-        default: return p.iv_pre;
+        case 6: return p.iv_pre;
+        default: return p.dn_pre[which - 7];
     }
 }
 
+// Whether a prefix runs over the subgraphs in LPT order (else by id).
+__device__ __forceinline__ bool plan_lpt(int which) { return which == 0 || which >= 7; }
+
 // Items of an n-node subgraph for each prefix of the plan.
-__device__ __forceinline__ int64_t plan_count(int which, int n) {
+__device__ __forceinline__ int64_t plan_count(int which, int n, int64_t nnz, int pushes) {
     const int64_t T = (n + kPT - 1) / kPT;
     switch (which) {
         case 0: return tiles_of(n);                                          // PPR source tiles
@@ -106,7 +112,8 @@ __device__ __forceinline__ int64_t plan_count(int which, int n) {
         case 3: return strip_task_count(T);                                  // layout tasks (S, J0)
         case 4: return T;                                                    // 64-row tiles
         case 5: return T * T * kPT;                                          // partial-block floats
-        default: return (int64_t)n * inv_ld(n);                              // 1/Delta pool floats
+        case 6: return (int64_t)n * inv_ld(n);                               // 1/Delta pool floats
+        default: return dense_plan(n, nnz, pushes).k > which - 7 ? dense_tiles(n, dense_bt(n)) : 0;  // product tiles
     }
 }
 
@@ -127,8 +134,9 @@ __device__ __forceinline__ int strip_class(int k, int T, int S, int J0) {
     return (kStripGroup * kStripBlocks * kPT * kPT - pairs) / 64;
 }
 
-__global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t* __restrict__ node_off, int32_t G,
-                                                                  BatchPlan p) {
+__global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t* __restrict__ node_off,
+                                                                  const int32_t* __restrict__ row_ptr, int32_t G,
+                                                                  int32_t series_T, BatchPlan p) {
     __shared__ int32_t hist[kBatchMaxN + 2];
     __shared__ int64_t scan_tmp[kPlanThreads];
     const int tid = threadIdx.x;
@@ -160,7 +168,12 @@ __global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t*
         const int per = (G + kPlanThreads - 1) / kPlanThreads;
         const int a = tid * per, b = min(G, a + per);
         int64_t loc = 0;
-        for (int i = a; i < b; ++i) loc += plan_count(which, graph_n(node_off, which == 0 ? p.order[i] : i));
+        auto count = [&](int i) {
+            const int g = plan_lpt(which) ? p.order[i] : i;
+            const int64_t nnz = which >= 7 ? row_ptr[node_off[g + 1]] - row_ptr[node_off[g]] : 0;
+            return plan_count(which, graph_n(node_off, g), nnz, series_T);
+        };
+        for (int i = a; i < b; ++i) loc += count(i);
         scan_tmp[tid] = loc;
         __syncthreads();
         if (tid == 0) {
@@ -175,7 +188,7 @@ __global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t*
         int64_t run = scan_tmp[tid];
         for (int i = a; i < b; ++i) {
             out[i] = run;
-            run += plan_count(which, graph_n(node_off, which == 0 ? p.order[i] : i));
+            run += count(i);
         }
         if (tid == kPlanThreads - 1) out[G] = run;
         __syncthreads();
@@ -245,7 +258,7 @@ __global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t*
     }
     __syncthreads();
     if (tid == 0) {
-        p.counter[0] = p.counter[1] = p.counter[2] = p.counter[3] = 0;
+        for (int i = 0; i < 4 + kDenseMaxK; ++i) p.counter[i] = 0;
         p.cls_pos[0] = 0;
         p.cls_pos[1] = cls_cnt[0];
         p.cls_pos[2] = cls_cnt[0] + cls_cnt[1];
@@ -258,13 +271,29 @@ struct BatchArgs {
     const int64_t* mat_off;
     const int32_t* row_ptr;
     int32_t G;
+    int32_t T;         // pushes
+    int32_t series_T;  // T where subgraphs may take the all-pairs series, else 0
+    const float* invd;
     ResArgs r;  // graph-global fields; src/tgt null (all pairs), ppr_out null
 };
+
+// The pools of the all-pairs series (subgraph blocks at mat_off, ld = n): V in
+// the 1/Delta pool, Y_m in the Delta pool (both are written after PPR only);
+// W_p alternates between the DPPR pool and one of its own, so that the last,
+// W_k as DPPR, lands in the former.
+struct SeriesPools {
+    float* v;
+    float* ym;
+    float* w[2];  // DPPR pool, the other
+};
+
+// The pool of W_p of a k-product series.
+__device__ __forceinline__ int series_pool(int k, int p) { return (k - p) & 1; }
 
 // Persistent kernel for the subgraphs of one tile width: blocks pop task ids
 // of the class's range (LPT order) until it is exhausted.
 template <int COLS, int CLS>
-__global__ __launch_bounds__(kResThreads) void batch_ppr_kernel(BatchArgs b, BatchPlan p) {
+__global__ __launch_bounds__(kResThreads) void batch_ppr_kernel(BatchArgs b, BatchPlan p, SeriesPools sp) {
     __shared__ ResLds L;
     __shared__ int32_t task_sh;
     const int p0 = p.cls_pos[CLS];
@@ -290,8 +319,64 @@ __global__ __launch_bounds__(kResThreads) void batch_ppr_kernel(BatchArgs b, Bat
         t.base = b.node_off[g];
         t.out_off = b.mat_off[g];
         t.ld = n;
-        res_graph_bases(t.base, b.row_ptr[t.base], b.row_ptr[t.base + n], g, n, t);
-        res_tile<COLS, false>(t, b.r, L);
+        const int e0 = b.row_ptr[t.base], e1 = b.row_ptr[t.base + n];
+        res_graph_bases(t.base, e0, e1, g, n, t);
+        const DensePlan d = dense_plan(n, e1 - e0, b.series_T);
+        t.T = b.T;
+        t.m = t.r = 0;
+        ResArgs a = b.r;
+        if (d.k > 0) {
+            t.T = d.m + 1;
+            t.m = d.m;
+            t.r = d.r;
+            a.yr = series_pool(d.k, 0) ? sp.w[1] : sp.w[0];
+            a.ym = sp.ym;
+            a.vd = sp.v;
+        }
+        res_tile<COLS, false>(t, a, L);
+    }
+}
+
+// The p-th product (p = 1 ..) of every subgraph that takes one, largest
+// subgraphs first; blocks pop tiles until none is left.
+union BatchDenseLds {
+    DenseLds<64> narrow;
+    DenseLds<128> wide;
+};
+
+__global__ __launch_bounds__(kDenseThreads, 2) void batch_product_kernel(BatchArgs b, BatchPlan p, SeriesPools sp,
+                                                                       int32_t phase) {
+    __shared__ BatchDenseLds L;
+    __shared__ int32_t task_sh;
+    const int64_t* pre = p.dn_pre[phase - 1];
+    const int64_t total = pre[b.G];
+    for (;;) {
+        if (threadIdx.x == 0) task_sh = atomicAdd(&p.counter[3 + phase], 1);
+        __syncthreads();
+        const int64_t task = __builtin_amdgcn_readfirstlane(task_sh);
+        __syncthreads();
+        if (task >= total) return;
+        const int pos = __builtin_amdgcn_readfirstlane(find_segment(pre, b.G, task));
+        const int g = __builtin_amdgcn_readfirstlane(p.order[pos]);
+        const int n = __builtin_amdgcn_readfirstlane(graph_n(b.node_off, g));
+        const int64_t base = b.node_off[g];
+        const DensePlan d = dense_plan(n, b.row_ptr[base + n] - b.row_ptr[base], b.series_T);
+        const int64_t off = b.mat_off[g];
+        const float* V = uniform_ptr(sp.v + off);
+        const float* Ym = uniform_ptr(sp.ym + off);
+        const float* W = phase == 1 && d.r == d.m ? Ym : uniform_ptr(sp.w[series_pool(d.k, phase - 1)] + off);
+        float* out = uniform_ptr(sp.w[series_pool(d.k, phase)] + off);
+        const float* deg = uniform_ptr(b.r.deg + base);
+        const float* invd = uniform_ptr(b.invd + base);
+        const int64_t t = task - pre[pos];
+        const bool last = phase == d.k;
+        if (dense_bt(n) == 64) {
+            if (last) dense_product_tile<64, true>(V, Ym, W, deg, invd, b.r.alpha, n, t, L.narrow, out);
+            else dense_product_tile<64, false>(V, Ym, W, deg, invd, b.r.alpha, n, t, L.narrow, out);
+        } else {
+            if (last) dense_product_tile<128, true>(V, Ym, W, deg, invd, b.r.alpha, n, t, L.wide, out);
+            else dense_product_tile<128, false>(V, Ym, W, deg, invd, b.r.alpha, n, t, L.wide, out);
+        }
     }
 }
 
@@ -495,7 +580,11 @@ struct BatchWs {
     float* px;  // strip partial blocks of the sweeps (x, y; the weight pass uses px)
     float* py;
     BatchPlan plan;
+    float* series;  // second W pool of the all-pairs series; nullptr: not taken
 };
+
+// Floats of the series' own pool (0: no subgraph is large enough).
+static size_t batch_series_floats(const ppr_batch* b) { return b->max_n >= kDenseMinN ? (size_t)b->pool_size : 0; }
 
 template <typename Cursor>
 static void batch_layout_ws(Cursor& c, const ppr_batch* b, BatchWs* w) {
@@ -535,6 +624,9 @@ static void batch_layout_ws(Cursor& c, const ppr_batch* b, BatchWs* w) {
 
     t.plan.counter = c.template take<int32_t>(64);
     t.plan.cls_pos = c.template take<int32_t>(64);
+    for (int p = 0; p < kDenseMaxK; ++p)
+        t.plan.dn_pre[p] = c.template take<int64_t>((size_t)b->n_graphs + 1);
+    t.series = nullptr;
     if (w) *w = t;
 }
 
@@ -581,7 +673,10 @@ static ppr_status batch_enqueue(const ppr_batch* b, float alpha, int32_t T, int3
     launch_degree(b->row_ptr, nullptr, b->n_nodes, w.deg, w.invd, s);
     launch_res_layout(b->row_ptr, b->col_idx, nullptr, w.invd, b->node_off, 0, G, w.slots, w.col_r, nullptr,
                       w.sorted_r, nullptr, s);
-    hipLaunchKernelGGL(batch_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, b->node_off, G, w.plan);
+    // with room for its pool, subgraphs may take the all-pairs series
+    const int series_T = w.series != nullptr ? T : 0;
+    hipLaunchKernelGGL(batch_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, b->node_off, b->row_ptr, G, series_T,
+                       w.plan);
     if (ev) PPRVIZ_HIP_TRY(hipEventRecord(ev[1], s));
 
     BatchArgs ba;
@@ -589,6 +684,9 @@ static ppr_status batch_enqueue(const ppr_batch* b, float alpha, int32_t T, int3
     ba.mat_off = b->mat_off;
     ba.row_ptr = b->row_ptr;
     ba.G = G;
+    ba.T = T;
+    ba.series_T = series_T;
+    ba.invd = w.invd;
     ba.r.slots = w.slots;
     ba.r.arcs = w.col_r;
     ba.r.warcs = nullptr;
@@ -596,14 +694,18 @@ static ppr_status batch_enqueue(const ppr_batch* b, float alpha, int32_t T, int3
     ba.r.src = nullptr;
     ba.r.tgt = nullptr;
     ba.r.alpha = alpha;
-    ba.r.T = T;
     ba.r.ppr_out = nullptr;
     ba.r.dppr_out = dppr_pool;
     ba.r.resid = nullptr;
+    ba.r.yr = ba.r.ym = ba.r.vd = nullptr;
+    const SeriesPools sp{w.inv, delta_pool, {dppr_pool, w.series}};
     const int cus = device_cu_count();
-    hipLaunchKernelGGL((batch_ppr_kernel<16, 0>), dim3(cus), dim3(kResThreads), 0, s, ba, w.plan);
-    hipLaunchKernelGGL((batch_ppr_kernel<32, 1>), dim3(cus), dim3(kResThreads), 0, s, ba, w.plan);
-    hipLaunchKernelGGL((batch_ppr_kernel<64, 2>), dim3(cus), dim3(kResThreads), 0, s, ba, w.plan);
+    hipLaunchKernelGGL((batch_ppr_kernel<16, 0>), dim3(cus), dim3(kResThreads), 0, s, ba, w.plan, sp);
+    hipLaunchKernelGGL((batch_ppr_kernel<32, 1>), dim3(cus), dim3(kResThreads), 0, s, ba, w.plan, sp);
+    hipLaunchKernelGGL((batch_ppr_kernel<64, 2>), dim3(cus), dim3(kResThreads), 0, s, ba, w.plan, sp);
+    if (series_T >= kDenseMinT && series_T <= kDenseMaxT)
+        for (int phase = 1; phase <= kDenseMaxK; ++phase)
+            hipLaunchKernelGGL(batch_product_kernel, dim3(2 * cus), dim3(kDenseThreads), 0, s, ba, w.plan, sp, phase);
     if (ev) PPRVIZ_HIP_TRY(hipEventRecord(ev[2], s));
 
     const unsigned grid = (unsigned)cus * 8;
@@ -665,6 +767,7 @@ size_t pprviz_batch_workspace(const ppr_batch* b) {
     if (b == nullptr || b->n_graphs < 1 || b->n_nodes < 1) return 0;
     WsSize c;
     batch_layout_ws(c, b, nullptr);
+    if (batch_series_floats(b) > 0) c.take<float>(batch_series_floats(b));
     return c.used;
 }
 
@@ -680,6 +783,7 @@ ppr_status pprviz_batch(const ppr_batch* b, float alpha, double tol_l1, int32_t 
     BatchWs w;
     batch_layout_ws(cur, b, &w);
     if (ws == nullptr || cur.used > ws_bytes) return PPR_EWORKSPACE;
+    if (batch_series_floats(b) > 0) w.series = cur.take<float>(batch_series_floats(b));
     if (pending_error() != PPR_OK) return PPR_EHIP;
     st = batch_enqueue(b, alpha, T, stress_iters, x0, x_out, dppr_pool, delta_pool, stress_out, w,
                        static_cast<hipStream_t>(stream));
@@ -701,6 +805,7 @@ ppr_status pprviz_batch_profile(const ppr_batch* b, float alpha, double tol_l1, 
     BatchWs w;
     batch_layout_ws(cur, b, &w);
     if (ws == nullptr || cur.used > ws_bytes) return PPR_EWORKSPACE;
+    if (batch_series_floats(b) > 0) w.series = cur.take<float>(batch_series_floats(b));
     if (pending_error() != PPR_OK) return PPR_EHIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipEvent_t ev[5] = {};
@@ -740,6 +845,7 @@ ppr_status pprviz_batch_plan_create(const ppr_batch* b, float alpha, double tol_
     BatchWs w;
     batch_layout_ws(cur, b, &w);
     if (ws == nullptr || cur.used > ws_bytes) return PPR_EWORKSPACE;
+    if (batch_series_floats(b) > 0) w.series = cur.take<float>(batch_series_floats(b));
     if (pending_error() != PPR_OK) return PPR_EHIP;
     hipStream_t cs = nullptr;
     PPRVIZ_HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));

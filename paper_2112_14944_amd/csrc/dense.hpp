@@ -1,8 +1,8 @@
 // Dense FP32 products on the matrix cores (v_mfma_f32_32x32x2_f32), one tile
 // of C[i][j] = sum_k A[k][i] f_k B[k][j] per block: both operands are read
 // row by row along k, so that every load is a contiguous row segment and LDS
-// needs no transposition.  Used by the adjoint of the weight gradient
-// (grad.hip).
+// needs no transposition.  Two users: the adjoint of the weight gradient
+// (grad.hip) and the products of the all-pairs PPR (ppr_dense.hpp).
 //
 // FP32 products and FP32 accumulation throughout: an element is summed in
 // ascending k, two terms per instruction, whatever the tile size, so a tile

@@ -174,6 +174,10 @@ static void bwd_layout(Cursor& c, int n, int64_t nnz, bool weighted, bool recomp
     if (w) *w = t;
 }
 
+// The recomputed forward takes the route ppr_matrix takes with the workspace
+// of ppr_matrix_workspace_fast, so that it gives the same bits.
+static size_t bwd_series(const ppr_csr* g) { return ppr_series_floats(g->n, g->n); }
+
 }  // namespace pprviz
 
 using namespace pprviz;
@@ -184,6 +188,7 @@ size_t ppr_backward_workspace(const ppr_csr* g, int recompute) {
     if (g == nullptr || g->n < 1 || g->nnz < 0) return 0;
     WsSize c;
     bwd_layout(c, g->n, g->nnz, g->weight != nullptr, recompute != 0, nullptr);
+    if (recompute && bwd_series(g) > 0) c.take<float>(bwd_series(g));
     return c.used;
 }
 
@@ -200,6 +205,7 @@ ppr_status ppr_matrix_backward(const ppr_csr* g, float alpha, int32_t T, const f
     BwdWs w;
     bwd_layout(cur, g->n, g->nnz, g->weight != nullptr, recompute, &w);
     if (ws == nullptr || cur.used > ws_bytes) return PPR_EWORKSPACE;
+    if (recompute && bwd_series(g) > 0) w.f.series = cur.take<float>(bwd_series(g));
     if (pending_error() != PPR_OK) return PPR_EHIP;
     if (g->nnz == 0) return PPR_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -6,6 +6,7 @@
 
 #include "common.hpp"
 #include "ppr_core.hpp"
+#include "ppr_dense.hpp"
 #include "ppr_mid.hpp"
 #include "ppr_stream.hpp"
 
@@ -29,7 +30,14 @@ struct PprWs {
     float* yb;
     double* part;
     int32_t* hist;
+    float* series;   // all-pairs series (ppr_series_floats), nullptr: not taken
 };
+
+// Floats of the all-pairs series for this call (0: it is never taken): every
+// node a source, a size of the resident range worth products.
+inline size_t ppr_series_floats(int n, int n_src) {
+    return res_cols_for(n) != 0 && n >= kDenseMinN && n_src == n ? (size_t)4 * n * n : 0;
+}
 
 template <typename Cursor>
 void ppr_ws_layout(Cursor& c, int n, int64_t nnz, bool weighted, int n_src, PprWs* w, bool with_stream = false) {

@@ -5,8 +5,9 @@
 #include <algorithm>
 #include <mutex>
 
-#include "ppr_core.hpp"
 #include "internal.hpp"
+#include "ppr_core.hpp"
+#include "ppr_dense.hpp"
 
 namespace pprviz {
 
@@ -343,7 +344,8 @@ void launch_res_layout(const int32_t* row_ptr, const int32_t* col_idx, const flo
 
 template <int COLS, bool WEIGHTED>
 __global__ __launch_bounds__(kResThreads) void ppr_resident_kernel(ResArgs a, int32_t n, int64_t nnz,
-                                                                 int32_t n_src, int32_t n_tgt) {
+                                                                 int32_t n_src, int32_t n_tgt, int32_t T,
+                                                                 int32_t m, int32_t r) {
     __shared__ ResLds L;
     TileTask t;
     t.n = n;
@@ -353,6 +355,9 @@ __global__ __launch_bounds__(kResThreads) void ppr_resident_kernel(ResArgs a, in
     t.base = 0;
     t.out_off = 0;
     t.ld = n_tgt;
+    t.T = T;
+    t.m = m;
+    t.r = r;
     res_graph_bases(0, 0, nnz, 0, n, t);
     res_tile<COLS, WEIGHTED>(t, a, L);
 }
@@ -364,14 +369,93 @@ void launch_degree(const int32_t* row_ptr, const float* weight, int64_t n, float
 }
 
 template <int COLS>
-static void launch_resident(bool weighted, const ResArgs& a, int n, int64_t nnz, int n_src, int n_tgt,
-                            hipStream_t s) {
+static void launch_resident(bool weighted, const ResArgs& a, int n, int64_t nnz, int n_src, int n_tgt, int T, int m,
+                            int r, hipStream_t s) {
     dim3 grid((n_src + COLS - 1) / COLS);
     if (weighted)
-        hipLaunchKernelGGL((ppr_resident_kernel<COLS, true>), grid, dim3(kResThreads), 0, s, a, n, nnz, n_src, n_tgt);
+        hipLaunchKernelGGL((ppr_resident_kernel<COLS, true>), grid, dim3(kResThreads), 0, s, a, n, nnz, n_src, n_tgt,
+                           T, m, r);
     else
         hipLaunchKernelGGL((ppr_resident_kernel<COLS, false>), grid, dim3(kResThreads), 0, s, a, n, nnz, n_src,
-                           n_tgt);
+                           n_tgt, T, m, r);
+}
+
+static void launch_resident_any(bool weighted, const ResArgs& a, int n, int64_t nnz, int n_src, int n_tgt, int T,
+                                int m, int r, hipStream_t s) {
+    switch (res_cols_for(n)) {
+        case 64: launch_resident<64>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, s); break;
+        case 32: launch_resident<32>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, s); break;
+        default: launch_resident<16>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, s); break;
+    }
+}
+
+// One product of the all-pairs series (ppr_dense.hpp), one 64-wide tile per
+// block: a single graph has too few 128-wide tiles to fill the chip (n = 2048:
+// 136 of them, 204 us a product; 528 64-wide ones, 136 us).
+constexpr int kSingleBT = 64;
+
+__global__ __launch_bounds__(kDenseThreads, 2) void ppr_product_kernel(const float* V, const float* Ym,
+                                                                     const float* W, const float* deg,
+                                                                     float alpha, int32_t n, float* out) {
+    __shared__ DenseLds<kSingleBT> L;
+    dense_product_tile<kSingleBT, false>(V, Ym, W, deg, nullptr, alpha, n, blockIdx.x, L, out);
+}
+
+// Outputs from Y_T, one block per source: pi_hat(s, t) = Y(s, t) d(t) / (1-alpha),
+// DPPR, and the FP64 residual over all nodes of the FP32 estimates.
+__global__ __launch_bounds__(256) void ppr_series_out_kernel(const float* __restrict__ Y,
+                                                             const float* __restrict__ deg,
+                                                             const float* __restrict__ invd, float alpha, int32_t n,
+                                                             const int32_t* __restrict__ src,
+                                                             const int32_t* __restrict__ tgt, int32_t n_tgt,
+                                                             float* __restrict__ ppr_out,
+                                                             float* __restrict__ dppr_out,
+                                                             double* __restrict__ resid) {
+    __shared__ double red[4];
+    const int i = blockIdx.x;
+    const int s = src ? src[i] : i;
+    const float* y = Y + (int64_t)s * n;
+    const float ds = deg[s];
+    for (int j = threadIdx.x; j < n_tgt; j += 256) {
+        const int t = tgt ? tgt[j] : j;
+        const float x = (float)((double)y[t] * dense_unscale(invd[t], alpha));
+        if (ppr_out) ppr_out[(int64_t)i * n_tgt + j] = x;
+        if (dppr_out) dppr_out[(int64_t)i * n_tgt + j] = x * ds;
+    }
+    double sum = 0.0;
+    for (int v = threadIdx.x; v < n; v += 256) sum += (double)(float)((double)y[v] * dense_unscale(invd[v], alpha));
+    sum = wave_sum(sum);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) resid[i] = 1.0 - ((red[0] + red[1]) + (red[2] + red[3]));
+}
+
+// All pairs by the series: a short run of pushes from every node, k products,
+// outputs.  buf: 4 n^2 floats (V, Y_m, and two that the W_p alternate between).
+static void ppr_series(const ppr_csr* g, const DensePlan& p, const int32_t* src, const int32_t* tgt, int32_t n_tgt,
+                       ResArgs a, const float* invd, float* ppr_out, float* dppr_out, double* resid, float* buf,
+                       hipStream_t s) {
+    const int n = g->n;
+    const int64_t n2 = (int64_t)n * n;
+    float* w[2] = {buf + 2 * n2, buf + 3 * n2};
+    a.src = nullptr;
+    a.tgt = nullptr;
+    a.ppr_out = a.dppr_out = nullptr;
+    a.resid = nullptr;
+    a.vd = buf;
+    a.ym = buf + n2;
+    a.yr = w[0];
+    launch_resident_any(g->weight != nullptr, a, n, g->nnz, n, n, p.m + 1, p.m, p.r, s);
+    const float* from = p.r == p.m ? a.ym : w[0];
+    for (int i = 0; i < p.k; ++i) {
+        float* to = w[(i + 1) & 1];
+        const dim3 grid((unsigned)dense_tiles(n, kSingleBT));
+        hipLaunchKernelGGL(ppr_product_kernel, grid, dim3(kDenseThreads), 0, s, a.vd, a.ym, from, a.deg, a.alpha, n,
+                           to);
+        from = to;
+    }
+    hipLaunchKernelGGL(ppr_series_out_kernel, dim3(n), dim3(256), 0, s, from, a.deg, invd, a.alpha, n, src, tgt,
+                       n_tgt, ppr_out, dppr_out, resid);
 }
 
 ppr_status validate_csr(const ppr_csr* g) {
@@ -383,9 +467,10 @@ ppr_status validate_csr(const ppr_csr* g) {
 bool use_resident(int n) { return res_cols_for(n) != 0; }
 
 // T pushes from every source; deg/invd must already hold the degrees.  Three
-// kernels by size: the LDS-resident tile (n <= 2304), the mid-size kernel
-// with the iterate columns in LDS (n <= 40831), and the streaming SpMM with
-// the iterate in HBM.
+// kernels by size: the LDS-resident tile (n <= 2304; all pairs by fewer pushes
+// and dense products where that is faster and the workspace has room for it),
+// the mid-size kernel with the iterate columns in LDS (n <= 40831), and the
+// streaming SpMM with the iterate in HBM.
 void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int32_t* tgt, int32_t n_tgt,
                  float alpha, int32_t T, float* ppr_out, float* dppr_out, const float* deg, const float* invd,
                  double* resid, const PprWs& w, hipStream_t s) {
@@ -401,16 +486,16 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
         a.src = src;
         a.tgt = tgt;
         a.alpha = alpha;
-        a.T = T;
         a.ppr_out = ppr_out;
         a.dppr_out = dppr_out;
         a.resid = resid;
-        const bool wt = g->weight != nullptr;
-        switch (res_cols_for(n)) {
-            case 64: launch_resident<64>(wt, a, n, g->nnz, n_src, n_tgt, s); break;
-            case 32: launch_resident<32>(wt, a, n, g->nnz, n_src, n_tgt, s); break;
-            default: launch_resident<16>(wt, a, n, g->nnz, n_src, n_tgt, s); break;
-        }
+        a.yr = a.ym = a.vd = nullptr;
+        // every node a source (sources are distinct): all pairs
+        const DensePlan p = dense_plan(n, g->nnz, n_src == n && w.series != nullptr ? T : 0);
+        if (p.k > 0)
+            ppr_series(g, p, src, tgt, n_tgt, a, invd, ppr_out, dppr_out, w.resid, w.series, s);
+        else
+            launch_resident_any(g->weight != nullptr, a, n, g->nnz, n_src, n_tgt, T, 0, 0, s);
     } else if (mid_cols_for(n) != 0) {
         mid_forward(g, src, n_src, tgt, n_tgt, alpha, T, ppr_out, dppr_out, deg, invd, resid, w.mid, s);
     } else {
@@ -438,11 +523,14 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
 
 // Scratch memory of ppr_matrix_noalloc: a fixed device array, one copy per
 // GPU, that replaces the caller's workspace for callers that cannot allocate
-// (graph capture, tight serving loops).  Host code never passes the array's
+// (graph capture, tight serving loops): kScratchBytes for the workspace
+// proper, then the buffers of the all-pairs series at the resident range's
+// largest size.  Host code never passes the array's
 // name to a kernel: scratch_address resolves it once per device, with that
 // device current, and keeps the device address.
 constexpr size_t kScratchBytes = size_t(8) << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchSeriesBytes = size_t(4) * Res<16>::NMAX * Res<16>::NMAX * sizeof(float);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSeriesBytes];
 constexpr int kMaxDevices = 64;
 
 static ppr_status scratch_address(hipStream_t s, void** out) {
@@ -493,6 +581,13 @@ static ppr_status ppr_matrix_impl(const ppr_csr* g, const int32_t* src, int32_t 
     PprWs w;
     ppr_ws_layout(cur, g->n, g->nnz, g->weight != nullptr, n_src, &w);
     if (ws == nullptr || cur.used > ws_bytes) return scratch_ws ? PPR_EUNSUPPORTED : PPR_EWORKSPACE;
+    // a workspace with room for the all-pairs series takes it
+    const size_t series = ppr_series_floats(g->n, n_src);
+    if (scratch_ws) {
+        cur.used = kScratchBytes;
+        cur.cap = kScratchBytes + kScratchSeriesBytes;
+    }
+    w.series = series > 0 ? cur.take<float>(series) : nullptr;
     if (pending_error() != PPR_OK) return PPR_EHIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int n = g->n;
@@ -566,6 +661,16 @@ size_t ppr_matrix_workspace(const ppr_csr* g, int32_t n_src, int32_t n_tgt) {
     if (g == nullptr || g->n < 1 || n_src < 0) return 0;
     WsSize c;
     ppr_ws_layout(c, g->n, g->nnz, g->weight != nullptr, n_src, nullptr);
+    return c.used;
+}
+
+size_t ppr_matrix_workspace_fast(const ppr_csr* g, int32_t n_src, int32_t n_tgt) {
+    (void)n_tgt;
+    if (g == nullptr || g->n < 1 || n_src < 0) return 0;
+    WsSize c;
+    ppr_ws_layout(c, g->n, g->nnz, g->weight != nullptr, n_src, nullptr);
+    const size_t series = ppr_series_floats(g->n, n_src);
+    if (series > 0) c.take<float>(series);
     return c.used;
 }
 

@@ -121,6 +121,8 @@ struct TileTask {
     int64_t tbase;    // first slot-table entry of the graph
     int64_t cbase;    // first arc-copy entry of the graph
     int32_t cwords;   // arc-copy entries of the graph (res_arc_words)
+    int32_t T;        // pushes
+    int32_t m, r;     // series form (m > 0): T = m + 1, the iterates Y_r, Y_m and Y_{m+1} - Y_m go out
 };
 
 // Where graph g's slot table and arc copy start, for a graph whose nodes start
@@ -140,10 +142,12 @@ struct ResArgs {
     const int32_t* src;      // source local ids by source index, or nullptr (source i = node i)
     const int32_t* tgt;      // target local ids, or nullptr (targets = nodes 0..n_tgt-1)
     float alpha;
-    int32_t T;               // pushes
     float* ppr_out;          // nullable
     float* dppr_out;         // nullable
     double* resid;           // nullable, indexed by source index
+    float* yr;               // series form: Y_r, Y_m and Y_{m+1} - Y_m of every graph, [source][node] at
+    float* ym;               // out_off with ld columns (yr is not written when r == m)
+    float* vd;
 };
 
 // Broadcast lane J of every quad to the whole quad (DPP quad_perm [J,J,J,J]).
@@ -253,6 +257,30 @@ struct ResLds {
 
 constexpr int kBufFlags = 0x00020000;  // buffer resource word 3: 32-bit data, no swizzle
 
+// The tile's iterate, as LDS holds it, to rows t.s0 .. of out ([source][node]):
+// a lane reads 4 columns of one node with one 16-byte read and the wave stores
+// them as four 256-byte row pieces.  The wave's nodes lie one tile row apart,
+// so the reads of a 16-column tile conflict four ways; it is done three times
+// per series.
+template <int COLS>
+__device__ __forceinline__ void res_dump(const TileTask& t, const float* __restrict__ lds, float* out) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int n = __builtin_amdgcn_readfirstlane(t.n);
+    const int vch = (n + kWave - 1) / kWave;
+    const gptr<float> o = as_global_w(out) + t.out_off + (int64_t)t.s0 * t.ld;
+    for (int i = wave; i < vch * (COLS / 4); i += kResWaves) {
+        const int c = (i / vch) * 4;
+        const int v = (i % vch) * kWave + lane;
+        if (c >= t.ncols || v >= n) continue;
+        const float4 y = lds_load4(lds, (v * COLS + c) * 4);
+        o[(int64_t)c * t.ld + v] = y.x;
+        if (c + 1 < t.ncols) o[(int64_t)(c + 1) * t.ld + v] = y.y;
+        if (c + 2 < t.ncols) o[(int64_t)(c + 2) * t.ld + v] = y.z;
+        if (c + 3 < t.ncols) o[(int64_t)(c + 3) * t.ld + v] = y.w;
+    }
+}
+
 // All T pushes for one source tile with the tile's iterate resident in LDS.
 // Each lane keeps its rows' new values (4 columns per row) in registers
 // between the two barriers of a step.  Pass k of wave w sums group
@@ -317,7 +345,7 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
             const uint32_t bits = (e.z == msrc[0] ? 1u : 0u) | (e.z == msrc[1] ? 2u : 0u) |
                                   (e.z == msrc[2] ? 4u : 0u) | (e.z == msrc[3] ? 8u : 0u);
             if (k < 8) sbits_lo |= bits << (4 * k); else sbits_hi |= bits << (4 * (k - 8));
-            if (a.T >= 1)
+            if (t.T >= 1)
                 xr[k] = make_float4(bits & 1u ? alpha : 0.f, bits & 2u ? alpha : 0.f, bits & 4u ? alpha : 0.f,
                                     bits & 8u ? alpha : 0.f);
         }
@@ -333,7 +361,9 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
     }
     __syncthreads();
 
-    for (int it = 1; it < a.T; ++it) {
+    const bool series = t.m > 0;
+    if (series && t.r == 1) res_dump<COLS>(t, lds, a.yr);
+    for (int it = 1; it < t.T; ++it) {
         // Chunk-level software pipeline: the arcs of the next chunk (of this
         // pass, else the first of the next pass) are loaded while the current
         // chunk is summed, alternating between two register sets.  A lane's 4
@@ -406,6 +436,21 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
             }
         }
         __syncthreads();
+        if (series && it == t.T - 1) {
+            // the last push of a series: what it adds
+#pragma unroll
+            for (int k = 0; k < kResMaxK; ++k) {
+                if ((wave + kResWaves * k) * RPW < n) {
+                    const float4 y = lds_load4(lds, vaddr[k]);
+                    *reinterpret_cast<float4*>(reinterpret_cast<char*>(lds) + vaddr[k]) =
+                        make_float4(xr[k].x * sc[k] - y.x, xr[k].y * sc[k] - y.y, xr[k].z * sc[k] - y.z,
+                                    xr[k].w * sc[k] - y.w);
+                }
+            }
+            __syncthreads();
+            res_dump<COLS>(t, lds, a.vd);
+            break;
+        }
 #pragma unroll
         for (int k = 0; k < kResMaxK; ++k) {
             if ((wave + kResWaves * k) * RPW < n)
@@ -413,6 +458,13 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
                     make_float4(xr[k].x * sc[k], xr[k].y * sc[k], xr[k].z * sc[k], xr[k].w * sc[k]);
         }
         __syncthreads();
+        // Y_{it+1} is whole; the next push overwrites it only after its own
+        // first barrier
+        if (series && (it + 1 == t.r || it + 1 == t.m)) res_dump<COLS>(t, lds, it + 1 == t.m ? a.ym : a.yr);
+    }
+    if (series) {
+        __syncthreads();
+        return;
     }
 
     // Epilogue.  FP64 residual 1 - sum_v pi_hat(s, v): per-column partial sums
@@ -476,14 +528,6 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
     }
     __syncthreads();
 }
-
-// Slot table and arc copy of the resident tile in group layout (see above),
-// one block per graph; node_off == nullptr means a single graph of n_single
-// nodes.  Needs the inverse degrees.
-__global__ void res_layout_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-                                  const float* __restrict__ weight, const float* __restrict__ invd,
-                                  const int64_t* __restrict__ node_off, int32_t n_single, ResSlot* __restrict__ slots,
-                                  int32_t* __restrict__ arcs, float* __restrict__ warcs);
 
 // Degree and inverse degree of every node (the d of Definition def:pprdist is
 // the out-degree; with weights, the sum of the node's arc weights).

@@ -1,0 +1,114 @@
+// All-pairs PPR of a graph of the resident range by a short push series and a
+// few dense products.
+//
+// On an undirected graph Y_t(s, v) = (1-alpha) X_t(s, v) / d(v), the form the
+// resident tile keeps the iterate in, is symmetric in s and v (reversibility),
+// and with X_T = alpha sum_{t<T} Q^t the series can be cut into pieces:
+//     Y_{m+b} = Y_m + (Y_{m+1} - Y_m) D Y_b / (alpha (1-alpha)).
+// With V = Y_{m+1} - Y_m and T = k m + r (0 < r <= m), T pushes from every
+// source are m + 1 pushes, which give Y_r, Y_m and V, and then k products
+//     W_0 = Y_r,   W_{p+1} = Y_m + V D W_p / (alpha (1-alpha)),   W_k = Y_T.
+// V, Y_m and W_p are symmetric, so a product takes only the tiles on and above
+// the diagonal and stores each twice: n^3 FLOP on the matrix cores, against
+// nnz n additions per push.  The products carry the last (1-alpha)^m of the
+// mass (3% of it for m = 22), so their rounding hardly shows in the result.
+//
+// Measured (MI355X): 512 block-model subgraphs of 32 to 2048 nodes (T = 86),
+// PPR stage 43.7 ms by pushes alone, 25.3 ms as 14.6 ms of pushes and 10.7 ms
+// of products; one graph of 2048 nodes, all pairs, 2.01 ms against 0.53 ms of
+// pushes and three products.
+//
+// A 32x32 block on or above the diagonal is stored as computed, one below it
+// is the mirror image of its partner, whatever the tile size: the batch and
+// the single-graph path give the same bits.
+#pragma once
+
+#include "dense.hpp"
+#include "ppr_core.hpp"
+
+namespace pprviz {
+
+constexpr int kDenseMinN = 192;   // below it a product's tiles are mostly padding and latency
+constexpr int kDenseMinT = 24;    // the pieces have at least 4 pushes
+constexpr int kDenseMaxT = 4096;  // keeps the cost comparison below 2^63
+constexpr int kDenseMaxK = 3;     // products
+constexpr int kDenseWideN = 512;  // batch: 128-wide tiles from this size on
+
+struct DensePlan {
+    int32_t k;  // products (0: all T pushes)
+    int32_t m;  // pushes behind Y_m
+    int32_t r;  // pushes behind W_0 = Y_r
+};
+
+// Number of products: the k with the least time, in hundredths of a push of
+// one arc from one source.  Measured in the batch: pushes run at 23e12
+// additions/s, products at 100 TFLOP/s, so n^3 FLOP cost what 0.22 n^2 / nnz
+// pushes do; writing the three matrices and the extra push behind V cost about
+// three pushes.  Integer arithmetic, so that host and device agree.
+__host__ __device__ inline DensePlan dense_plan(int n, int64_t nnz, int T) {
+    DensePlan best{0, T, 0};
+    if (n < kDenseMinN || n > Res<16>::NMAX || T < kDenseMinT || T > kDenseMaxT) return best;
+    int64_t cost = 90 * (int64_t)T * nnz;  // a tenth less than T pushes
+    for (int k = 1; k <= kDenseMaxK; ++k) {
+        const int m = (T + k) / (k + 1);
+        const int64_t c = 100 * (int64_t)(m + 4) * nnz + 22 * (int64_t)k * n * (n + 64);
+        if (c < cost) {
+            cost = c;
+            best = DensePlan{k, m, T - k * m};
+        }
+    }
+    return best;
+}
+
+__host__ __device__ inline int dense_bt(int n) { return n < kDenseWideN ? 64 : 128; }
+__host__ __device__ inline int64_t dense_tiles(int n, int bt) {
+    const int64_t nt = (n + bt - 1) / bt;
+    return nt * (nt + 1) / 2;
+}
+
+// Tile t of the upper triangle (row by row) -> (I, J), I <= J.
+__device__ __forceinline__ void dense_tile_ij(int64_t t, int nt, int& I, int& J) {
+    int i = 0;
+    while (t >= nt - i) {
+        t -= nt - i;
+        ++i;
+    }
+    I = i;
+    J = i + (int)t;
+}
+
+// X(s, v) from Y(s, v): over the FP32 scale (1-alpha)/d(v) the resident tile
+// multiplied by, in FP64, so that neither the scale's rounding nor the way
+// back adds to the result's.
+__device__ __forceinline__ double dense_unscale(float invd, float alpha) {
+    const float sc = (1.0f - alpha) * invd;
+    const double r = (double)__builtin_amdgcn_rcpf(sc);
+    const double r1 = r * (2.0 - (double)sc * r);  // two steps from 1 ulp of FP32
+    return r1 * (2.0 - (double)sc * r1);
+}
+
+// One tile of W_{p+1} (all n x n, row-major, ld = n).  FINAL: the result goes
+// out as DPPR, d(s) X(s, v) with X rounded to FP32 first, like ppr_matrix's.
+template <int BT, bool FINAL>
+__device__ __forceinline__ void dense_product_tile(const float* V, const float* Ym, const float* W,
+                                                   const float* deg, const float* invd, float alpha, int n, int64_t t,
+                                                   DenseLds<BT>& L, float* out) {
+    int I, J;
+    dense_tile_ij(t, (n + BT - 1) / BT, I, J);
+    const int i0 = I * BT, j0 = J * BT;
+    DenseTile<BT> c;
+    dense_tile<BT, 0>(V, n, W, n, deg, 1.0f / (alpha * (1.0f - alpha)), n, i0, j0, L, c);
+    dense_each<BT>(c, i0, j0, [&](int i, int j, float v) {
+        if (i >= n || j >= n || (i >> 5) > (j >> 5)) return;
+        const float y = as_global(Ym)[(int64_t)i * n + j] + v;
+        float a = y, b = y;
+        if (FINAL) {
+            a = (float)((double)y * dense_unscale(as_global(invd)[j], alpha)) * as_global(deg)[i];
+            b = (float)((double)y * dense_unscale(as_global(invd)[i], alpha)) * as_global(deg)[j];
+        }
+        as_global_w(out)[(int64_t)i * n + j] = a;
+        if ((i >> 5) < (j >> 5)) as_global_w(out)[(int64_t)j * n + i] = b;
+    });
+}
+
+}  // namespace pprviz

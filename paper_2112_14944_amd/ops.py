@@ -80,7 +80,7 @@ def ppr_matrix(g: Csr, src, tgt=None, alpha=0.15, tol=1e-6, max_iter=100000, wan
     else:
         n_tgt = g.n
     cg = g.c()
-    ws = _ws(L.lib().ppr_matrix_workspace(C.byref(cg), n_src, n_tgt), dev)
+    ws = _ws(L.lib().ppr_matrix_workspace_fast(C.byref(cg), n_src, n_tgt), dev)
     ppr = torch.empty((n_src, n_tgt), dtype=torch.float32, device=dev) if want_ppr else None
     dppr = torch.empty((n_src, n_tgt), dtype=torch.float32, device=dev) if want_dppr else None
     resid = np.zeros(max(n_src, 1), dtype=np.float64) if check_residual else None

@@ -61,3 +61,66 @@ def test_weight_gradient_adjoint(n, T):
     # sum of the terms' sizes), everything after it FP64
     assert ((got - want).norm() / want.norm()).item() <= 2e-5
 
+
+def _series_plan(n, nnz, T):
+    """The number of products and the pieces of the all-pairs series (the rule
+    of csrc/ppr_dense.hpp)."""
+    best, cost = (0, T, 0), 90 * T * nnz
+    if n < 192 or n > 2304 or T < 24 or T > 4096:
+        return best
+    for k in (1, 2, 3):
+        m = (T + k) // (k + 1)
+        c = 100 * (m + 4) * nnz + 22 * k * n * (n + 64)
+        if c < cost:
+            cost, best = c, (k, m, T - k * m)
+    return best
+
+
+# sizes around the smallest graph that takes products (192), the change from
+# 64- to 128-wide product tiles (512), the widths of the push tile (576, 1152)
+# and the largest (2304); degrees and T that give every number of products,
+# T = 24 and 25 the shortest series; and one that takes all pushes
+@pytest.mark.parametrize("n,degree,T,k", [(191, 30, 86, 0), (192, 30, 86, 3), (193, 5, 86, 2), (511, 20, 86, 3),
+                                          (512, 9, 86, 2), (513, 6, 86, 1), (577, 60, 24, 2), (640, 40, 25, 2),
+                                          (1153, 50, 87, 3), (2304, 60, 86, 2), (2304, 8, 86, 0), (700, 40, 142, 3)])
+def test_all_pairs_series(n, degree, T, k):
+    ops = get_ops()
+    g0 = synth.sbm(synth.equal_blocks(n, 4), min(1.0, 3.2 * degree / n), 0.27 * degree / n, 70 + n,
+                   weighted=(0.5, 2.0, 71 + n))
+    keep = (g0.eu != 9) & (g0.ev != 9)  # an isolated node
+    g = synth.build_graph(n, g0.eu[keep], g0.ev[keep], g0.weight[keep])
+    assert _series_plan(n, g.nnz, T)[0] == k, _series_plan(n, g.nnz, T)
+    csr = ops.Csr.from_graph(g, "cuda")
+    rng = np.random.default_rng(n)
+    src = rng.permutation(n)
+    tgt = rng.permutation(n)[: n // 2 + 1]
+    print(f"[series] n={n} nnz={g.nnz} T={T} products={k}", flush=True)
+    ppr, dppr, Tg, resid = ops.ppr_matrix(csr, src, tgt=tgt, tol=0.0, max_iter=T, check_residual=True)
+    assert Tg == T
+    _, d, Q, _, _ = _walk64(g)
+    pi = torch.zeros_like(Q)
+    for _ in range(T):
+        pi = ALPHA * torch.eye(n, dtype=torch.float64, device="cuda") + pi @ Q
+    s = torch.as_tensor(src, device="cuda").long()
+    t = torch.as_tensor(tgt, device="cuda").long()
+    want = pi[s][:, t]
+    # the package's bars: PPR 1e-6, DPPR 1e-6 max(1, d(s)), residual 2e-6
+    assert (ppr.double() - want).abs().max().item() <= 1e-6
+    assert ((dppr.double() - d[s][:, None] * want) / d[s].clamp(min=1.0)[:, None]).abs().max().item() <= 1e-6
+    assert np.abs(resid - (1.0 - pi[s].sum(1)).cpu().numpy()).max() <= 2e-6
+    # the route without the series' buffers (the smaller workspace) agrees
+    from paper_2112_14944_amd import _lib as L
+    import ctypes as C
+    cg = csr.c()
+    lib = L.lib()
+    small = torch.empty(lib.ppr_matrix_workspace(C.byref(cg), n, n), dtype=torch.uint8, device="cuda")
+    assert lib.ppr_matrix_workspace_fast(C.byref(cg), n, n) >= small.numel() + (16 * n * n if n >= 192 else 0)
+    out = torch.empty((n, n), device="cuda")
+    si = s.to(torch.int32).contiguous()
+    st = lib.ppr_matrix(C.byref(cg), C.c_void_p(si.data_ptr()), n, None, n, ALPHA, 0.0, T, C.c_void_p(out.data_ptr()),
+                        None, None, None, C.c_void_p(small.data_ptr()), small.numel(),
+                        C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0
+    # either route rounds each value about T times by u = 2^-24, at random:
+    # 1e-6 of the matrix's norm bounds the difference with room to spare
+    assert ((out[:, t] - ppr).norm() / ppr.norm()).item() <= 1e-6
