@@ -134,6 +134,22 @@ __device__ __forceinline__ int strip_class(int k, int T, int S, int J0) {
     return (kStripGroup * kStripBlocks * kPT * kPT - pairs) / 64;
 }
 
+// Exclusive prefix sum over the block's threads.
+template <typename T>
+__device__ __forceinline__ T plan_scan(T v, T* tmp) {
+    const int tid = threadIdx.x;
+    __syncthreads();
+    tmp[tid] = v;
+    __syncthreads();
+    for (int o = 1; o < kPlanThreads; o <<= 1) {
+        const T x = tid >= o ? tmp[tid - o] : 0;
+        __syncthreads();
+        tmp[tid] += x;
+        __syncthreads();
+    }
+    return tmp[tid] - v;
+}
+
 __global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t* __restrict__ node_off,
                                                                   const int32_t* __restrict__ row_ptr, int32_t G,
                                                                   int32_t series_T, BatchPlan p) {
@@ -145,11 +161,14 @@ __global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t*
     for (int g = tid; g < G; g += kPlanThreads) atomicAdd(&hist[min(graph_n(node_off, g), kBatchMaxN + 1)], 1);
     __syncthreads();
     // exclusive prefix over sizes in descending order: start[size]
-    if (tid == 0) {
-        int32_t run = 0;
-        for (int sz = kBatchMaxN + 1; sz >= 0; --sz) {
-            const int32_t c = hist[sz];
-            hist[sz] = run;
+    {
+        constexpr int kPer = (kBatchMaxN + 2 + kPlanThreads - 1) / kPlanThreads;
+        int64_t loc = 0;
+        for (int q = tid * kPer; q < min(kBatchMaxN + 2, (tid + 1) * kPer); ++q) loc += hist[kBatchMaxN + 1 - q];
+        int64_t run = plan_scan(loc, scan_tmp);
+        for (int q = tid * kPer; q < min(kBatchMaxN + 2, (tid + 1) * kPer); ++q) {
+            const int32_t c = hist[kBatchMaxN + 1 - q];
+            hist[kBatchMaxN + 1 - q] = (int32_t)run;
             run += c;
         }
     }
@@ -174,18 +193,7 @@ __global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t*
             return plan_count(which, graph_n(node_off, g), nnz, series_T);
         };
         for (int i = a; i < b; ++i) loc += count(i);
-        scan_tmp[tid] = loc;
-        __syncthreads();
-        if (tid == 0) {
-            int64_t run = 0;
-            for (int i = 0; i < kPlanThreads; ++i) {
-                const int64_t c = scan_tmp[i];
-                scan_tmp[i] = run;
-                run += c;
-            }
-        }
-        __syncthreads();
-        int64_t run = scan_tmp[tid];
+        int64_t run = plan_scan(loc, scan_tmp);
         for (int i = a; i < b; ++i) {
             out[i] = run;
             run += count(i);
@@ -219,14 +227,8 @@ __global__ __launch_bounds__(kPlanThreads) void batch_plan_kernel(const int64_t*
         }
     }
     __syncthreads();
-    if (tid == 0) {
-        int32_t run = 0;
-        for (int c = 0; c < kStripClasses; ++c) {
-            const int32_t n = scls[c];
-            scls[c] = run;
-            run += n;
-        }
-    }
+    static_assert(kStripClasses == kPlanThreads, "one class per thread");
+    scls[tid] = (int32_t)plan_scan<int64_t>(scls[tid], scan_tmp);
     __syncthreads();
     for (int g = tid; g < G; g += kPlanThreads) {
         const int k = graph_n(node_off, g);
@@ -568,7 +570,7 @@ __global__ void copy_kernel(const float* __restrict__ a, float* __restrict__ b, 
 }
 
 struct BatchWs {
-    ResSlot* slots;  // resident-tile slot tables (res_layout_kernel)
+    ResSlot* slots;  // resident-tile slot tables (res_sort_kernel)
     int32_t* col_r;  // arc copies in group layout
     int32_t* sorted_r;  // arcs grouped by LDS bank class (layout staging)
     float* deg;

@@ -29,27 +29,37 @@ __global__ void degree_kernel(const int32_t* __restrict__ row_ptr, const float* 
 }
 
 // Slot table and arc copy of the resident tile (group layout, see
-// ppr_core.hpp), one block per graph.
+// ppr_core.hpp), in two kernels.
+// res_sort_kernel, one block per graph:
 //  1. Rows sorted by degree, longest first, ties by row id (bitonic sort of
 //     4096 keys in LDS; a graph of the resident tile has at most 2304 rows).
 //  2. Group g's length: its longest row (at least 1: a row without arcs gets
 //     its self arc) in 8-arc halves; chunk offsets by a prefix sum in sorted
-//     order.
+//     order; the slot table.
+// res_deal_kernel, one block per four groups:
 //  3. Arcs are dealt by LDS bank class.  One LDS cycle of the tile's
 //     16-byte reads serves M rows at once (M = 4, 2, 1 for 16, 32, 64
 //     columns: 64 bytes of each of 4 rows, 128 of 2, 256 of 1;
 //     res_conflict_set names them), and row u starts in bank class u mod M.
-//     One thread takes such a set of M rows and fills their positions m = 0,
-//     1, ... together: each row takes, among the classes no other row has
+//     Each lane first groups the arcs of one row by class.  Then one lane
+//     takes such a set of M rows and fills their positions m = 0, 1, ...
+//     together: each row takes, among the classes no other row has
 //     taken at m, the one it holds most arcs of; a row with no such arc pads
 //     with the zero row of a free class (the tile has one zero row per class)
 //     as long as it can still fit its arcs, and otherwise takes a
 //     conflicting class.  Only the order of each row's arcs changes (and
-//     with it the order of the FP32 sum).  The copy holds each arc's LDS byte
+//     with it the order of the FP32 sum).  The deal notes where an arc is to
+//     be found, so that nothing it does waits for memory; all lanes then put
+//     the arcs themselves in place.  The copy holds each arc's LDS byte
 //     offset in the tile, (u - first node) * 4 COLS, not its node id.
 // A graph whose padded groups exceed its reserved region (possible only with
 // repeated arcs, when a row is longer than n) gets one half chunk per row
 // holding the row's own offset and a NaN scale, so that its outputs are NaN.
+//
+// Bound: latency.  One block per graph for all of it left a graph's rows to
+// 256 threads, each with its own chain of dependent loads (n = 2048, 1.3e5
+// arcs: 1190 us, more than its push series); with four groups per block
+// 182 us (28 the sort, 154 the deal).
 // The rows of a group whose LDS reads are served in the same cycles.  A
 // 16-byte LDS read by a wave is served 16 lanes at a time, lanes grouped by
 // lane bit 5 and the parity of lane bits 2..4 (a probe of the patterns
@@ -88,98 +98,99 @@ struct ResDealSet {
     int64_t base;
     bool over;      // NaN layout: each row holds only its own offset
     const int32_t* row_ptr;
-    const int32_t* sorted;  // each row's arcs as LDS offsets, grouped by class (CSR order within a class)
-    const float* wsorted;   // their weights, or nullptr
-    const int32_t (*cstart)[4];  // per row: first arc of each class within its group of sorted
+    const int32_t (*cstart)[4];  // per row of the block: where its arcs of each class start in the grouped copy
+    int row0;                    // the group's first row in cstart
 };
 
 // Fills the set's rows position by position.  At position m the rows choose
 // in the order m, m+1, ... (mod M); each takes the free class it holds most
-// arcs of, pads with the zero row of a free class when it has none and can
-// still fit its arcs, and otherwise takes its largest class (a conflict).
-// Rows without arcs hold their own offset first; v[i] < 0 marks a dummy slot.
+// arcs of (the lowest such class), pads with the zero row of a free class when
+// it has none and can still fit its arcs, and otherwise takes its largest
+// class (a conflict).  Rows without arcs hold their own offset first; v[i] < 0
+// marks a dummy slot.  The choice is arithmetic on keys 4 count + 3 - class,
+// without branches: the lanes of a wave hold rows of different lengths, and
+// branching cost each of them every path.
 template <int M>
 __device__ __forceinline__ void res_deal_set(const ResDealSet& d, const int rr[4], const int v[4]) {
     auto at = [&](int m) { return (int64_t)(m >> 4) * 16 * d.GW + (m & 15); };
-    auto zero_row = [&](int c) { return (d.n + (((c - d.n) % M) + M) % M) * d.stride; };
+    int zero[M];  // offset of each class's zero row
+#pragma unroll
+    for (int c = 0; c < M; ++c) zero[c] = (d.n + (((c - d.n) % M) + M) % M) * d.stride;
     auto put = [&](int i, int m, int off, float w) {
         d.ca[16 * rr[i] + at(m)] = off;
         if (d.wa) d.wa[16 * rr[i] + at(m)] = w;
     };
-    int cnt[M][M], cur[M][M], rem[M], re[M];
-    bool fixed[M];  // rows written outside the deal (own offset first, or dummies)
+    int cnt[M][M], end[M][M], rem[M];  // arcs left per class, one past the class's last arc, arcs left
+    bool fixed[M];                     // rows written outside the deal (own offset first)
 #pragma unroll
     for (int i = 0; i < M; ++i) {
         rem[i] = 0;
-        re[i] = 0;
         fixed[i] = false;
 #pragma unroll
-        for (int c = 0; c < M; ++c) cnt[i][c] = cur[i][c] = 0;
+        for (int c = 0; c < M; ++c) cnt[i][c] = end[i][c] = 0;
         if (v[i] < 0) continue;
         const int rs = d.row_ptr[d.base + v[i]];
-        re[i] = d.row_ptr[d.base + v[i] + 1];
-        if (d.over || re[i] == rs) {
+        const int re = d.row_ptr[d.base + v[i] + 1];
+        if (d.over || re == rs) {
             put(i, 0, v[i] * d.stride, 1.f);
             for (int m = 1; m < d.words; ++m) put(i, m, d.n * d.stride, 0.f);
             fixed[i] = true;
             continue;
         }
-        rem[i] = re[i] - rs;
+        rem[i] = re - rs;
 #pragma unroll
         for (int c = 0; c < M; ++c) {
-            const int c0 = d.cstart[v[i]][c];
-            const int c1 = c + 1 < M ? d.cstart[v[i]][c + 1] : re[i] - rs;
+            const int c0 = d.cstart[d.row0 + rr[i]][c];
+            const int c1 = c + 1 < M ? d.cstart[d.row0 + rr[i]][c + 1] : re - rs;
             cnt[i][c] = c1 - c0;
-            cur[i][c] = rs + c0;
+            end[i][c] = rs + c1;
         }
     }
+    constexpr uint32_t kFull = (1u << M) - 1u;
     for (int mb = 0; mb < d.L; mb += M) {
 #pragma unroll
         for (int s = 0; s < M; ++s) {
             const int m = mb + s;
-            uint32_t taken = 0, placed = 0;
+            uint32_t taken = 0;
+            bool live[M];
+#pragma unroll
+            for (int i = 0; i < M; ++i) live[i] = rem[i] > 0;
 #pragma unroll
             for (int k = 0; k < M; ++k) {
                 const int i = (s + k) % M;
-                if (fixed[i] || rem[i] == 0) continue;
-                int pick = -1, pany = -1, pickv = 0, panyv = 0;
+                int any = 0, fre = 0;
 #pragma unroll
                 for (int c = 0; c < M; ++c) {
-                    const int x = cnt[i][c];
-                    if (x > panyv) {
-                        pany = c;
-                        panyv = x;
-                    }
-                    if (!(taken >> c & 1u) && x > pickv) {
-                        pick = c;
-                        pickv = x;
-                    }
+                    const int key = 4 * cnt[i][c] + 3 - c;
+                    any = max(any, key);
+                    fre = max(fre, (taken >> c & 1u) ? 0 : key);
                 }
-                placed |= 1u << i;
-                if (pick < 0 && rem[i] < d.L - m && taken != (1u << M) - 1u) {
-                    const int c = __builtin_ctz(~taken);
-                    taken |= 1u << c;
-                    put(i, m, zero_row(c), 0.f);
-                    continue;
-                }
-                if (pick < 0) pick = pany;
-                taken |= 1u << pick;
+                const bool has = fre >= 4;
+                const bool pad = !has && rem[i] < d.L - m && taken != kFull;
+                const int open = __builtin_ctz(~taken);
+                const int c = pad ? open : 3 - ((has ? fre : any) & 3);
+                // the arc's place in the grouped copy, as a negative number:
+                // the arcs are filled in afterwards
+                int off = pad ? zero[0] : cnt[i][0] - 1 - end[i][0];
 #pragma unroll
-                for (int c = 0; c < M; ++c) {
-                    if (c != pick) continue;
-                    const int e = cur[i][c]++;
-                    put(i, m, d.sorted[e], d.wsorted ? d.wsorted[e] : 0.f);
-                    --cnt[i][c];
-                }
-                --rem[i];
+                for (int q = 1; q < M; ++q) off = c == q ? (pad ? zero[q] : cnt[i][q] - 1 - end[i][q]) : off;
+                if (live[i]) put(i, m, off, 0.f);
+                taken |= live[i] ? 1u << c : 0u;
+                const int took = live[i] && !pad ? 1 : 0;
+                rem[i] -= took;
+#pragma unroll
+                for (int q = 0; q < M; ++q) cnt[i][q] -= c == q ? took : 0;
             }
             // rows already done, and dummy slots: zero rows of free classes
 #pragma unroll
             for (int i = 0; i < M; ++i) {
-                if (fixed[i] || (placed >> i & 1u)) continue;
-                const int c = taken == (1u << M) - 1u ? 0 : __builtin_ctz(~taken);
-                taken |= 1u << c;
-                put(i, m, zero_row(c), 0.f);
+                const bool idle = !live[i] && !fixed[i];
+                const int c = taken == kFull ? 0 : __builtin_ctz(~taken);
+                int off = zero[0];
+#pragma unroll
+                for (int q = 1; q < M; ++q) off = c == q ? zero[q] : off;
+                if (idle) put(i, m, off, 0.f);
+                taken |= idle ? 1u << c : 0u;
             }
         }
     }
@@ -191,33 +202,29 @@ __device__ __forceinline__ void res_deal_set(const ResDealSet& d, const int rr[4
     }
 }
 
-__global__ __launch_bounds__(256) void res_layout_kernel(const int32_t* __restrict__ row_ptr,
-                                                        const int32_t* __restrict__ col_idx,
-                                                        const float* __restrict__ weight,
-                                                        const float* __restrict__ invd,
-                                                        const int64_t* __restrict__ node_off, int32_t n_single,
-                                                        ResSlot* __restrict__ slots, int32_t* __restrict__ arcs,
-                                                        float* __restrict__ warcs, int32_t* __restrict__ sorted,
-                                                        float* __restrict__ wsorted) {
+constexpr int kResSortThreads = 512;
+
+__global__ __launch_bounds__(kResSortThreads) void res_sort_kernel(const int32_t* __restrict__ row_ptr,
+                                                                  const float* __restrict__ invd,
+                                                                  const int64_t* __restrict__ node_off,
+                                                                  int32_t n_single, ResSlot* __restrict__ slots) {
     constexpr int kMaxRows = 4096;
     __shared__ uint32_t key[kMaxRows];
-    __shared__ int32_t cstart[Res<16>::NMAX][4];
-    __shared__ int64_t goff[kResMaxGroups + 1];
+    __shared__ int64_t goff[256];  // group offsets; kResMaxGroups + 1 used
     __shared__ int32_t ghalves[kResMaxGroups];
+    static_assert(kResMaxGroups < 256, "the prefix sum below covers 256 groups");
     const int g = blockIdx.x;
     const int64_t base = node_off ? node_off[g] : 0;
     const int n = node_off ? (int)(node_off[g + 1] - base) : n_single;
     const int cols = n > 0 ? res_cols_for(n) : 0;
     if (cols == 0) return;  // larger graphs never use the resident tile
-    const int GW = 256 / cols;                            // group size, Res<cols>::RPW
-    const int M = cols == 16 ? 4 : (cols == 32 ? 2 : 1);  // bank classes = rows per LDS pass
-    const int stride = cols * 4;                          // LDS bytes per row
+    const int GW = 256 / cols;  // group size, Res<cols>::RPW
     TileTask tb;
     res_graph_bases(base, row_ptr[base], row_ptr[base + n], g, n, tb);
 
     int P = 1;
     while (P < n) P <<= 1;
-    for (int i = threadIdx.x; i < P; i += 256) {
+    for (int i = threadIdx.x; i < P; i += kResSortThreads) {
         if (i < n) {
             const int d = min(row_ptr[base + i + 1] - row_ptr[base + i], 4095);
             key[i] = ((uint32_t)(4095 - d) << 12) | (uint32_t)i;
@@ -229,72 +236,54 @@ __global__ __launch_bounds__(256) void res_layout_kernel(const int32_t* __restri
     // bitonic sort, ascending key = descending degree, ties by row id
     for (int k = 2; k <= P; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < P; i += 256) {
-                const int ixj = i ^ j;
-                if (ixj > i) {
-                    const uint32_t x = key[i], y = key[ixj];
-                    const bool up = (i & k) == 0;
-                    if ((x > y) == up) {
-                        key[i] = y;
-                        key[ixj] = x;
-                    }
+            for (int h = threadIdx.x; h < P / 2; h += kResSortThreads) {
+                const int i = ((h & ~(j - 1)) << 1) | (h & (j - 1));
+                const int ixj = i | j;
+                const uint32_t x = key[i], y = key[ixj];
+                const bool up = (i & k) == 0;
+                if ((x > y) == up) {
+                    key[i] = y;
+                    key[ixj] = x;
                 }
             }
             __syncthreads();
         }
     }
-    // each row's arcs as LDS offsets, grouped by bank class (CSR order within
-    // a class), and where each class starts
-    for (int v = threadIdx.x; v < n; v += 256) {
-        const int rs = row_ptr[base + v], re = row_ptr[base + v + 1];
-        int c0 = 0, c1 = 0, c2 = 0, c3 = 0;
-        for (int e = rs; e < re; ++e) {
-            const int c = (int)((col_idx[e] - base) & (M - 1));
-            c0 += c == 0;
-            c1 += c == 1;
-            c2 += c == 2;
-            c3 += c == 3;
-        }
-        int pos[4] = {rs, rs + c0, rs + c0 + c1, rs + c0 + c1 + c2};
-        cstart[v][0] = 0;
-        cstart[v][1] = c0;
-        cstart[v][2] = c0 + c1;
-        cstart[v][3] = c0 + c1 + c2;
-        for (int e = rs; e < re; ++e) {
-            const int u = (int)(col_idx[e] - base);
-            const int c = u & (M - 1);
-            const int at = c == 0 ? pos[0]++ : (c == 1 ? pos[1]++ : (c == 2 ? pos[2]++ : pos[3]++));
-            sorted[at] = u * stride;
-            if (wsorted) wsorted[at] = weight[e];
-        }
-    }
     const int ng = (n + GW - 1) / GW;
-    for (int gi = threadIdx.x; gi < ng; gi += 256) {
-        int dmax = 1;
-        for (int r = 0; r < GW; ++r) {
-            const int p = gi * GW + r;
-            if (p < n) {
-                const int64_t gv = base + (int)(key[p] & 4095u);
-                dmax = max(dmax, row_ptr[gv + 1] - row_ptr[gv]);
+    if (threadIdx.x < 256) {
+        const int gi = threadIdx.x;
+        int64_t words = 0;
+        if (gi < ng) {
+            int dmax = 1;
+            for (int r = 0; r < GW; ++r) {
+                const int p = gi * GW + r;
+                if (p < n) {
+                    const int64_t gv = base + (int)(key[p] & 4095u);
+                    dmax = max(dmax, row_ptr[gv + 1] - row_ptr[gv]);
+                }
             }
+            const int h = (int)(((int64_t)dmax + 7) / 8);
+            ghalves[gi] = h;
+            words = (int64_t)((h + 1) / 2) * 16 * GW;
         }
-        const int h = (int)(((int64_t)dmax + 7) / 8);
-        ghalves[gi] = h;
-        goff[gi + 1] = (int64_t)((h + 1) / 2) * 16 * GW;
+        goff[gi] = words;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        goff[0] = 0;
-        for (int gi = 0; gi < ng; ++gi) goff[gi + 1] += goff[gi];
+    // exclusive prefix sum of the groups' sizes
+    for (int o = 1; o < 256; o <<= 1) {
+        int64_t x = 0;
+        if (threadIdx.x < 256 && (int)threadIdx.x >= o) x = goff[threadIdx.x - o];
+        __syncthreads();
+        if (threadIdx.x < 256) goff[threadIdx.x] += x;
+        __syncthreads();
     }
-    __syncthreads();
-    const bool over = goff[ng] > (int64_t)tb.cwords;
+    const bool over = goff[ng - 1] > (int64_t)tb.cwords;
     // slot table
-    for (int p = threadIdx.x; p < ng * GW; p += 256) {
+    for (int p = threadIdx.x; p < ng * GW; p += kResSortThreads) {
         const int gi = p / GW;
         const int r = p - gi * GW;
         const int h = over ? 1 : ghalves[gi];
-        const int64_t o = over ? (int64_t)gi * 16 * GW + 16 * r : goff[gi] + 16 * r;
+        const int64_t o = (over ? (int64_t)gi * 16 * GW : (gi > 0 ? goff[gi - 1] : 0)) + 16 * r;
         int v = n;
         float iv = 0.f;
         if (p < n) {
@@ -303,43 +292,132 @@ __global__ __launch_bounds__(256) void res_layout_kernel(const int32_t* __restri
         }
         slots[tb.tbase + p] = ResSlot{(int32_t)o, h, v, iv};
     }
-    // arcs: one thread per set of M rows of a group whose reads share LDS
-    // cycles (4 sets per group)
-    for (int t = threadIdx.x; t < ng * 4; t += 256) {
-        const int gi = t >> 2;
+}
+
+constexpr int kResDealThreads = 256;
+constexpr int kResDealGroups = 4;                                                      // groups per block
+constexpr int kResDealBlocks = (kResMaxGroups + kResDealGroups - 1) / kResDealGroups;  // blocks per graph, at most
+
+__global__ __launch_bounds__(kResDealThreads) void res_deal_kernel(const int32_t* __restrict__ row_ptr,
+                                                      const int32_t* __restrict__ col_idx,
+                                                      const float* __restrict__ weight,
+                                                      const int64_t* __restrict__ node_off, int32_t n_single,
+                                                      const ResSlot* __restrict__ slots, int32_t* __restrict__ arcs,
+                                                      float* __restrict__ warcs, int32_t* sorted, float* wsorted) {
+    __shared__ int32_t cstart[kResDealGroups * Res<16>::RPW][4];
+    const int lane = threadIdx.x;
+    const int g = blockIdx.x / kResDealBlocks;
+    const int g0 = (blockIdx.x % kResDealBlocks) * kResDealGroups;
+    const int64_t base = node_off ? node_off[g] : 0;
+    const int n = node_off ? (int)(node_off[g + 1] - base) : n_single;
+    const int cols = n > 0 ? res_cols_for(n) : 0;
+    if (cols == 0) return;
+    const int GW = 256 / cols;
+    const int ng = (n + GW - 1) / GW;
+    if (g0 >= ng) return;
+    const int M = cols == 16 ? 4 : (cols == 32 ? 2 : 1);  // bank classes = rows per LDS pass
+    const int stride = cols * 4;                          // LDS bytes per row
+    TileTask tb;
+    res_graph_bases(base, row_ptr[base], row_ptr[base + n], g, n, tb);
+    const ResSlot* tab = slots + tb.tbase;
+    const float s0 = tab[0].invd;
+    const bool over = s0 != s0;
+    const int gn = min(kResDealGroups, ng - g0);
+    // each row's arcs as LDS offsets, grouped by bank class (CSR order within
+    // a class), and where each class starts
+    for (int q = lane; q < gn * GW; q += kResDealThreads) {
+        const int v = tab[g0 * GW + q].v;
+        if (v >= n || over) continue;
+        const int rs = row_ptr[base + v], re = row_ptr[base + v + 1];
+        int c0 = 0, c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll 8
+        for (int e = rs; e < re; ++e) {
+            const int c = (int)((col_idx[e] - base) & (M - 1));
+            c0 += c == 0;
+            c1 += c == 1;
+            c2 += c == 2;
+            c3 += c == 3;
+        }
+        int pos[4] = {rs, rs + c0, rs + c0 + c1, rs + c0 + c1 + c2};
+        cstart[q][0] = 0;
+        cstart[q][1] = c0;
+        cstart[q][2] = c0 + c1;
+        cstart[q][3] = c0 + c1 + c2;
+#pragma unroll 8
+        for (int e = rs; e < re; ++e) {
+            const int u = (int)(col_idx[e] - base);
+            const int c = u & (M - 1);
+            const int at = c == 0 ? pos[0]++ : (c == 1 ? pos[1]++ : (c == 2 ? pos[2]++ : pos[3]++));
+            sorted[at] = u * stride;
+            if (wsorted) wsorted[at] = weight[e];
+        }
+    }
+    __syncthreads();
+    // one lane per set of M rows of a group whose reads share LDS cycles (4
+    // sets per group)
+    if (lane < gn * 4) {
+        const int gi = g0 + (lane >> 2);
+        const ResSlot e = tab[gi * GW];
         ResDealSet d;
-        d.L = over ? 8 : ghalves[gi] * 8;
-        d.words = over ? 16 : (ghalves[gi] + 1) / 2 * 16;
-        d.ca = arcs + tb.cbase + (over ? (int64_t)gi * 16 * GW : goff[gi]);
-        d.wa = warcs ? warcs + tb.cbase + (over ? (int64_t)gi * 16 * GW : goff[gi]) : nullptr;
+        d.L = e.halves * 8;
+        d.words = (e.halves + 1) / 2 * 16;
+        d.ca = arcs + tb.cbase + e.off;
+        d.wa = warcs ? warcs + tb.cbase + e.off : nullptr;
         d.GW = GW;
         d.n = n;
         d.stride = stride;
         d.base = base;
         d.over = over;
         d.row_ptr = row_ptr;
-        d.sorted = sorted;
-        d.wsorted = weight ? wsorted : nullptr;
         d.cstart = cstart;
+        d.row0 = (lane >> 2) * GW;
         int rr[4];
-        res_conflict_set(M, t & 3, rr);
+        res_conflict_set(M, lane & 3, rr);
         int v[4];
+    #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int p = gi * GW + rr[i];
-            v[i] = (i < M && p < n) ? (int)(key[p] & 4095u) : -1;
+            v[i] = (i < M && p < n) ? tab[p].v : -1;
         }
         if (M == 4) res_deal_set<4>(d, rr, v);
         else if (M == 2) res_deal_set<2>(d, rr, v);
         else res_deal_set<1>(d, rr, v);
     }
+    __syncthreads();
+    // the arcs, where the deal put them
+    const int64_t w0 = tb.cbase + tab[g0 * GW].off;
+    const ResSlot le = tab[(g0 + gn - 1) * GW];
+    const int64_t w1 = tb.cbase + le.off + (int64_t)((le.halves + 1) / 2) * 16 * GW;
+    constexpr int kBatch = 8;  // loads in flight per lane
+    for (int64_t i0 = w0 + lane; i0 < w1; i0 += kBatch * kResDealThreads) {
+        int a[kBatch], x[kBatch];
+        float w[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int64_t i = i0 + j * kResDealThreads;
+            a[j] = i < w1 ? arcs[i] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            x[j] = a[j] < 0 ? sorted[-1 - a[j]] : 0;
+            w[j] = a[j] < 0 && warcs ? wsorted[-1 - a[j]] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            if (a[j] >= 0) continue;
+            arcs[i0 + j * kResDealThreads] = x[j];
+            if (warcs) warcs[i0 + j * kResDealThreads] = w[j];
+        }
+    }
 }
-
 
 void launch_res_layout(const int32_t* row_ptr, const int32_t* col_idx, const float* weight, const float* invd,
                        const int64_t* node_off, int32_t n_single, int32_t blocks, ResSlot* slots, int32_t* arcs,
                        float* warcs, int32_t* sorted, float* wsorted, hipStream_t s) {
-    hipLaunchKernelGGL(res_layout_kernel, dim3(blocks), dim3(256), 0, s, row_ptr, col_idx, weight, invd, node_off,
-                       n_single, slots, arcs, warcs, sorted, wsorted);
+    hipLaunchKernelGGL(res_sort_kernel, dim3(blocks), dim3(kResSortThreads), 0, s, row_ptr, invd, node_off, n_single,
+                       slots);
+    hipLaunchKernelGGL(res_deal_kernel, dim3(blocks * kResDealBlocks), dim3(kResDealThreads), 0, s, row_ptr, col_idx, weight,
+                       node_off, n_single, slots, arcs, warcs, sorted, wsorted);
 }
 
 template <int COLS, bool WEIGHTED>

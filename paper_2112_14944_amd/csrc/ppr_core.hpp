@@ -50,7 +50,7 @@ __host__ __device__ inline int res_cols_for(int n) {
     return n <= Res<64>::NMAX ? 64 : (n <= Res<32>::NMAX ? 32 : (n <= Res<16>::NMAX ? 16 : 0));
 }
 
-// Group layout of the resident tile (res_layout_kernel).  The slots of a
+// Group layout of the resident tile (res_sort_kernel).  The slots of a
 // graph are its rows in degree order, longest first; slots g*RPW .. g*RPW +
 // RPW - 1 form group g, the rows one wave sums side by side in one pass.
 // Every row of a group is padded (with the tile's zero row) to the length of
@@ -135,7 +135,7 @@ __host__ __device__ inline void res_graph_bases(int64_t base, int64_t e0, int64_
 }
 
 struct ResArgs {
-    const ResSlot* slots;    // per graph: slot table in group layout (res_layout_kernel)
+    const ResSlot* slots;    // per graph: slot table in group layout (res_sort_kernel)
     const int32_t* arcs;     // arc copy in group layout: LDS byte offset of each arc's neighbour row
     const float* warcs;      // arc weights in the same layout, or nullptr
     const float* deg;        // per global node: weighted degree d
