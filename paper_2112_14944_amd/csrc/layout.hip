@@ -53,15 +53,24 @@ __global__ __launch_bounds__(256) void pdist_backward_kernel(const float* __rest
     }
 }
 
+// One row sweep; returns the number of stress partials it writes.
 template <int MODE>
-static void launch_layout(const float* delta, int32_t k, const float* x, float* xout, double* part, float scale,
-                          float* gx, float* gd, hipStream_t s) {
-    const unsigned blocks = (unsigned)((k + kLayoutRowsPerBlock - 1) / kLayoutRowsPerBlock);
-    hipLaunchKernelGGL((layout_rows_kernel<MODE>), dim3(blocks), dim3(256), 0, s, delta, (int64_t)k, k,
-                       reinterpret_cast<const float2*>(x), reinterpret_cast<float2*>(xout), part, scale,
-                       reinterpret_cast<float2*>(gx), gd);
+static int64_t launch_layout(const float* delta, int32_t k, const float* x, float* xout, double* part, float scale,
+                             float* gx, float* gd, hipStream_t s) {
+    const LayoutSplit p = layout_split(k, MODE == kLayoutStepStress || MODE == kLayoutStress);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)p.blocks), dim3(kSplitThreads), 0, s, delta, k,
+                           reinterpret_cast<const float2*>(x), reinterpret_cast<float2*>(xout), part, scale,
+                           reinterpret_cast<float2*>(gx), gd, p.sl);
+    };
+    if (p.units == 4) go(layout_split_kernel<MODE, 4>);
+    else if (p.units == 2) go(layout_split_kernel<MODE, 2>);
+    else go(layout_split_kernel<MODE, 1>);
+    return p.blocks;
 }
 
+// Stress partials a workspace holds (one per 16 rows, at least what a sweep
+// writes).
 static unsigned layout_blocks(int32_t k) {
     return (unsigned)((k + kLayoutRowsPerBlock - 1) / kLayoutRowsPerBlock);
 }
@@ -103,8 +112,8 @@ ppr_status stress_eval(const float* delta, int32_t k, const float* x, double* st
     if (pending_error() != PPR_OK) return PPR_EHIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     double* part = static_cast<double*>(ws);
-    launch_layout<kLayoutStress>(delta, k, x, nullptr, part, 1.f, nullptr, nullptr, s);
-    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, part, (int64_t)layout_blocks(k), stress_out);
+    const int64_t m = launch_layout<kLayoutStress>(delta, k, x, nullptr, part, 1.f, nullptr, nullptr, s);
+    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, part, m, stress_out);
     return launch_status();
 }
 
@@ -116,9 +125,8 @@ ppr_status layout_step(const float* delta, int32_t k, const float* x_in, float* 
     hipStream_t s = static_cast<hipStream_t>(stream);
     double* part = static_cast<double*>(ws);
     if (stress_out) {
-        launch_layout<kLayoutStepStress>(delta, k, x_in, x_out, part, 1.f, nullptr, nullptr, s);
-        hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, part, (int64_t)layout_blocks(k),
-                           stress_out);
+        const int64_t m = launch_layout<kLayoutStepStress>(delta, k, x_in, x_out, part, 1.f, nullptr, nullptr, s);
+        hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, part, m, stress_out);
     } else {
         launch_layout<kLayoutStep>(delta, k, x_in, x_out, nullptr, 1.f, nullptr, nullptr, s);
     }

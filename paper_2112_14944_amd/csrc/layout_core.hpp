@@ -63,11 +63,13 @@ __device__ __forceinline__ void layout_pair(float Dv, bool off, float2 xi, float
     const float r2 = fmaf(dx, dx, fmaf(dy, dy, kMinSq));
     const float rs = __builtin_amdgcn_rsqf(r2);
     if (STEP) {
-        const float c = inv * rs;
-        ax = fmaf(w, xj.x, fmaf(c, dx, ax));
-        ay = fmaf(w, xj.y, fmaf(c, dy, ay));
+        const float g = fmaf(inv, rs, -w);
+        ax = fmaf(g, dx, ax);
+        ay = fmaf(g, dy, ay);
     }
     if (STRESS || GRAD) {
+        // no contraction: every mode gives dL/dX the same bits
+#pragma clang fp contract(off)
         const float d = r2 * rs;
         const float t = fmaf(-d, inv, 1.0f);
         if (STRESS) as = off ? fmaf(t, t, as) : as;
@@ -85,7 +87,9 @@ __device__ __forceinline__ void layout_pair(float Dv, bool off, float2 xi, float
 // coalesced and each X_j load serves 4 rows.
 //   step:   X+_i = (sum_j w X_j + c (X_i - X_j)) / sum_j w,
 //           w = Delta^-2, c = w Delta / d = Delta^-1 d^-1  (Jacobi sweep of
-//           L^w X = L^Y Y; a coincident pair adds only w X_j)
+//           L^w X = L^Y Y; a coincident pair adds only w X_j), taken as
+//           X_i + sum_j g (X_i - X_j) / sum_j w with g = c - w: a correction
+//           to X_i, whose rounding is that of the correction's size
 //   stress: sum_{j != i} (1 - d/Delta)^2, halved per unordered pair
 //   grad:   dL/dX_i = sum_j 2 w (d - Delta) (X_i - X_j)/d,
 //           dL/dDelta_ij = 2 (1 - d/Delta) d / Delta^2
@@ -166,7 +170,7 @@ __device__ __forceinline__ double layout_rows(const float* __restrict__ delta, i
             const float sy = wave_sum(ay[r]);
             if (STEP) {
                 const float sw = INV ? wsum[i] : wave_sum(aw[r]);
-                if (lane == 0) xout[i] = sw > 0.f ? make_float2(sx / sw, sy / sw) : xi[r];
+                if (lane == 0) xout[i] = sw > 0.f ? make_float2(xi[r].x + sx / sw, xi[r].y + sy / sw) : xi[r];
             } else if (gx && lane == 0) {
                 gx[i] = make_float2(scale * sx, scale * sy);
             }
@@ -176,21 +180,149 @@ __device__ __forceinline__ double layout_rows(const float* __restrict__ delta, i
     return 0.5 * st;
 }
 
-// One block = 16 rows (4 waves x 4 rows) of one k-node layout.
-template <int MODE>
-__global__ __launch_bounds__(256) void layout_rows_kernel(const float* __restrict__ delta, int64_t ld, int32_t k,
-                                                          const float2* __restrict__ x, float2* __restrict__ xout,
-                                                          double* __restrict__ part, float scale,
-                                                          float2* __restrict__ gx, float* __restrict__ gd) {
-    __shared__ double red[4];
-    const int wave = threadIdx.x >> 6;
-    const int row_begin = blockIdx.x * kLayoutRowsPerBlock + wave * kLayoutRowsPerWave;
-    const double st = layout_rows<MODE, false>(delta, ld, k, x, row_begin, xout, scale, gx, gd, nullptr);
-    if (MODE == kLayoutStepStress || MODE == kLayoutStress) {
-        if ((threadIdx.x & 63) == 0) red[wave] = st;
-        __syncthreads();
-        if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+// ---------------------------------------------------------------------------
+// Row sweep of one k-node layout (the formulas of layout_rows).  A row group
+// is 4 rows; S = 1 << sl of the block's 8 waves share it, each with every S-th
+// piece of U x 64 columns, and add their sums through LDS in wave order.
+//
+// Bound: latency below a few thousand nodes (Delta fits the caches, and a wave
+// that walks all columns alone waits for one load after another), the Delta
+// stream above.  The split gives a sweep about 4096 waves (4 per SIMD) where
+// the rows alone would give k / 4: k = 1999 16.9 us per sweep with one wave
+// per row group, 6.5 us with eight; k = 500 7.1 us and 3.9 us.  From 16384
+// nodes on a row group has a wave of its own.  All loads of a piece (4 U Delta
+// values, U positions) go out before its arithmetic, columns past k through a
+// clamped address.
+constexpr int kSplitWaves = 8;
+constexpr int kSplitThreads = kSplitWaves * kWave;
+
+// Sum over the wave's lanes, in lane 63 (DPP row shifts and row broadcasts).
+__device__ __forceinline__ float wave_sum_last(float v) {
+#define PPRVIZ_DPP_ADD(CTRL, ROWS) \
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
+    PPRVIZ_DPP_ADD(0x111, 0xf)  // row_shr:1
+    PPRVIZ_DPP_ADD(0x112, 0xf)  // row_shr:2
+    PPRVIZ_DPP_ADD(0x114, 0xf)  // row_shr:4
+    PPRVIZ_DPP_ADD(0x118, 0xf)  // row_shr:8
+    PPRVIZ_DPP_ADD(0x142, 0xa)  // row_bcast:15 into rows 1 and 3
+    PPRVIZ_DPP_ADD(0x143, 0xc)  // row_bcast:31 into rows 2 and 3
+#undef PPRVIZ_DPP_ADD
+    return v;
+}
+
+template <int MODE, int U>
+__global__ __launch_bounds__(kSplitThreads) void layout_split_kernel(const float* __restrict__ delta, int32_t k,
+                                                                   const float2* __restrict__ x,
+                                                                   float2* __restrict__ xout,
+                                                                   double* __restrict__ part, float scale,
+                                                                   float2* __restrict__ gx, float* __restrict__ gd,
+                                                                   int32_t sl) {
+    constexpr int R = kLayoutRowsPerWave;
+    constexpr bool STEP = (MODE == kLayoutStep || MODE == kLayoutStepStress);
+    constexpr bool STRESS = (MODE == kLayoutStepStress || MODE == kLayoutStress);
+    constexpr bool GRAD = (MODE == kLayoutGradX || MODE == kLayoutGradBoth);
+    __shared__ float sums[kSplitWaves][R][3];
+    __shared__ double red[kSplitWaves];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int S = 1 << sl;
+    const int row0 = ((int)blockIdx.x * (kSplitWaves >> sl) + (wave >> sl)) * R;
+    float2 xi[R];
+    const float* drow[R];
+    float ax[R], ay[R], aw[R], as[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = min(row0 + r, k - 1);  // rows past k repeat the last one; nothing of them is stored
+        xi[r] = x[i];
+        drow[r] = delta + (int64_t)i * k;
+        ax[r] = ay[r] = aw[r] = as[r] = 0.f;
     }
+    auto piece = [&](int c0, bool full) {
+        float2 xv[U];
+        float dv[U][R];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = full ? c0 + u * kWave + lane : min(c0 + u * kWave + lane, k - 1);
+            xv[u] = x[j];
+#pragma unroll
+            for (int r = 0; r < R; ++r) dv[u][r] = drow[r][j];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = c0 + u * kWave + lane;
+            const bool in = full || j < k;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float g = 0.f;
+                layout_pair<MODE, false>(in ? dv[u][r] : 1.0f, in && j != row0 + r, xi[r], xv[u], ax[r], ay[r], aw[r],
+                                         as[r], scale, &g);
+                if (MODE == kLayoutGradBoth && in && row0 + r < k) gd[(int64_t)(row0 + r) * k + j] = g;
+            }
+        }
+    };
+    if (row0 < k) {
+        int c0 = (wave & (S - 1)) * (U * kWave);
+        for (; c0 + U * kWave <= k; c0 += S * U * kWave) piece(c0, true);
+        if (c0 < k) piece(c0, false);
+    }
+    if (STEP || GRAD) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float tx = wave_sum_last(ax[r]);
+            const float ty = wave_sum_last(ay[r]);
+            const float tw = STEP ? wave_sum_last(aw[r]) : 0.f;
+            if (lane == 63) {
+                sums[wave][r][0] = tx;
+                sums[wave][r][1] = ty;
+                sums[wave][r][2] = tw;
+            }
+        }
+    }
+    if (STRESS) {
+        double st = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) st += row0 + r < k ? (double)as[r] : 0.0;
+        st = wave_sum(st);
+        if (lane == 0) red[wave] = st;
+    }
+    __syncthreads();
+    if (STRESS && threadIdx.x == 0) {
+        double st = 0.0;
+        for (int w = 0; w < kSplitWaves; ++w) st += red[w];
+        part[blockIdx.x] = 0.5 * st;
+    }
+    // one thread per row adds its waves' sums
+    const int rows = (kSplitWaves >> sl) * R;
+    const int i = (int)blockIdx.x * rows + (int)threadIdx.x;
+    if ((STEP || GRAD) && (int)threadIdx.x < rows && i < k) {
+        const int w0 = (threadIdx.x / R) << sl, r = threadIdx.x % R;
+        float sx = 0.f, sy = 0.f, sw = 0.f;
+        for (int w = w0; w < w0 + S; ++w) {
+            sx += sums[w][r][0];
+            sy += sums[w][r][1];
+            sw += sums[w][r][2];
+        }
+        if (STEP) xout[i] = sw > 0.f ? make_float2(x[i].x + sx / sw, x[i].y + sy / sw) : x[i];
+        else if (gx) gx[i] = make_float2(scale * sx, scale * sy);
+    }
+}
+
+// Waves per row group (as a power of two) and 64-column units per piece: as
+// many waves as bring the sweep to 4096, at most 8 and no more than there are
+// units of columns.  A sweep that writes stress partials stops at two waves
+// per group: its blocks then cover at least the 16 rows a workspace holds a
+// partial for.
+struct LayoutSplit {
+    int sl, units, blocks;
+};
+inline LayoutSplit layout_split(int32_t k, bool stress) {
+    const int64_t groups = ((int64_t)k + kLayoutRowsPerWave - 1) / kLayoutRowsPerWave;
+    const int units = (k + kWave - 1) / kWave;
+    int sl = 0;
+    while (sl < (stress ? 1 : 3) && (groups << (sl + 1)) <= 4096 && (2 << sl) <= units) ++sl;
+    const int per = (units + (1 << sl) - 1) >> sl;
+    const int64_t gpb = kSplitWaves >> sl;
+    return LayoutSplit{sl, per >= 4 ? 4 : (per >= 2 ? 2 : 1), (int)((groups + gpb - 1) / gpb)};
 }
 
 // ---------------------------------------------------------------------------
