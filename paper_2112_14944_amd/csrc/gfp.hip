@@ -41,7 +41,6 @@
 // the device, and overwrites their columns with the backward rounds.
 #include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "internal.hpp"
 
@@ -54,8 +53,12 @@ constexpr int kGfpInfo = 4;      // [0] bad leaf lists, [1] largest leaf set, [2
 // Rows with more arcs than this are gathered by a whole wave (8 lane groups
 // on one row) instead of one 8-lane group: the longest row then takes 64
 // arcs per pass instead of 8, which keeps it from outlasting the rest of a
-// round.
+// round.  On a grid that is resident at once a round lasts as long as its
+// longest row, 8 arcs per load latency, and the limit is lower (20000 nodes,
+// 4e5 arcs: 26.5 us per round at 256 arcs, 12 us at 32); on larger grids
+// whole waves on short rows would leave lanes idle.
 constexpr int kGfpWideDeg = 256;
+constexpr int kGfpWideDegSmall = 32;
 static_assert(kGfpWideDeg + 2 <= kDegKeys, "wide rows must have degree classes of their own");
 // A block whose pushing rows hold more arcs than this, or more than half of
 // the block's arcs, in a round is over the mark cap: it writes no receive
@@ -156,11 +159,12 @@ __global__ void gfp_check_idx_kernel(const int32_t* __restrict__ leaf_idx, int64
     }
 }
 
-// Rows with more than kGfpWideDeg arcs: after the scatter of the degree
-// order, hist[c] is the end of class c (classes run from the largest degree
-// down), so the end of the class of degree kGfpWideDeg + 1 counts them.
-__global__ void gfp_wide_count_kernel(const int32_t* __restrict__ hist, int32_t* __restrict__ info) {
-    info[2] = hist[kDegKeys - 2 - kGfpWideDeg];
+// Rows with more than wide_deg arcs: after the scatter of the degree order,
+// hist[c] is the end of class c (classes run from the largest degree down), so
+// the end of the class of degree wide_deg + 1 counts them.
+__global__ void gfp_wide_count_kernel(const int32_t* __restrict__ hist, int32_t wide_deg,
+                                      int32_t* __restrict__ info) {
+    info[2] = hist[kDegKeys - 2 - wide_deg];
 }
 
 // Initial residues of column c, supernode i = col_set[c] (c itself when
@@ -303,7 +307,7 @@ struct GfpRound {
     int32_t* over;          // over[t] = 1 when some block of round t was over the mark cap
     int32_t* sparse;        // sparse[t] = 1 when some block of round t pushed along < 7/8 of its arcs
     int32_t n;
-    int32_t wide;           // rows 0 .. wide-1 of the degree order have > kGfpWideDeg arcs
+    int32_t wide;           // rows 0 .. wide-1 of the degree order are wide
     int32_t wide_blocks;    // blocks of 4 wide rows (one per wave), ahead of the rest
     float alpha;
     float r_max;
@@ -372,10 +376,10 @@ __global__ __launch_bounds__(256) void gfp_round_kernel(GfpRound a, StreamGrid g
             const_cast<float*>(a.send_in + slab_off), 0, (int)slab_bytes, 0x00020000);
         if (wide) {
             if (flagless)
-                acc = slab_gather<WEIGHTED, false, kWave>(rin, a.col_idx, a.weight, rs + kSlabVec * grp,
+                acc = slab_gather<WEIGHTED, false, kWave, !MARKS>(rin, a.col_idx, a.weight, rs + kSlabVec * grp,
                                                           max(dg - kSlabVec * grp, 0), lane, qoff);
             else
-                acc = slab_gather<WEIGHTED, true, kWave>(rin, a.col_idx, a.weight, rs + kSlabVec * grp,
+                acc = slab_gather<WEIGHTED, true, kWave, !MARKS>(rin, a.col_idx, a.weight, rs + kSlabVec * grp,
                                                          max(dg - kSlabVec * grp, 0), lane, qoff,
                                                          a.flag_in + flag_off, &got);
             // add the 8 groups' sums (a fixed tree) into every group
@@ -388,9 +392,9 @@ __global__ __launch_bounds__(256) void gfp_round_kernel(GfpRound a, StreamGrid g
                 got |= __shfl_xor(got, o, kWave);
             }
         } else if (flagless) {
-            acc = slab_gather<WEIGHTED, false>(rin, a.col_idx, a.weight, rs, dg, lane, qoff);
+            acc = slab_gather<WEIGHTED, false, kSlabVec, !MARKS>(rin, a.col_idx, a.weight, rs, dg, lane, qoff);
         } else {
-            acc = slab_gather<WEIGHTED, true>(rin, a.col_idx, a.weight, rs, dg, lane, qoff, a.flag_in + flag_off,
+            acc = slab_gather<WEIGHTED, true, kSlabVec, !MARKS>(rin, a.col_idx, a.weight, rs, dg, lane, qoff, a.flag_in + flag_off,
                                               &got);
         }
     }
@@ -681,11 +685,12 @@ ppr_status gfp_prepare(const GfpArgs& A, const GfpWs& w, const int32_t* targets,
         hipLaunchKernelGGL(gbp_columns_kernel, dim3((unsigned)((n_targets + 255) / 256)), dim3(256), 0, s, targets,
                            rb_max, n_targets, A.k, w.col_set, w.th_col, w.info);
     }
-    // Row order by degree; the rows with more than kGfpWideDeg arcs come
-    // first, and their count is read back with the check results.
+    // Row order by degree; the wide rows come first, and their count is read back with the check results.
     launch_degree(A.g->row_ptr, A.g->weight, n, w.deg, w.invd, s);
     stream_row_order(A.g->row_ptr, n, w.hist, w.rows, s);
-    hipLaunchKernelGGL(gfp_wide_count_kernel, dim3(1), dim3(1), 0, s, w.hist, w.info);
+    const bool small = (int64_t)n / kStreamRowsPerBlock * (gfp_ld(A.k) / kSlab) <= kGfpMarkMinBlocks;
+    hipLaunchKernelGGL(gfp_wide_count_kernel, dim3(1), dim3(1), 0, s, w.hist,
+                       small ? kGfpWideDegSmall : kGfpWideDeg, w.info);
     ppr_status st = launch_status();
     if (st != PPR_OK) return st;
     if ((st = read_i32(w.info, info, kGfpInfo, s)) != PPR_OK) return st;
@@ -748,12 +753,13 @@ ppr_status gfp_run(const GfpArgs& A, const GfpWs& w, const int32_t info[kGfpInfo
     gfp_launch_round<false, true>(weighted, backward, marks, a, grid, s);
 
     // Rounds 1 .. max_rounds - 1 in growing batches; after each batch the
-    // host reads the last round's flag and stops when it is clear.
-    int32_t launched = 1, last = -1, batch = 4;
+    // host reads which rounds pushed and stops when one did not.  A read leaves
+    // the GPU idle for 40-80 us, a round launched past the end returns at once
+    // (4 us at 20000 nodes, 8 us at 10^6).
+    constexpr int32_t kFirst = 16, kSecond = 24, kMost = 64;
+    bool capped = false;
+    int32_t seen = 0, launched = 1, batch = kFirst - 1, rounds = 0;
     while (true) {
-        if ((st = launch_status()) != PPR_OK) return st;
-        if ((st = read_i32(w.active + launched - 1, &last, 1, s)) != PPR_OK) return st;
-        if (last == 0 || launched == A.max_rounds) break;
         const int32_t end = std::min(A.max_rounds, launched + batch);
         for (int32_t t = launched; t < end; ++t) {
             a.t = t;
@@ -767,18 +773,17 @@ ppr_status gfp_run(const GfpArgs& A, const GfpWs& w, const int32_t info[kGfpInfo
             gfp_launch_round<true, true>(weighted, backward, marks, a, grid, s);
         }
         launched = end;
-        batch = std::min(batch * 2, 64);
+        if ((st = launch_status()) != PPR_OK) return st;
+        int32_t pushed[kMost];
+        if ((st = read_i32(w.active + seen, pushed, (size_t)(launched - seen), s)) != PPR_OK) return st;
+        // rounds run: up to and including the first that pushed nothing
+        while (rounds < launched && pushed[rounds - seen] != 0) ++rounds;
+        capped = rounds == launched;
+        if (!capped) ++rounds;
+        if (!capped || launched == A.max_rounds) break;
+        seen = launched;
+        batch = launched == kFirst ? kSecond : (launched < 128 ? kFirst : kMost);
     }
-    // Rounds run: up to and including the first that pushed nothing.
-    std::vector<int32_t> counts((size_t)launched);
-    if ((st = read_i32(w.active, counts.data(), (size_t)launched, s)) != PPR_OK) return st;
-    int32_t rounds = launched;
-    for (int32_t t = 0; t < launched; ++t)
-        if (counts[(size_t)t] == 0) {
-            rounds = t + 1;
-            break;
-        }
-    const bool capped = counts[(size_t)rounds - 1] != 0;
     if (capped) {
         // deliver what the last round sent, so that the residues and the
         // estimates satisfy the invariant

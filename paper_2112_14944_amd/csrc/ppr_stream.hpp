@@ -218,7 +218,14 @@ __device__ __forceinline__ float4 slab_load(__amdgpu_buffer_rsrc_t r, uint32_t o
 // STEP: arcs a lane group advances per pass; 8 when each group owns a row,
 // 64 when the wave's 8 groups share one row (group g then passes its row's
 // arcs from 8g on, and the caller adds the groups' sums).
-template <bool WEIGHTED, bool FLAGGED = false, int STEP = kSlabVec>
+// AHEAD: the gathers of a pass go out before the pass ahead of it is summed,
+// so that a row waits for half a load latency per pass; it costs 32 registers
+// (streaming step at 10^6 nodes, 3e7 arcs, 64 columns: 1233 us per push
+// without, 1040 us with); it also shortens the Group Forward-Push rounds of
+// small grids, whose longest row sets their time.  The flagged rounds of large grids lose
+// more by the lower occupancy than they gain (late rounds 57-135 us without,
+// 100 us and more with), dense ones do not change.
+template <bool WEIGHTED, bool FLAGGED, int STEP, bool AHEAD>
 __device__ __forceinline__ float4 slab_gather(__amdgpu_buffer_rsrc_t rin, const int32_t* __restrict__ col_idx,
                                               const float* __restrict__ weight, int rs, int dg, int lane,
                                               uint32_t qoff, const uint8_t* __restrict__ flags = nullptr,
@@ -231,17 +238,18 @@ __device__ __forceinline__ float4 slab_gather(__amdgpu_buffer_rsrc_t rin, const 
     int any = 0;
     const int lead = (lane & ~(kSlabVec - 1)) * 4;  // ds_bpermute address of the group's first lane
     // Software pipeline over the passes: arc indices are loaded two passes
-    // ahead, weights and push flags one pass ahead, so that a long row's
-    // pass waits only on its own gathers.
+    // ahead of a pass's gathers, weights and push flags one pass ahead.  A
+    // pass past the longest row reads zeros and touches no memory.
     int idx_cur = q < dg ? col_idx[rs + q] : -1;
     int idx_next = STEP + q < dg ? col_idx[rs + STEP + q] : -1;
     float wl_cur = 0.f;
     if (WEIGHTED) wl_cur = q < dg ? weight[rs + q] : 0.f;
     bool on_cur = true;
     if (FLAGGED) on_cur = idx_cur >= 0 && flags[idx_cur] != 0;
-    for (int k0 = 0; k0 < dmax; k0 += STEP) {
+    int k0 = 0;  // the pass issued next
+    auto issue = [&](float4 (&y)[kSlabVec], float& wl) {
         int idx = idx_cur;
-        const float wl = wl_cur;
+        wl = wl_cur;
         const bool on = on_cur;
         const int idx_after = k0 + 2 * STEP + q < dg ? col_idx[rs + k0 + 2 * STEP + q] : -1;
         if (WEIGHTED) wl_cur = k0 + STEP + q < dg ? weight[rs + k0 + STEP + q] : 0.f;
@@ -252,12 +260,14 @@ __device__ __forceinline__ float4 slab_gather(__amdgpu_buffer_rsrc_t rin, const 
         }
         idx_cur = idx_next;
         idx_next = idx_after;
-        float4 y[kSlabVec];
+        k0 += STEP;
 #pragma unroll
         for (int j = 0; j < kSlabVec; ++j) {
             const int u = __builtin_amdgcn_ds_bpermute(lead + 4 * j, idx);
             y[j] = slab_load(rin, ((uint32_t)u << 7) | qoff);
         }
+    };
+    auto add = [&](const float4 (&y)[kSlabVec], float wl) {
 #pragma unroll
         for (int j = 0; j < kSlabVec; ++j) {
             if (WEIGHTED) {
@@ -266,6 +276,26 @@ __device__ __forceinline__ float4 slab_gather(__amdgpu_buffer_rsrc_t rin, const 
             } else {
                 f4_acc(acc, y[j]);
             }
+        }
+    };
+    float4 ya[kSlabVec], yb[kSlabVec];
+    float wa = 0.f, wb = 0.f;
+    if (!AHEAD) {
+        while (k0 < dmax) {
+            issue(ya, wa);
+            add(ya, wa);
+        }
+    } else if (dmax > 0) {
+        issue(ya, wa);
+        for (;;) {
+            const bool more = k0 < dmax;  // wave-uniform
+            issue(yb, wb);
+            add(ya, wa);
+            if (!more) break;
+            const bool more2 = k0 < dmax;
+            issue(ya, wa);
+            add(yb, wb);
+            if (!more2) break;
         }
     }
     if (FLAGGED) {
@@ -307,7 +337,7 @@ __global__ __launch_bounds__(256) void stream_step_kernel(
         v = e.v;
     }
     const uint32_t qoff = (uint32_t)q * 16u;
-    float4 acc = slab_gather<WEIGHTED>(rin, col_idx, weight, rs, dg, lane, qoff);
+    float4 acc = slab_gather<WEIGHTED, false, kSlabVec, true>(rin, col_idx, weight, rs, dg, lane, qoff);
     if (has_row && dg == 0) acc = slab_load(rin, ((uint32_t)v << 7) | qoff);
     if (!has_row) return;
     const int col0 = slab * kSlab + q * 4;
