@@ -87,10 +87,16 @@ ppr_status pprviz_pushes_for_tolerance(float alpha, double tol, int32_t max_iter
 size_t ppr_matrix_workspace(const ppr_csr* g, int32_t n_src, int32_t n_tgt);
 
 /* Workspace bytes with which ppr_matrix takes its fastest route: at least
- * ppr_matrix_workspace(), and 16 n^2 bytes more for all pairs (n_src == n) of
- * a graph of 192 <= n <= 2304 nodes, whose push series is then cut into a
- * shorter one and dense products where that is faster.  The two routes agree
- * to FP32 rounding. */
+ * ppr_matrix_workspace(), and what these need beyond it, where they apply:
+ *  - all pairs (n_src == n) of 192 <= n <= 2304 nodes: 16 n^2 bytes, with which
+ *    the push series is cut into a shorter one and dense products;
+ *  - up to 256 sources of a graph of n <= 40831 nodes: the iterate in HBM
+ *    (about 8 n n_src bytes), each push over the whole GPU;
+ *  - n_tgt == n_src, for calls whose tgt is the src array itself: the buffers
+ *    of a product of about n_src^2 entries that halves the pushes.
+ * Each is taken where it is faster.  The routes agree to FP32 rounding; with a
+ * smaller workspace (at least ppr_matrix_workspace()) a call takes a general
+ * one. */
 size_t ppr_matrix_workspace_fast(const ppr_csr* g, int32_t n_src, int32_t n_tgt);
 
 /*
@@ -113,8 +119,8 @@ size_t ppr_matrix_workspace_fast(const ppr_csr* g, int32_t n_src, int32_t n_tgt)
  * when max_iter capped T before the tolerance was met.
  * Kernel by size: n <= 2304 keeps a tile of sources in LDS; n <= 40831 keeps
  * 4, 2 or 1 source columns of every node in LDS (these two never move the
- * iterate through HBM); larger n streams the iterate through HBM.  On the
- * first two paths a row that lists more than n arcs (repeated neighbours) can
+ * iterate through HBM); larger n, and few sources of a smaller graph, stream
+ * the iterate through HBM.  For n <= 40831 a row that lists more than n arcs (repeated neighbours) can
  * exceed the workspace bound of the padded arc copy: the outputs and the
  * residual are then NaN (PPR_ENONFINITE when resid_out is asked for).
  */
@@ -135,9 +141,9 @@ ppr_status ppr_matrix(const ppr_csr* g, const int32_t* src, int32_t n_src,
  * Limit: the workspace ppr_matrix_workspace(g, n_src, n_tgt) would ask for
  * must fit ppr_matrix_noalloc_max_scratch() bytes (8 MiB), else the call
  * returns PPR_EUNSUPPORTED before any launch.  That covers, for example, the
- * LDS-resident path (n <= 2304) up to about 1 million arcs unweighted.  The
- * 16 n^2 bytes that the fastest route of all pairs adds have room of their
- * own (85 MB) and do not count.
+ * LDS-resident path (n <= 2304) up to about 1 million arcs unweighted.  What
+ * ppr_matrix_workspace_fast() adds has room of its own (85 MB) and does not
+ * count.
  *
  * The scratch is one array per GPU, held from the first call on that GPU
  * until the process ends (its device address is looked up once per device).

@@ -174,10 +174,6 @@ static void bwd_layout(Cursor& c, int n, int64_t nnz, bool weighted, bool recomp
     if (w) *w = t;
 }
 
-// The recomputed forward takes the route ppr_matrix takes with the workspace
-// of ppr_matrix_workspace_fast, so that it gives the same bits.
-static size_t bwd_series(const ppr_csr* g) { return ppr_series_floats(g->n, g->n); }
-
 }  // namespace pprviz
 
 using namespace pprviz;
@@ -188,7 +184,7 @@ size_t ppr_backward_workspace(const ppr_csr* g, int recompute) {
     if (g == nullptr || g->n < 1 || g->nnz < 0) return 0;
     WsSize c;
     bwd_layout(c, g->n, g->nnz, g->weight != nullptr, recompute != 0, nullptr);
-    if (recompute && bwd_series(g) > 0) c.take<float>(bwd_series(g));
+    if (recompute) ppr_extra_layout(c, g->n, g->n, false, nullptr);
     return c.used;
 }
 
@@ -205,7 +201,9 @@ ppr_status ppr_matrix_backward(const ppr_csr* g, float alpha, int32_t T, const f
     BwdWs w;
     bwd_layout(cur, g->n, g->nnz, g->weight != nullptr, recompute, &w);
     if (ws == nullptr || cur.used > ws_bytes) return PPR_EWORKSPACE;
-    if (recompute && bwd_series(g) > 0) w.f.series = cur.take<float>(bwd_series(g));
+    // the recomputed forward takes the route ppr_matrix takes with the
+    // workspace of ppr_matrix_workspace_fast, so that it gives the same bits
+    if (recompute) ppr_extra_take(cur, g->n, g->n, false, &w.f);
     if (pending_error() != PPR_OK) return PPR_EHIP;
     if (g->nnz == 0) return PPR_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -236,10 +234,9 @@ ppr_status ppr_matrix_backward(const ppr_csr* g, float alpha, int32_t T, const f
         sa.ncols = n;
         sa.ld = stream_ld(n);
         sa.alpha = alpha;
-        sa.src = nullptr;
         sa.forcing = grad_dppr;
         sa.ld_forcing = n;
-        const float* A = stream_power_iteration(sa, T, f.ya, f.yb, s);
+        const float* A = stream_adjoint(sa, T, f.ya, f.yb, s);
         hipLaunchKernelGGL(arc_dot_kernel<true>, dots, dim3(256), 0, s, w.row_of_arc, g->col_idx, g->nnz, A, pi, n,
                            w.dq);
     }

@@ -8,6 +8,7 @@
 #include "ppr_core.hpp"
 #include "ppr_dense.hpp"
 #include "ppr_mid.hpp"
+#include "ppr_query.hpp"
 #include "ppr_stream.hpp"
 
 namespace pprviz {
@@ -30,13 +31,58 @@ struct PprWs {
     float* yb;
     double* part;
     int32_t* hist;
-    float* series;   // all-pairs series (ppr_series_floats), nullptr: not taken
+    float* series;   // all-pairs series (ppr_extra_layout), nullptr: not taken
+    QueryWs query;   // iterate in HBM; ya == nullptr: not taken
 };
 
-// Floats of the all-pairs series for this call (0: it is never taken): every
-// node a source, a size of the resident range worth products.
-inline size_t ppr_series_floats(int n, int n_src) {
-    return res_cols_for(n) != 0 && n >= kDenseMinN && n_src == n ? (size_t)4 * n * n : 0;
+// Bytes a call's fastest route needs beyond ppr_ws_layout (none of them is
+// needed: without them the call takes its general route):
+//  - all pairs of 192 to 2304 nodes: 4 n^2 floats of the series;
+//  - a few sources of a graph that fits LDS: the iterate in HBM;
+//  - targets that may be the sources (same): the pieces of the product that
+//    halves the pushes.
+constexpr int kQueryMaxSame = 8192;
+template <typename Cursor>
+void ppr_extra_layout(Cursor& c, int n, int n_src, bool same, PprWs* w) {
+    float* series = nullptr;
+    QueryWs q{};
+    const bool lds = res_cols_for(n) != 0 || mid_cols_for(n) != 0;
+    if (res_cols_for(n) != 0 && n >= kDenseMinN && n_src == n) {
+        series = c.template take<float>((size_t)4 * n * n);
+    } else if (lds && n_src > 0 && n_src <= kQueryMaxSrc && n_src < n) {
+        const size_t ld = (size_t)query_ld(n_src);
+        q.hist = c.template take<int32_t>(kDegKeys);
+        q.refuse = c.template take<int32_t>(1);
+        q.deg_sorted = c.template take<int32_t>((size_t)n);
+        q.ya = c.template take<float>((size_t)n * ld);
+        q.yb = c.template take<float>((size_t)n * ld);
+        q.part = c.template take<double>((size_t)stream_resid_chunks(n) * ld);
+    }
+    if (same && n_src > 0 && (lds ? n_src <= kQueryMaxSrc && n_src < n : n_src <= kQueryMaxSame)) {
+        q.pieces = query_pieces(n, n_src);
+        q.gram = c.template take<float>(query_gram_floats(n, n_src));
+        q.prod = c.template take<double>((size_t)n_src * n_src);
+    }
+    if (w) {
+        w->series = series;
+        if (!lds) {
+            q.hist = w->hist;
+            q.ya = w->ya;
+            q.yb = w->yb;
+            q.part = w->part;
+        }
+        w->query = q;
+    }
+}
+// The extra buffers where the workspace has room for them.
+inline void ppr_extra_take(WsCursor& c, int n, int n_src, bool same, PprWs* w) {
+    WsCursor t = c;
+    ppr_extra_layout(t, n, n_src, same, w);
+    if (t.used <= t.cap) {
+        c = t;
+    } else {
+        ppr_extra_layout(c, n, 0, false, w);  // none of them
+    }
 }
 
 template <typename Cursor>

@@ -500,6 +500,7 @@ __global__ __launch_bounds__(256) void ppr_series_out_kernel(const float* __rest
         if (ppr_out) ppr_out[(int64_t)i * n_tgt + j] = x;
         if (dppr_out) dppr_out[(int64_t)i * n_tgt + j] = x * ds;
     }
+    if (resid == nullptr) return;
     double sum = 0.0;
     for (int v = threadIdx.x; v < n; v += 256) sum += (double)(float)((double)y[v] * dense_unscale(invd[v], alpha));
     sum = wave_sum(sum);
@@ -548,12 +549,24 @@ bool use_resident(int n) { return res_cols_for(n) != 0; }
 // kernels by size: the LDS-resident tile (n <= 2304; all pairs by fewer pushes
 // and dense products where that is faster and the workspace has room for it),
 // the mid-size kernel with the iterate columns in LDS (n <= 40831), and the
-// streaming SpMM with the iterate in HBM.
+// iterate in HBM (larger graphs; smaller ones with few sources where that is
+// faster and the workspace has room for it).
 void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int32_t* tgt, int32_t n_tgt,
                  float alpha, int32_t T, float* ppr_out, float* dppr_out, const float* deg, const float* invd,
                  double* resid, const PprWs& w, hipStream_t s) {
     const int n = g->n;
-    if (use_resident(n)) {
+    // The iterate in HBM: always for graphs that do not fit LDS, else for few
+    // sources where it is faster.  The targets being the sources halves the
+    // pushes where the product costs less than the pushes it saves (60
+    // TFLOP/s against 7 TB/s of gathers); a residual needs every node.
+    QueryWs q = w.query;
+    const bool halve = q.gram != nullptr && tgt == src && n_tgt == n_src && resid == nullptr && T >= kQueryMinT &&
+                       (double)n * n_src / 60e12 < 0.5 * T * (double)g->nnz * 4 / 7e12;
+    if (!halve) q.gram = nullptr;
+    const bool lds = use_resident(n) || mid_cols_for(n) != 0;
+    if (!lds || (q.ya != nullptr && query_faster(n, g->nnz, n_src, T, halve))) {
+        query_forward(g, src, n_src, tgt, n_tgt, alpha, T, ppr_out, dppr_out, deg, invd, resid, w.rows, q, s);
+    } else if (use_resident(n)) {
         launch_res_layout(g->row_ptr, g->col_idx, g->weight, invd, nullptr, n, 1, w.slots, w.col_r,
                           g->weight ? w.w_r : nullptr, w.sorted_r, g->weight ? w.sorted_w : nullptr, s);
         ResArgs a;
@@ -571,30 +584,11 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
         // every node a source (sources are distinct): all pairs
         const DensePlan p = dense_plan(n, g->nnz, n_src == n && w.series != nullptr ? T : 0);
         if (p.k > 0)
-            ppr_series(g, p, src, tgt, n_tgt, a, invd, ppr_out, dppr_out, w.resid, w.series, s);
+            ppr_series(g, p, src, tgt, n_tgt, a, invd, ppr_out, dppr_out, resid, w.series, s);
         else
             launch_resident_any(g->weight != nullptr, a, n, g->nnz, n_src, n_tgt, T, 0, 0, s);
-    } else if (mid_cols_for(n) != 0) {
-        mid_forward(g, src, n_src, tgt, n_tgt, alpha, T, ppr_out, dppr_out, deg, invd, resid, w.mid, s);
     } else {
-        stream_row_order(g->row_ptr, n, w.hist, w.rows, s);
-        StreamArgs sa;
-        sa.rows = w.rows;
-        sa.row_ptr = g->row_ptr;
-        sa.col_idx = g->col_idx;
-        sa.weight = g->weight;
-        sa.invd = invd;
-        sa.deg = deg;
-        sa.n = n;
-        sa.ncols = n_src;
-        sa.ld = stream_ld(n_src);
-        sa.alpha = alpha;
-        sa.src = src;
-        sa.forcing = nullptr;
-        sa.ld_forcing = 0;
-        const float* x = stream_power_iteration(sa, T, w.ya, w.yb, s);
-        stream_write_outputs(x, sa, tgt, n_tgt, ppr_out, dppr_out, s);
-        if (resid) stream_residuals(x, sa, w.part, resid, s);
+        mid_forward(g, src, n_src, tgt, n_tgt, alpha, T, ppr_out, dppr_out, deg, invd, resid, w.mid, s);
     }
 }
 
@@ -602,13 +596,14 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
 // Scratch memory of ppr_matrix_noalloc: a fixed device array, one copy per
 // GPU, that replaces the caller's workspace for callers that cannot allocate
 // (graph capture, tight serving loops): kScratchBytes for the workspace
-// proper, then the buffers of the all-pairs series at the resident range's
-// largest size.  Host code never passes the array's
+// proper, then room for the buffers of the faster routes (the all-pairs series
+// of the resident range's largest size needs the most of those a graph whose
+// workspace fits can take).  Host code never passes the array's
 // name to a kernel: scratch_address resolves it once per device, with that
 // device current, and keeps the device address.
 constexpr size_t kScratchBytes = size_t(8) << 20;
-constexpr size_t kScratchSeriesBytes = size_t(4) * Res<16>::NMAX * Res<16>::NMAX * sizeof(float);
-static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSeriesBytes];
+constexpr size_t kScratchExtraBytes = size_t(4) * Res<16>::NMAX * Res<16>::NMAX * sizeof(float);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchExtraBytes];
 constexpr int kMaxDevices = 64;
 
 static ppr_status scratch_address(hipStream_t s, void** out) {
@@ -659,19 +654,20 @@ static ppr_status ppr_matrix_impl(const ppr_csr* g, const int32_t* src, int32_t 
     PprWs w;
     ppr_ws_layout(cur, g->n, g->nnz, g->weight != nullptr, n_src, &w);
     if (ws == nullptr || cur.used > ws_bytes) return scratch_ws ? PPR_EUNSUPPORTED : PPR_EWORKSPACE;
-    // a workspace with room for the all-pairs series takes it
-    const size_t series = ppr_series_floats(g->n, n_src);
+    // a workspace with room for a faster route's buffers takes it
     if (scratch_ws) {
         cur.used = kScratchBytes;
-        cur.cap = kScratchBytes + kScratchSeriesBytes;
+        cur.cap = kScratchBytes + kScratchExtraBytes;
     }
-    w.series = series > 0 ? cur.take<float>(series) : nullptr;
+    const bool same = tgt != nullptr && tgt == src && n_tgt == n_src;
+    ppr_extra_take(cur, g->n, n_src, same, &w);
     if (pending_error() != PPR_OK) return PPR_EHIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int n = g->n;
     launch_degree(g->row_ptr, g->weight, n, w.deg, w.invd, s);
 
-    ppr_forward(g, src, n_src, tgt, n_tgt, alpha, T, ppr_out, dppr_out, w.deg, w.invd, w.resid, w, s);
+    ppr_forward(g, src, n_src, tgt, n_tgt, alpha, T, ppr_out, dppr_out, w.deg, w.invd,
+                resid_out ? w.resid : nullptr, w, s);
     st = launch_status();
     if (st != PPR_OK) return st;
     if (resid_out) {
@@ -743,12 +739,10 @@ size_t ppr_matrix_workspace(const ppr_csr* g, int32_t n_src, int32_t n_tgt) {
 }
 
 size_t ppr_matrix_workspace_fast(const ppr_csr* g, int32_t n_src, int32_t n_tgt) {
-    (void)n_tgt;
     if (g == nullptr || g->n < 1 || n_src < 0) return 0;
     WsSize c;
     ppr_ws_layout(c, g->n, g->nnz, g->weight != nullptr, n_src, nullptr);
-    const size_t series = ppr_series_floats(g->n, n_src);
-    if (series > 0) c.take<float>(series);
+    ppr_extra_layout(c, g->n, n_src, n_src == n_tgt, nullptr);
     return c.used;
 }
 

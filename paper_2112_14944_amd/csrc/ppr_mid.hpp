@@ -95,6 +95,31 @@ constexpr int kPlanInts = kPlanHubs + 1;
 // and the first 16 slices; nothing is split when the longest row fits in a
 // wave's mean share.
 
+// The part length D, the number H of rows cut and the number P of their parts,
+// for row lengths len(0) >= len(1) >= ...
+template <typename F>
+__device__ __forceinline__ void mid_split_choose(F len, int32_t n, int64_t nnz, int32_t C, int64_t& D, int& H,
+                                                 int& P) {
+    // target part length: half a wave's mean share of the arcs (16 waves)
+    const int64_t groups = (nnz * 11 / 10 + kMidGroup - 1) / kMidGroup;
+    D = 4 * max((int64_t)2, (groups + 2 * kMidWaves - 1) / (2 * kMidWaves));
+    // no split when the widest slice is no wider than a wave's mean share:
+    // the deal already balances such slices
+    const int64_t maxdeg = len(0);
+    if ((maxdeg + 3) / 4 <= groups / kMidWaves) D = INT64_MAX / 4;
+    const int cap = min(kMidMaxParts, (kMidLdsFloats - (n + 1) * C) / C);
+    for (;;) {
+        H = 0;
+        P = 0;
+        while (H < n && len(H) > D && P <= cap) {
+            P += (int)((len(H) + D - 1) / D);
+            ++H;
+        }
+        if (P <= cap && (H == n || len(H) <= D)) break;
+        D *= 2;
+    }
+}
+
 // One block.  Chooses D, writes the row list after splitting (parts first,
 // tagged with their partial index + 1), one combine entry per split row
 // (LDS byte address of the row, scale, LDS byte address of its first
@@ -111,25 +136,9 @@ static __global__ __launch_bounds__(1024) void mid_split_kernel(const RowEnt* __
     __shared__ int32_t sH, sP;
     const int tid = threadIdx.x;
     if (tid == 0) {
-        // target part length: half a wave's mean share of the arcs (16 waves)
-        const int64_t groups = (nnz * 11 / 10 + kMidGroup - 1) / kMidGroup;
-        int64_t D = 4 * max((int64_t)2, (groups + 2 * kMidWaves - 1) / (2 * kMidWaves));
-        // no split when the widest slice is no wider than a wave's mean share:
-        // the deal already balances such slices
-        const int64_t maxdeg = rows[0].re - rows[0].rs;
-        if ((maxdeg + 3) / 4 <= groups / kMidWaves) D = INT64_MAX / 4;
-        const int cap = min(kMidMaxParts, (kMidLdsFloats - (n + 1) * C) / C);
-        int H = 0, P = 0;
-        for (;;) {
-            H = 0;
-            P = 0;
-            while (H < n && (int64_t)(rows[H].re - rows[H].rs) > D && P <= cap) {
-                P += (int)(((int64_t)(rows[H].re - rows[H].rs) + D - 1) / D);
-                ++H;
-            }
-            if (P <= cap && (H == n || (int64_t)(rows[H].re - rows[H].rs) <= D)) break;
-            D *= 2;
-        }
+        int64_t D;
+        int H, P;
+        mid_split_choose([&](int i) { return (int64_t)(rows[i].re - rows[i].rs); }, n, nnz, C, D, H, P);
         int pb = 0;
         for (int h = 0; h < H; ++h) {
             hub_pb[h] = pb;

@@ -1,12 +1,10 @@
-// Power iteration for graphs too large to keep any source column of the
-// iterate in LDS (more than 40831 nodes): the iterate lives in HBM (ping-pong
-// buffers, column slabs of 32 sources) and each push is one launch.  A wave
-// takes 8 rows side by side, so every gathered neighbour row is one
-// contiguous 128-byte read (details at stream_step_kernel).
-//
-// The same step serves the adjoint solve of the weight gradient:
-//     A_{k+1} = Gb + (1-alpha) P^T A_k      (Gb = D G, forcing term)
-// which gathers over the same neighbours with the same coefficients.
+// Iterates in HBM in column slabs of 32: the degree row order, the slab gather
+// of the Group Forward- and Backward-Push rounds, and the adjoint solve of the
+// weight gradient by streaming steps,
+//     A_{k+1} = Gb + (1-alpha) P^T A_k      (Gb = D G, forcing term),
+// one launch per term.  A wave takes 8 rows side by side, so every gathered
+// neighbour row is one contiguous 128-byte read (details at
+// stream_step_kernel).
 #pragma once
 
 #include "ppr_core.hpp"
@@ -36,11 +34,10 @@ struct StreamArgs {
     const float* invd;
     const float* deg;
     int32_t n;
-    int32_t ncols;        // valid columns (sources / adjoint right-hand sides)
+    int32_t ncols;        // valid columns (right-hand sides)
     int64_t ld;           // columns held (multiple of 64)
     float alpha;
-    const int32_t* src;   // forward: source node of column s (nullptr: column s = node s)
-    const float* forcing; // adjoint: G [n][ld_forcing] (Gb = deg[v] * G[v][s]); nullptr = forward
+    const float* forcing; // G [n][ld_forcing] (Gb = deg[v] * G[v][s])
     int64_t ld_forcing;
 };
 
@@ -307,16 +304,15 @@ __device__ __forceinline__ float4 slab_gather(__amdgpu_buffer_rsrc_t rin, const 
     return acc;
 }
 
-// One push (MODE 0: forward, forcing alpha at each column's source row;
-// MODE 1: adjoint, forcing deg[v] * G[v][col]).  A wave takes 8 rows of the
+// One adjoint term, forcing deg[v] * G[v][col].  A wave takes 8 rows of the
 // degree order side by side within one slab: lane = 8 * g + q, where g picks
 // the row and q 4 of the slab's 32 columns (one 16-byte load per arc, summed
 // by slab_gather).
-template <int MODE, bool WEIGHTED, bool FINAL>
+template <bool WEIGHTED, bool FINAL>
 __global__ __launch_bounds__(256) void stream_step_kernel(
     const RowEnt* __restrict__ rows, const int32_t* __restrict__ col_idx,
     const float* __restrict__ weight, const float* __restrict__ invd, const float* __restrict__ deg,
-    const int32_t* __restrict__ src, const float* __restrict__ forcing, int64_t ld_forcing, int32_t n,
+    const float* __restrict__ forcing, int64_t ld_forcing, int32_t n,
     int32_t ncols, float alpha, StreamGrid grid, const float* __restrict__ yin, float* __restrict__ yout) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -343,29 +339,15 @@ __global__ __launch_bounds__(256) void stream_step_kernel(
     const int col0 = slab * kSlab + q * 4;
     float x[4] = {acc.x, acc.y, acc.z, acc.w};
     const float sv = FINAL ? 1.0f : (1.0f - alpha) * invd[v];
-    const float dv = MODE == 1 ? deg[v] : 0.f;
+    const float dv = deg[v];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const int col = col0 + c;
-        if (MODE == 0) {
-            if (col < ncols && v == (src ? src[col] : col)) x[c] += alpha;
-        } else {
-            x[c] += col < ncols ? dv * forcing[(int64_t)v * ld_forcing + col] : 0.0f;
-        }
+        x[c] += col < ncols ? dv * forcing[(int64_t)v * ld_forcing + col] : 0.0f;
         x[c] = FINAL ? x[c] : x[c] * sv;
     }
     float4* o4 = reinterpret_cast<float4*>(yout + slab_off);
     o4[(int64_t)v * kSlabVec + q] = make_float4(x[0], x[1], x[2], x[3]);
-}
-
-// Y_0 for the forward iteration: zero everywhere but the source rows.
-static __global__ void stream_init_forward_kernel(const int32_t* __restrict__ src, const float* __restrict__ invd,
-                                           int32_t n, int32_t ncols, float alpha, int final_,
-                                           float* __restrict__ y) {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= ncols) return;
-    int v = src ? src[s] : s;
-    y[sidx(v, s, n)] = final_ ? alpha : alpha * (1.0f - alpha) * invd[v];
 }
 
 // Y_0 = (1-alpha)/d * Gb for the adjoint (Gb = d * G), or Gb itself when final.
@@ -380,56 +362,6 @@ static __global__ void stream_init_adjoint_kernel(const float* __restrict__ forc
     y[sidx(v, col, n)] = final_ ? g : g * (1.0f - alpha) * invd[v];
 }
 
-// out[s][j] = X[tgt[j]][s] (and d(src_s) times it), 64x64 tiles through LDS.
-static __global__ __launch_bounds__(256) void stream_transpose_kernel(
-    const float* __restrict__ x, int32_t n, int32_t ncols, const int32_t* __restrict__ src,
-    const int32_t* __restrict__ tgt, int32_t n_tgt, const float* __restrict__ deg,
-    float* __restrict__ ppr_out, float* __restrict__ dppr_out, int64_t ld_out) {
-    __shared__ float tile[64][65];
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const int64_t j0 = (int64_t)blockIdx.x * 64;
-    const int64_t s0 = (int64_t)blockIdx.y * 64;
-    for (int jj = w; jj < 64; jj += 4) {
-        const int64_t j = j0 + jj;
-        float val = 0.f;
-        if (j < n_tgt) {
-            const int64_t tn = tgt ? tgt[j] : j;
-            val = x[sidx(tn, s0 + lane, n)];
-        }
-        tile[jj][lane] = val;
-    }
-    __syncthreads();
-    for (int ss = w; ss < 64; ss += 4) {
-        const int64_t s = s0 + ss;
-        if (s >= ncols) break;
-        const int64_t j = j0 + lane;
-        if (j >= n_tgt) continue;
-        const float val = tile[lane][ss];
-        if (ppr_out) ppr_out[s * ld_out + j] = val;
-        if (dppr_out) {
-            const int sn = src ? src[s] : (int)s;
-            dppr_out[s * ld_out + j] = val * deg[sn];
-        }
-    }
-}
-
-// Column sums of X over row chunks in FP64 (first pass of the residual).
-static __global__ __launch_bounds__(256) void stream_colsum_kernel(const float* __restrict__ x, int32_t n, int64_t ld,
-                                                            double* __restrict__ part) {
-    __shared__ double red[4][64];
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const int64_t col = (int64_t)blockIdx.y * 64 + lane;
-    const int64_t r0 = (int64_t)blockIdx.x * kStreamResidRows;
-    const int64_t r1 = min((int64_t)n, r0 + kStreamResidRows);
-    double s = 0.0;
-    for (int64_t r = r0 + w; r < r1; r += 4) s += (double)x[sidx(r, col, n)];
-    red[w][lane] = s;
-    __syncthreads();
-    if (w == 0) part[(int64_t)blockIdx.x * ld + col] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-}
-
 static __global__ void stream_resid_kernel(const double* __restrict__ part, int64_t chunks, int64_t ld, int32_t ncols,
                                     double* __restrict__ resid) {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -439,7 +371,7 @@ static __global__ void stream_resid_kernel(const double* __restrict__ part, int6
     resid[s] = 1.0 - t;
 }
 
-template <int MODE, bool FINAL>
+template <bool FINAL>
 inline void stream_launch_step(const StreamArgs& a, const float* yin, float* yout, hipStream_t s) {
     StreamGrid g;
     g.row_blocks = (a.n + kStreamRowsPerBlock - 1) / kStreamRowsPerBlock;
@@ -447,60 +379,30 @@ inline void stream_launch_step(const StreamArgs& a, const float* yin, float* you
     g.full_rounds = ((int64_t)a.n * kSlab * 4 <= kStreamSlabBudget) ? g.slabs / kXcds : 0;
     const dim3 grid((unsigned)((int64_t)g.row_blocks * g.slabs));
     if (a.weight)
-        hipLaunchKernelGGL((stream_step_kernel<MODE, true, FINAL>), grid, dim3(256), 0, s, a.rows, a.col_idx,
-                           a.weight, a.invd, a.deg, a.src, a.forcing, a.ld_forcing, a.n, a.ncols, a.alpha, g, yin,
-                           yout);
+        hipLaunchKernelGGL((stream_step_kernel<true, FINAL>), grid, dim3(256), 0, s, a.rows, a.col_idx, a.weight,
+                           a.invd, a.deg, a.forcing, a.ld_forcing, a.n, a.ncols, a.alpha, g, yin, yout);
     else
-        hipLaunchKernelGGL((stream_step_kernel<MODE, false, FINAL>), grid, dim3(256), 0, s, a.rows, a.col_idx,
-                           a.weight, a.invd, a.deg, a.src, a.forcing, a.ld_forcing, a.n, a.ncols, a.alpha, g, yin,
-                           yout);
+        hipLaunchKernelGGL((stream_step_kernel<false, FINAL>), grid, dim3(256), 0, s, a.rows, a.col_idx, a.weight,
+                           a.invd, a.deg, a.forcing, a.ld_forcing, a.n, a.ncols, a.alpha, g, yin, yout);
 }
 
-// T pushes (forward, a.forcing == nullptr) or T adjoint terms; returns the
-// buffer that holds the final unscaled iterate.
-inline const float* stream_power_iteration(const StreamArgs& a, int T, float* ya, float* yb, hipStream_t s) {
-    const int64_t total = (int64_t)a.n * a.ld;
-    const bool adj = a.forcing != nullptr;
-    fill<float>(ya, 0.0f, total, s);
+// T adjoint terms; returns the buffer that holds the final unscaled iterate.
+inline const float* stream_adjoint(const StreamArgs& a, int T, float* ya, float* yb, hipStream_t s) {
+    fill<float>(ya, 0.0f, (int64_t)a.n * a.ld, s);
     if (T <= 0) return ya;
-    if (adj) {
-        dim3 grid((unsigned)((a.n + 3) / 4), (unsigned)(a.ld / 64));
-        hipLaunchKernelGGL(stream_init_adjoint_kernel, grid, dim3(256), 0, s, a.forcing, a.ld_forcing, a.deg,
-                           a.invd, a.n, a.ncols, a.ld, a.alpha, T == 1 ? 1 : 0, ya);
-    } else {
-        hipLaunchKernelGGL(stream_init_forward_kernel, dim3((a.ncols + 255) / 256), dim3(256), 0, s, a.src,
-                           a.invd, a.n, a.ncols, a.alpha, T == 1 ? 1 : 0, ya);
-    }
+    const dim3 grid((unsigned)((a.n + 3) / 4), (unsigned)(a.ld / 64));
+    hipLaunchKernelGGL(stream_init_adjoint_kernel, grid, dim3(256), 0, s, a.forcing, a.ld_forcing, a.deg, a.invd, a.n,
+                       a.ncols, a.ld, a.alpha, T == 1 ? 1 : 0, ya);
     float* in = ya;
     float* out = yb;
     for (int it = 1; it < T; ++it) {
-        const bool fin = (it == T - 1);
-        if (adj) {
-            if (fin) stream_launch_step<1, true>(a, in, out, s); else stream_launch_step<1, false>(a, in, out, s);
-        } else {
-            if (fin) stream_launch_step<0, true>(a, in, out, s); else stream_launch_step<0, false>(a, in, out, s);
-        }
+        if (it == T - 1) stream_launch_step<true>(a, in, out, s);
+        else stream_launch_step<false>(a, in, out, s);
         float* t = in;
         in = out;
         out = t;
     }
     return in;
-}
-
-inline void stream_write_outputs(const float* x, const StreamArgs& a, const int32_t* tgt, int32_t n_tgt,
-                                 float* ppr_out, float* dppr_out, hipStream_t s) {
-    if (!ppr_out && !dppr_out) return;
-    dim3 grid((unsigned)((n_tgt + 63) / 64), (unsigned)((a.ncols + 63) / 64));
-    hipLaunchKernelGGL(stream_transpose_kernel, grid, dim3(256), 0, s, x, a.n, a.ncols, a.src, tgt, n_tgt, a.deg,
-                       ppr_out, dppr_out, (int64_t)n_tgt);
-}
-
-inline void stream_residuals(const float* x, const StreamArgs& a, double* part, double* resid, hipStream_t s) {
-    const int64_t chunks = stream_resid_chunks(a.n);
-    dim3 grid((unsigned)chunks, (unsigned)(a.ld / 64));
-    hipLaunchKernelGGL(stream_colsum_kernel, grid, dim3(256), 0, s, x, a.n, a.ld, part);
-    hipLaunchKernelGGL(stream_resid_kernel, dim3((a.ncols + 255) / 256), dim3(256), 0, s, part, chunks, a.ld,
-                       a.ncols, resid);
 }
 
 }  // namespace pprviz

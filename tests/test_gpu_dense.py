@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import synth
-from gpu_util import ALPHA, get_ops
+from gpu_util import ALPHA, get_ops, oracle_ppr
 
 pytestmark = pytest.mark.gpu
 
@@ -124,3 +124,43 @@ def test_all_pairs_series(n, degree, T, k):
     # either route rounds each value about T times by u = 2^-24, at random:
     # 1e-6 of the matrix's norm bounds the difference with room to spare
     assert ((out[:, t] - ppr).norm() / ppr.norm()).item() <= 1e-6
+
+
+# Few sources: the iterate in HBM in slabs of 8, 16 and 32 columns (8 / 9 / 16 /
+# 17 sources around their widths, 64 / 65 around a product tile), graphs of
+# every size class, rows around and far above the 64 arcs of a whole-wave row
+# (the power-law graphs), an isolated node among the sources, weights, T odd,
+# even and short; targets that are the sources (about T / 2 pushes and one
+# product), other targets, and all nodes.
+@pytest.mark.parametrize("n,sources,T,targets", [
+    (2000, 1, 86, "all"), (2000, 8, 85, "same"), (2300, 9, 86, "same"), (2305, 16, 87, "some"), (2305, 17, 8, "same"),
+    (6000, 64, 86, "same"), (6000, 65, 99, "same"), (12000, 33, 7, "same"), (20000, 40, 100, "all"),
+    (20000, 256, 60, "same"), (41000, 3, 86, "same"), (41000, 70, 31, "some"), (41000, 100, 41, "same")])
+def test_few_sources(n, sources, T, targets):
+    ops = get_ops()
+    g0 = synth.chung_lu(n, 2.2, 20, 500 + n + sources)
+    hub = int(np.argmax(np.diff(g0.row_ptr)))
+    rng = np.random.default_rng(n + T)
+    keep = (g0.eu != n - 2) & (g0.ev != n - 2)  # an isolated node
+    w = (0.5 + 1.5 * rng.random(g0.m_und)).astype(np.float32) if T % 2 else None
+    g = synth.build_graph(n, g0.eu[keep], g0.ev[keep], None if w is None else w[keep])
+    src = rng.permutation(n)[:sources].astype(np.int32)
+    src[0] = hub
+    if sources > 2:
+        src[1] = n - 2
+    src = np.array(list(dict.fromkeys(src.tolist())), dtype=np.int32)  # distinct, unsorted
+    csr = ops.Csr.from_graph(g, "cuda")
+    sd = torch.as_tensor(src, device="cuda")
+    tgt = {"all": None, "same": sd, "some": torch.as_tensor(rng.permutation(n)[:77].astype(np.int32), device="cuda")}
+    tg = tgt[targets]
+    print(f"[few] n={n} nnz={g.nnz} sources={len(src)} T={T} targets={targets}", flush=True)
+    ppr, dppr, _, _ = ops.ppr_matrix(csr, sd, tgt=tg, tol=0.0, max_iter=T)
+    ppr2, _, _, resid = ops.ppr_matrix(csr, sd, tgt=tg, tol=0.0, max_iter=T, check_residual=True)
+    est, _, _, res, d = oracle_ppr(g, src, T=T)
+    want = est if tg is None else est[:, tg.cpu().numpy()]
+    # the package's bars: PPR 1e-6, DPPR 1e-6 max(1, d(s)), residual 2e-6
+    for p in (ppr, ppr2):
+        assert np.abs(p.double().cpu().numpy() - want).max() <= 1e-6
+    dw = d[src][:, None] * want
+    assert (np.abs(dppr.double().cpu().numpy() - dw) / np.maximum(1.0, d[src])[:, None]).max() <= 1e-6
+    assert np.abs(resid - res).max() <= 2e-6
