@@ -308,6 +308,18 @@ ppr_status stress_eval(const float* delta, int32_t k, const float* x, double* st
 ppr_status layout_step(const float* delta, int32_t k, const float* x_in, float* x_out,
                        double* stress_out, void* ws, size_t ws_bytes, void* stream);
 
+/* Workspace bytes needed by layout_run. */
+size_t layout_run_workspace(int32_t k);
+
+/*
+ * `steps` sweeps of layout_step, enqueued by one call: x_out is the layout
+ * after the last of them (x_in when steps = 0).  Up to 192 nodes they are one
+ * launch.  x_out must not alias x_in.  The sweeps agree with layout_step's to
+ * FP32 rounding.
+ */
+ppr_status layout_run(const float* delta, int32_t k, const float* x_in, float* x_out, int32_t steps,
+                      void* ws, size_t ws_bytes, void* stream);
+
 /* Workspace bytes needed by layout_step_exact. */
 size_t layout_exact_workspace(int32_t k);
 

@@ -187,10 +187,11 @@ __device__ __forceinline__ double layout_rows(const float* __restrict__ delta, i
 //
 // Bound: latency below a few thousand nodes (Delta fits the caches, and a wave
 // that walks all columns alone waits for one load after another), the Delta
-// stream above.  The split gives a sweep about 4096 waves (4 per SIMD) where
-// the rows alone would give k / 4: k = 1999 16.9 us per sweep with one wave
-// per row group, 6.5 us with eight; k = 500 7.1 us and 3.9 us.  From 16384
-// nodes on a row group has a wave of its own.  All loads of a piece (4 U Delta
+// stream above.  The split gives a sweep up to 16384 waves (the chip holds 8192
+// at once) where the rows alone would give k / 4: k = 1999 16.9 us per sweep
+// with one wave per row group, 5.6 us with eight; k = 500 7.1 and 3.8 us; k =
+// 8192 56 and 40 us; k = 20000 291 and 271 us (5.9 TB/s), two waves evening out
+// the last blocks.  All loads of a piece (4 U Delta
 // values, U positions) go out before its arithmetic, columns past k through a
 // clamped address.
 constexpr int kSplitWaves = 8;
@@ -207,6 +208,31 @@ __device__ __forceinline__ float wave_sum_last(float v) {
     PPRVIZ_DPP_ADD(0x142, 0xa)  // row_bcast:15 into rows 1 and 3
     PPRVIZ_DPP_ADD(0x143, 0xc)  // row_bcast:31 into rows 2 and 3
 #undef PPRVIZ_DPP_ADD
+    return v;
+}
+
+// The same in FP64, and the sum over the 16 lanes of a DPP row in every lane.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+    v += dpp_f64<0x111, 0xf>(v);
+    v += dpp_f64<0x112, 0xf>(v);
+    v += dpp_f64<0x114, 0xf>(v);
+    v += dpp_f64<0x118, 0xf>(v);
+    v += dpp_f64<0x142, 0xa>(v);
+    v += dpp_f64<0x143, 0xc>(v);
+    return v;
+}
+__device__ __forceinline__ double row_sum16(double v) {
+    v += dpp_f64<0x128, 0xf>(v);
+    v += dpp_f64<0x124, 0xf>(v);
+    v += dpp_f64<0x122, 0xf>(v);
+    v += dpp_f64<0x121, 0xf>(v);
     return v;
 }
 
@@ -308,7 +334,7 @@ __global__ __launch_bounds__(kSplitThreads) void layout_split_kernel(const float
 }
 
 // Waves per row group (as a power of two) and 64-column units per piece: as
-// many waves as bring the sweep to 4096, at most 8 and no more than there are
+// many waves as bring the sweep to 16384, at most 8 and no more than there are
 // units of columns.  A sweep that writes stress partials stops at two waves
 // per group: its blocks then cover at least the 16 rows a workspace holds a
 // partial for.
@@ -319,7 +345,7 @@ inline LayoutSplit layout_split(int32_t k, bool stress) {
     const int64_t groups = ((int64_t)k + kLayoutRowsPerWave - 1) / kLayoutRowsPerWave;
     const int units = (k + kWave - 1) / kWave;
     int sl = 0;
-    while (sl < (stress ? 1 : 3) && (groups << (sl + 1)) <= 4096 && (2 << sl) <= units) ++sl;
+    while (sl < (stress ? 1 : 3) && (groups << (sl + 1)) <= 16384 && (2 << sl) <= units) ++sl;
     const int per = (units + (1 << sl) - 1) >> sl;
     const int64_t gpb = kSplitWaves >> sl;
     return LayoutSplit{sl, per >= 4 ? 4 : (per >= 2 ? 2 : 1), (int)((groups + gpb - 1) / gpb)};

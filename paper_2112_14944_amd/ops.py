@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import math
+import operator
 from dataclasses import dataclass
 
 import numpy as np
@@ -262,15 +263,13 @@ def layout_step(delta, x, with_stress=False, out=None, ws=None):
 
 
 def layout(delta, x0, steps):
-    """`steps` Jacobi sweeps from x0 (one launch per sweep)."""
+    """`steps` Jacobi sweeps from x0 (one call into the library)."""
     k = _check_layout(delta, x0)
-    ws = _ws(L.lib().layout_workspace(k), x0.device)
-    a = x0.clone()
-    b = torch.empty_like(x0)
-    for _ in range(steps):
-        layout_step(delta, a, out=b, ws=ws)
-        a, b = b, a
-    return a
+    out = torch.empty_like(x0)
+    ws = _ws(L.lib().layout_run_workspace(k), x0.device)
+    L.check("layout_run", L.lib().layout_run(_ptr(delta), k, _ptr(x0), _ptr(out), max(operator.index(steps), 0),
+                                              _ptr(ws), ws.numel(), _stream(x0.device)))
+    return out
 
 
 def layout_metrics(x, g: Csr | None = None):

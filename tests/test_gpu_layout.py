@@ -112,3 +112,36 @@ def test_pdist_backward(ops, k):
     np.fill_diagonal(want, 0.0)
     scale = np.abs(want).max()
     assert np.abs(got - want).max() <= 1e-5 * scale
+
+
+# one launch for all sweeps up to 192 nodes (64 rows per pass of its block), one
+# launch per sweep above, with 8, 4 or 2 waves on a row group by size
+@pytest.mark.parametrize("k", [1, 2, 25, 63, 64, 65, 128, 129, 192, 193, 257, 1023, 2050, 8195, 17001])
+def test_layout_run(ops, k):
+    steps = 3 if k > 3000 else 7
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    D = torch.rand((k, k), device="cuda", generator=gen) * 8 + 2
+    D = torch.triu(D, 1)
+    D = (D + D.T).contiguous()
+    X = (torch.rand((k, 2), device="cuda", generator=gen) * 2 - 1).contiguous()
+    if k > 30:
+        X[3] = X[7]  # a coincident pair
+    got = ops.layout(D, X, steps)
+    assert torch.equal(ops.layout(D, X, 0), X)
+    # FP64 sweeps of the same formula, by row blocks
+    want = X.double()
+    for _ in range(steps if k > 1 else 0):
+        nxt = torch.empty_like(want)
+        for a in range(0, k, 2048):
+            b = min(k, a + 2048)
+            d = D[a:b].double()
+            inv = torch.where(d > 0, 1.0 / d, 0.0)
+            dx = want[a:b, None, 0] - want[None, :, 0]
+            dy = want[a:b, None, 1] - want[None, :, 1]
+            r = torch.sqrt(dx * dx + dy * dy)
+            c = torch.where(r > 0, inv / r, 0.0)
+            w = inv * inv
+            nxt[a:b] = (w @ want + torch.stack([(c * dx).sum(1), (c * dy).sum(1)], 1)) / w.sum(1, keepdim=True)
+        want = nxt
+    # the package's bar of one step (1e-5 of the layout's scale) for the few steps
+    assert (got.double() - want).abs().max().item() <= STEP_REL * want.abs().max().item()
