@@ -13,10 +13,17 @@
 //   direction:  beta = r.r(new) / r.r(old);  p = r + beta p;  stop test
 // Every dot product is summed in FP64 from per-block partials in a fixed
 // order, so the iterates do not depend on scheduling.  The host launches the
-// iterations in batches (8, then doubling) and reads the stop flag after each;
-// kernels launched after the flag is set return at once.  The apply is the
-// pairwise row sweep of the Jacobi step (4 rows per wave, lanes striding
-// over j, 4 columns of loads in flight); it reads Delta once, 4 k^2 bytes.
+// iterations in batches of 8, later 32, and reads the stop flag after each;
+// kernels launched after the flag is set return at once.  The apply is a
+// pairwise row sweep like the Jacobi step's (16 rows per block, four waves on
+// each group of 4 rows); it reads Delta once, 4 k^2 bytes.
+//
+// Bound: launches and latency.  Up to kCgOneBlock nodes update and direction
+// are one launch of one block, which needs no partials between them; up to
+// kCgOneLaunch nodes the whole solve is one block of the batch form's kernel.
+// k = 4096, per iteration: apply 15.8, update 3.6 and direction 3.4 us with
+// one wave per 4 rows and two vector launches; apply 11.3 (5.9 TB/s) and step
+// 5.4 us now.
 #include <math.h>
 
 #include <algorithm>
@@ -116,106 +123,123 @@ __global__ void cg_center_kernel(const float2* __restrict__ y, int32_t k, const 
     x[i] = make_float2((float)((double)y[i].x - st->mean[0]), (float)((double)y[i].y - st->mean[1]));
 }
 
-// Pairwise pass of 16 rows per block.
+constexpr int kCgOneBlock = 8192;  // nodes up to which one block takes update and direction
+constexpr int kCgOneLaunch = 192;  // nodes up to which one block takes the whole solve
+constexpr int kCgSplit = 4;        // waves per group of 4 rows
+constexpr int kCgRowThreads = kCgRows / kLayoutRowsPerWave * kCgSplit * kWave;
+
+// Pairwise pass of 16 rows per block: four groups of 4 rows, each shared by
+// four waves that take every fourth piece of U x 64 columns and add their sums
+// through LDS in wave order.
 //  kCgRhs (x = Y):   b_i = sum_j c_ij (Y_i - Y_j), c = 1/(Delta d) (0 when
 //                    coincident), and r_i = b_i - sum_j w_ij (Y_i - Y_j), which
 //                    is b - L^w x0 because L^w annihilates the mean; writes
 //                    r and p = r; partials |b|^2, |r|^2 per coordinate.
 //  kCgApply (x = p): Ap_i = sum_j w_ij (p_i - p_j); partials p . Ap.
-template <int MODE>
-__global__ __launch_bounds__(256) void cg_rows_kernel(const float* __restrict__ delta, int32_t k,
-                                                      const float2* __restrict__ x, float2* __restrict__ out_a,
-                                                      float2* __restrict__ out_b, double* __restrict__ part,
-                                                      const CgState* __restrict__ st) {
+template <int MODE, int U>
+__global__ __launch_bounds__(kCgRowThreads) void cg_rows_kernel(const float* __restrict__ delta, int32_t k,
+                                                              const float2* __restrict__ x,
+                                                              float2* __restrict__ out_a,
+                                                              float2* __restrict__ out_b, double* __restrict__ part,
+                                                              const CgState* __restrict__ st) {
     if (st->done) return;
     constexpr int R = kLayoutRowsPerWave;
-    __shared__ double red[4][4];
+    constexpr int NV = MODE == kCgRhs ? 4 : 2;
+    __shared__ float sums[kCgRowThreads / kWave][R][NV];
+    __shared__ double red[kCgRows][4];
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int row_begin = blockIdx.x * kCgRows + wave * R;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int row0 = blockIdx.x * kCgRows + wave / kCgSplit * R;
     float2 xi[R];
-    bool ok[R];
+    const float* drow[R];
     float bx[R], by[R], lx[R], ly[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int i = row_begin + r;
-        ok[r] = i < k;
-        xi[r] = ok[r] ? x[i] : make_float2(0.f, 0.f);
+        const int i = min(row0 + r, k - 1);  // rows past k repeat the last one; nothing of them is stored
+        xi[r] = x[i];
+        drow[r] = delta + (int64_t)i * k;
         bx[r] = by[r] = lx[r] = ly[r] = 0.f;
     }
-    auto pair = [&](int r, float Dv, bool off, float2 xj) {
-        const float inv = off ? __builtin_amdgcn_rcpf(Dv) : 0.f;
-        const float w = inv * inv;
-        const float dx = xi[r].x - xj.x;
-        const float dy = xi[r].y - xj.y;
-        lx[r] = fmaf(w, dx, lx[r]);
-        ly[r] = fmaf(w, dy, ly[r]);
-        if (MODE == kCgRhs) {
-            const float rs = __builtin_amdgcn_rsqf(fmaf(dx, dx, fmaf(dy, dy, kMinSq)));
-            const float c = inv * rs;
-            bx[r] = fmaf(c, dx, bx[r]);
-            by[r] = fmaf(c, dy, by[r]);
+    auto piece = [&](int c0, bool full) {
+        float2 xv[U];
+        float dv[U][R];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = full ? c0 + u * kWave + lane : min(c0 + u * kWave + lane, k - 1);
+            xv[u] = x[j];
+#pragma unroll
+            for (int r = 0; r < R; ++r) dv[u][r] = drow[r][j];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = c0 + u * kWave + lane;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const bool off = (full || j < k) && j != row0 + r;
+                const float inv = off ? __builtin_amdgcn_rcpf(dv[u][r]) : 0.f;
+                const float w = inv * inv;
+                const float dx = xi[r].x - xv[u].x;
+                const float dy = xi[r].y - xv[u].y;
+                lx[r] = fmaf(w, dx, lx[r]);
+                ly[r] = fmaf(w, dy, ly[r]);
+                if (MODE == kCgRhs) {
+                    const float rs = __builtin_amdgcn_rsqf(fmaf(dx, dx, fmaf(dy, dy, kMinSq)));
+                    const float c = inv * rs;
+                    bx[r] = fmaf(c, dx, bx[r]);
+                    by[r] = fmaf(c, dy, by[r]);
+                }
+            }
         }
     };
-    int j = lane;
-    if (row_begin + R <= k) {
-        const float* __restrict__ drow = delta + (int64_t)row_begin * k;
-        for (; j + 3 * kWave < k; j += 4 * kWave) {
-            float2 xv[4];
-            float dv[4][R];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                xv[u] = x[j + u * kWave];
-#pragma unroll
-                for (int r = 0; r < R; ++r) dv[u][r] = drow[(int64_t)r * k + j + u * kWave];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int r = 0; r < R; ++r) pair(r, dv[u][r], j + u * kWave != row_begin + r, xv[u]);
-        }
+    if (row0 < k) {
+        int c0 = wave % kCgSplit * (U * kWave);
+        for (; c0 + U * kWave <= k; c0 += kCgSplit * U * kWave) piece(c0, true);
+        if (c0 < k) piece(c0, false);
     }
-    for (; j < k; j += kWave) {
-        const float2 xj = x[j];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (ok[r]) pair(r, delta[(int64_t)(row_begin + r) * k + j], j != row_begin + r, xj);
-    }
-    double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (!ok[r]) continue;  // wave-uniform
-        const int i = row_begin + r;
-        const float sx = wave_sum(lx[r]);
-        const float sy = wave_sum(ly[r]);
+        float v[4] = {wave_sum_last(lx[r]), wave_sum_last(ly[r]), 0.f, 0.f};
         if (MODE == kCgRhs) {
-            const float tx = wave_sum(bx[r]);
-            const float ty = wave_sum(by[r]);
-            const float2 rv = make_float2(tx - sx, ty - sy);
-            if (lane == 0) {
+            v[2] = wave_sum_last(bx[r]);
+            v[3] = wave_sum_last(by[r]);
+        }
+        if (lane == 63)
+#pragma unroll
+            for (int c = 0; c < NV; ++c) sums[wave][r][c] = v[c];
+    }
+    __syncthreads();
+    if (threadIdx.x < kCgRows) {
+        const int g = threadIdx.x / R, r = threadIdx.x % R;
+        const int i = blockIdx.x * kCgRows + threadIdx.x;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int w = g * kCgSplit; w < (g + 1) * kCgSplit; ++w)
+#pragma unroll
+            for (int c = 0; c < NV; ++c) v[c] += sums[w][r][c];
+        double d[4] = {0.0, 0.0, 0.0, 0.0};
+        if (i < k) {
+            if (MODE == kCgRhs) {
+                const float2 rv = make_float2(v[2] - v[0], v[3] - v[1]);
                 out_a[i] = rv;
                 out_b[i] = rv;
+                d[0] = (double)v[2] * v[2];
+                d[1] = (double)v[3] * v[3];
+                d[2] = (double)rv.x * rv.x;
+                d[3] = (double)rv.y * rv.y;
+            } else {
+                out_a[i] = make_float2(v[0], v[1]);
+                const float2 p = x[i];
+                d[0] = (double)p.x * v[0];
+                d[1] = (double)p.y * v[1];
             }
-            d0 += (double)tx * tx;
-            d1 += (double)ty * ty;
-            d2 += (double)rv.x * rv.x;
-            d3 += (double)rv.y * rv.y;
-        } else {
-            if (lane == 0) out_a[i] = make_float2(sx, sy);
-            d0 += (double)xi[r].x * sx;
-            d1 += (double)xi[r].y * sy;
         }
-    }
-    if (lane == 0) {
-        red[wave][0] = d0;
-        red[wave][1] = d1;
-        red[wave][2] = d2;
-        red[wave][3] = d3;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) red[threadIdx.x][c] = d[c];
     }
     __syncthreads();
     if (threadIdx.x < 4) {
-        const int c = threadIdx.x;
-        part[(int64_t)blockIdx.x * 4 + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
+        double t = 0.0;
+        for (int r = 0; r < kCgRows; ++r) t += red[r][threadIdx.x];
+        part[(int64_t)blockIdx.x * 4 + threadIdx.x] = t;
     }
 }
 
@@ -307,6 +331,87 @@ __global__ __launch_bounds__(256) void cg_direction_kernel(int32_t k, int32_t it
     }
 }
 
+// Fixed-order sum of two FP64 values per thread over a block of 16 waves
+// (wave trees and a tree over the waves, by DPP); every thread gets both.
+constexpr int kCgWaves = 16;
+__device__ __forceinline__ void cg_block_sum2(double& a, double& b, double (*red)[kCgWaves]) {
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    a = wave_sum_last(a);
+    b = wave_sum_last(b);
+    __syncthreads();  // the previous sum's readers are done with red
+    if (lane == 63) {
+        red[0][wave] = a;
+        red[1][wave] = b;
+    }
+    __syncthreads();
+    a = row_sum16(red[0][lane & 15]);
+    b = row_sum16(red[1][lane & 15]);
+}
+
+// Update and direction of one iteration in one block of 1024 (k <= kCgOneBlock):
+// the same arithmetic, with |r|^2 summed in the block.
+constexpr int kCgStepThreads = 1024;
+static_assert(kCgStepThreads / kWave == kCgWaves, "cg_block_sum2");
+
+__global__ __launch_bounds__(kCgStepThreads) void cg_step_kernel(int32_t k, int32_t it,
+                                                               const double* __restrict__ part_rows,
+                                                               int64_t row_blocks, float2* __restrict__ p,
+                                                               const float2* __restrict__ ap,
+                                                               float2* __restrict__ x, float2* __restrict__ r,
+                                                               double tol2, CgState* __restrict__ st) {
+    constexpr int kPer = kCgOneBlock / kCgStepThreads;
+    __shared__ double red[2][kCgWaves];
+    if (st->done) return;
+    const double r0 = st->rr[it & 1][0], r1 = st->rr[it & 1][1];
+    const double b0 = st->bb[0], b1 = st->bb[1];
+    const int tid = threadIdx.x;
+    // vectors first: they do not wait for the sums
+    float2 pv[kPer], av[kPer], xv[kPer], rv[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = tid + u * kCgStepThreads;
+        if (i >= k) continue;
+        pv[u] = p[i];
+        av[u] = ap[i];
+        xv[u] = x[i];
+        rv[u] = r[i];
+    }
+    double p0 = 0.0, p1 = 0.0;
+    for (int64_t i = tid; i < row_blocks; i += kCgStepThreads) {
+        p0 += part_rows[i * 4];
+        p1 += part_rows[i * 4 + 1];
+    }
+    cg_block_sum2(p0, p1, red);
+    const float a0 = p0 > 0.0 ? (float)(r0 / p0) : 0.f;
+    const float a1 = p1 > 0.0 ? (float)(r1 / p1) : 0.f;
+    double n0 = 0.0, n1 = 0.0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = tid + u * kCgStepThreads;
+        if (i >= k) continue;
+        rv[u].x = fmaf(-a0, av[u].x, rv[u].x);
+        rv[u].y = fmaf(-a1, av[u].y, rv[u].y);
+        r[i] = rv[u];
+        x[i] = make_float2(fmaf(a0, pv[u].x, xv[u].x), fmaf(a1, pv[u].y, xv[u].y));
+        n0 += (double)rv[u].x * rv[u].x;
+        n1 += (double)rv[u].y * rv[u].y;
+    }
+    cg_block_sum2(n0, n1, red);
+    const float e0 = r0 > 0.0 ? (float)(n0 / r0) : 0.f;
+    const float e1 = r1 > 0.0 ? (float)(n1 / r1) : 0.f;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = tid + u * kCgStepThreads;
+        if (i < k) p[i] = make_float2(fmaf(e0, pv[u].x, rv[u].x), fmaf(e1, pv[u].y, rv[u].y));
+    }
+    if (tid == 0) {
+        st->rr[(it + 1) & 1][0] = n0;
+        st->rr[(it + 1) & 1][1] = n1;
+        st->iters = it + 1;
+        if (n0 <= tol2 * b0 && n1 <= tol2 * b1) st->done = 1;
+    }
+}
 
 // ---------------------------------------------------------------- batch form
 // The exact step for every subgraph of a batch in one launch: one block of
@@ -318,27 +423,7 @@ __global__ __launch_bounds__(256) void cg_direction_kernel(int32_t k, int32_t it
 constexpr int kCgBatchMaxN = Res<16>::NMAX;  // the batch's largest subgraph (2304, the resident PPR tile's limit)
 constexpr int kCgBatchThreads = 1024;
 constexpr int kCgBatchWaves = kCgBatchThreads / kWave;
-
-// Fixed-order block sum of two FP64 values per thread; every thread gets both.
-__device__ __forceinline__ void cg_batch_sum2(double& a, double& b, double (*red)[kCgBatchWaves]) {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    a = wave_sum(a);
-    b = wave_sum(b);
-    __syncthreads();  // the previous sum's readers are done with red
-    if (lane == 0) {
-        red[0][wave] = a;
-        red[1][wave] = b;
-    }
-    __syncthreads();
-    double s0 = 0.0, s1 = 0.0;
-    for (int w = 0; w < kCgBatchWaves; ++w) {
-        s0 += red[0][w];
-        s1 += red[1][w];
-    }
-    a = s0;
-    b = s1;
-}
+static_assert(kCgBatchWaves == kCgWaves, "cg_block_sum2");
 
 // Row pass over subgraph rows with v = Y (RHS: b_i and r_i = b_i - (L^w Y)_i,
 // written to r and p; FP64 |b|^2 and |r|^2 per coordinate) or v = p (APPLY:
@@ -419,18 +504,20 @@ __device__ __forceinline__ void cg_batch_rows(const float* __restrict__ delta, i
     }
 }
 
+// node_off == nullptr: one layout of n_single nodes.
 __global__ __launch_bounds__(kCgBatchThreads) void cg_batch_kernel(const int64_t* __restrict__ node_off,
                                                                    const int64_t* __restrict__ mat_off,
+                                                                   int32_t n_single,
                                                                    const float* __restrict__ delta_pool,
                                                                    const float2* __restrict__ x_in,
                                                                    float2* __restrict__ x_out, double tol2,
                                                                    int32_t max_iter, int32_t* __restrict__ iters_out,
                                                                    int32_t* __restrict__ conv_out) {
     __shared__ float2 Y[kCgBatchMaxN], X[kCgBatchMaxN], Rv[kCgBatchMaxN], P[kCgBatchMaxN], AP[kCgBatchMaxN];
-    __shared__ double red[2][kCgBatchWaves];
+    __shared__ double red[2][kCgWaves];
     const int g = blockIdx.x;
-    const int64_t base = node_off[g];
-    const int64_t kk = node_off[g + 1] - base;
+    const int64_t base = node_off ? node_off[g] : 0;
+    const int64_t kk = node_off ? node_off[g + 1] - base : n_single;
     if (kk < 1 || kk > kCgBatchMaxN) {  // uniform in the block
         if (threadIdx.x == 0) {
             if (iters_out) iters_out[g] = -1;
@@ -439,7 +526,7 @@ __global__ __launch_bounds__(kCgBatchThreads) void cg_batch_kernel(const int64_t
         return;
     }
     const int k = (int)kk;
-    const float* __restrict__ delta = delta_pool + mat_off[g];
+    const float* __restrict__ delta = delta_pool + (mat_off ? mat_off[g] : 0);
     // centred start x0 = Y - mean(Y), mean in FP64
     double mx = 0.0, my = 0.0;
     for (int i = threadIdx.x; i < k; i += kCgBatchThreads) {
@@ -448,7 +535,7 @@ __global__ __launch_bounds__(kCgBatchThreads) void cg_batch_kernel(const int64_t
         mx += (double)y.x;
         my += (double)y.y;
     }
-    cg_batch_sum2(mx, my, red);
+    cg_block_sum2(mx, my, red);
     mx /= k;
     my /= k;
     for (int i = threadIdx.x; i < k; i += kCgBatchThreads)
@@ -456,14 +543,14 @@ __global__ __launch_bounds__(kCgBatchThreads) void cg_batch_kernel(const int64_t
     __syncthreads();
     double b0 = 0.0, b1 = 0.0, r0 = 0.0, r1 = 0.0;
     cg_batch_rows<kCgRhs>(delta, k, Y, Rv, P, b0, b1, r0, r1);
-    cg_batch_sum2(b0, b1, red);
-    cg_batch_sum2(r0, r1, red);
+    cg_block_sum2(b0, b1, red);
+    cg_block_sum2(r0, r1, red);
     bool done = r0 <= tol2 * b0 && r1 <= tol2 * b1;
     int it = 0;
     for (; !done && it < max_iter; ++it) {
         double p0 = 0.0, p1 = 0.0, unused0 = 0.0, unused1 = 0.0;
         cg_batch_rows<kCgApply>(delta, k, P, AP, nullptr, p0, p1, unused0, unused1);
-        cg_batch_sum2(p0, p1, red);  // its barriers also order the Ap writes before the reads below
+        cg_block_sum2(p0, p1, red);  // its barriers also order the Ap writes before the reads below
         const float a0 = p0 > 0.0 ? (float)(r0 / p0) : 0.f;
         const float a1 = p1 > 0.0 ? (float)(r1 / p1) : 0.f;
         double n0 = 0.0, n1 = 0.0;
@@ -479,7 +566,7 @@ __global__ __launch_bounds__(kCgBatchThreads) void cg_batch_kernel(const int64_t
             n0 += (double)rv.x * rv.x;
             n1 += (double)rv.y * rv.y;
         }
-        cg_batch_sum2(n0, n1, red);
+        cg_block_sum2(n0, n1, red);
         const float e0 = r0 > 0.0 ? (float)(n0 / r0) : 0.f;
         const float e1 = r1 > 0.0 ? (float)(n1 / r1) : 0.f;
         for (int i = threadIdx.x; i < k; i += kCgBatchThreads) {
@@ -533,32 +620,51 @@ ppr_status layout_step_exact(const float* delta, int32_t k, const float* x_in, f
     const double tol2 = cg_tol * cg_tol;
     const int64_t rb = cg_row_blocks(k), vb = cg_vec_blocks(k);
 
+    CgState hs{};
+    auto read_state = [&]() -> ppr_status {
+        if (launch_status() != PPR_OK) return PPR_EHIP;
+        PPRVIZ_HIP_TRY(hipMemcpyAsync(&hs, w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
+        PPRVIZ_HIP_TRY(hipStreamSynchronize(s));
+        return PPR_OK;
+    };
+    ppr_status rs = PPR_OK;
+    if (k <= kCgOneLaunch) {
+        hipLaunchKernelGGL(cg_batch_kernel, dim3(1), dim3(kCgBatchThreads), 0, s, nullptr, nullptr, k, delta, y, x,
+                           tol2, cg_max_iter, &w.st->iters, &w.st->done);
+        if ((rs = read_state()) != PPR_OK) return rs;
+        if (cg_iters_out) *cg_iters_out = hs.iters;
+        return hs.done ? PPR_OK : PPR_ENOCONV;
+    }
+
     hipLaunchKernelGGL(cg_mean_kernel, dim3(1), dim3(256), 0, s, y, k, w.st);
     hipLaunchKernelGGL(cg_center_kernel, dim3((unsigned)vb), dim3(kCgVec), 0, s, y, k, w.st, x);
-    hipLaunchKernelGGL((cg_rows_kernel<kCgRhs>), dim3((unsigned)rb), dim3(256), 0, s, delta, k, y, w.r, w.p,
-                       w.part_rows, w.st);
+    hipLaunchKernelGGL((cg_rows_kernel<kCgRhs, 4>), dim3((unsigned)rb), dim3(kCgRowThreads), 0, s, delta, k, y, w.r,
+                       w.p, w.part_rows, w.st);
     hipLaunchKernelGGL(cg_init_kernel, dim3(1), dim3(256), 0, s, w.part_rows, rb, tol2, w.st);
 
-    // Iterations in growing batches; between batches the host reads the
-    // stop flag.  Kernels launched after the flag is set return at once.
+    // Iterations in batches; between batches the host reads the stop flag (the
+    // GPU is idle for 40-80 us meanwhile; an iteration launched past the end
+    // takes 9 us).
     int32_t launched = 0, batch = 8;
-    CgState hs{};
     while (true) {
         const int32_t end = std::min(cg_max_iter, launched + batch);
         for (int32_t it = launched; it < end; ++it) {
-            hipLaunchKernelGGL((cg_rows_kernel<kCgApply>), dim3((unsigned)rb), dim3(256), 0, s, delta, k, w.p, w.ap,
-                               nullptr, w.part_rows, w.st);
+            hipLaunchKernelGGL((cg_rows_kernel<kCgApply, 8>), dim3((unsigned)rb), dim3(kCgRowThreads), 0, s, delta, k,
+                               w.p, w.ap, nullptr, w.part_rows, w.st);
+            if (k <= kCgOneBlock) {
+                hipLaunchKernelGGL(cg_step_kernel, dim3(1), dim3(kCgStepThreads), 0, s, k, it, w.part_rows, rb, w.p,
+                                   w.ap, x, w.r, tol2, w.st);
+                continue;
+            }
             hipLaunchKernelGGL(cg_update_kernel, dim3((unsigned)vb), dim3(kCgVec), 0, s, k, it, w.part_rows, rb, w.p,
                                w.ap, x, w.r, w.part_vec, w.st);
             hipLaunchKernelGGL(cg_direction_kernel, dim3((unsigned)vb), dim3(kCgVec), 0, s, k, it, w.part_vec, vb,
                                tol2, w.r, w.p, w.st);
         }
         launched = end;
-        if (launch_status() != PPR_OK) return PPR_EHIP;
-        PPRVIZ_HIP_TRY(hipMemcpyAsync(&hs, w.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
-        PPRVIZ_HIP_TRY(hipStreamSynchronize(s));
+        if ((rs = read_state()) != PPR_OK) return rs;
         if (hs.done || launched >= cg_max_iter) break;
-        batch = std::min(batch * 2, 128);
+        batch = launched < 64 ? 8 : 32;
     }
     if (cg_iters_out) *cg_iters_out = hs.iters;
     return hs.done ? PPR_OK : PPR_ENOCONV;
@@ -575,7 +681,7 @@ ppr_status pprviz_batch_step_exact(const ppr_batch* b, const float* delta_pool, 
     if (b->max_n > kCgBatchMaxN) return PPR_EUNSUPPORTED;
     if (pending_error() != PPR_OK) return PPR_EHIP;
     hipLaunchKernelGGL(cg_batch_kernel, dim3((unsigned)b->n_graphs), dim3(kCgBatchThreads), 0,
-                       static_cast<hipStream_t>(stream), b->node_off, b->mat_off, delta_pool,
+                       static_cast<hipStream_t>(stream), b->node_off, b->mat_off, 0, delta_pool,
                        reinterpret_cast<const float2*>(x_in), reinterpret_cast<float2*>(x_out), cg_tol * cg_tol,
                        cg_max_iter, iters_out, converged_out);
     return launch_status();
