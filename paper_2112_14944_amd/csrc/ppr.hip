@@ -469,7 +469,7 @@ static void launch_resident_any(bool weighted, const ResArgs& a, int n, int64_t 
 
 // One product of the all-pairs series (ppr_dense.hpp), one 64-wide tile per
 // block: a single graph has too few 128-wide tiles to fill the chip (n = 2048:
-// 136 of them, 204 us a product; 528 64-wide ones, 136 us).
+// 136 of them, 204 us a product; 528 64-wide ones, 136 us then, 125 us now).
 constexpr int kSingleBT = 64;
 
 __global__ __launch_bounds__(kDenseThreads, 2) void ppr_product_kernel(const float* V, const float* Ym,

@@ -202,7 +202,7 @@ static __global__ void query_init_kernel(const int32_t* __restrict__ src, const 
 static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
     const float* __restrict__ lo, const float* __restrict__ hi, int use_hi, const float* __restrict__ deg,
     float scale, int32_t n, int W, int32_t ld, int32_t k, int32_t rows, float* __restrict__ part) {
-    constexpr int KB = dense_k(64);
+    constexpr int KB = kDenseK;
     constexpr int NP = KB / 4;
     __shared__ DenseLds<64> L;
     int I, J;
@@ -238,15 +238,16 @@ static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
         __syncthreads();
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            L.a[0][lr + 4 * p][lc] = ra[p];
-            L.b[0][lr + 4 * p][lc] = rb[p];
+            const int row = lr + 4 * p, col = lc ^ (32 * (row & 1));
+            L.a[0][row][col] = ra[p];
+            L.b[0][row][col] = rb[p];
         }
         __syncthreads();
         fetch(v + KB);
 #pragma unroll
         for (int kk = 0; kk < KB; kk += 2)
-            c = __builtin_amdgcn_mfma_f32_32x32x2f32(L.a[0][kk + half][wi + l32], L.b[0][kk + half][wj + l32], c, 0,
-                                                     0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x2f32(L.a[0][kk + half][(wi ^ (32 * half)) + l32],
+                                                     L.b[0][kk + half][(wj ^ (32 * half)) + l32], c, 0, 0, 0);
     }
     float* out = part + (int64_t)blockIdx.y * k * k;
 #pragma unroll
