@@ -62,6 +62,37 @@ def test_weight_gradient_adjoint(n, T):
     assert ((got - want).norm() / want.norm()).item() <= 2e-5
 
 
+# rows of 1 to n - 1 arcs, so that a block's 32 arcs are many rows, one, or a
+# part of one; 63, 64 and 513 around a wave's and eight waves' columns
+@pytest.mark.parametrize("n", [63, 64, 257, 513, 1000])
+def test_weight_gradient_hub_rows(n):
+    ops = get_ops()
+    T = 60
+    rng = np.random.default_rng(n)
+    eu = np.concatenate([np.zeros(n - 1, np.int64), np.arange(1, n - 1), rng.integers(n // 2, n - 1, 40 * (n // 16))])
+    ev = np.concatenate([np.arange(1, n), np.arange(2, n), np.full(40 * (n // 16), n - 1)])
+    e = np.unique(np.stack([eu, ev], 1), axis=0)
+    g = synth.build_graph(n, e[:, 0], e[:, 1], (0.5 + rng.random(len(e))).astype(np.float32))
+    csr = ops.Csr.from_graph(g, "cuda")
+    G = torch.randn((n, n), device="cuda", generator=torch.Generator(device="cuda").manual_seed(n))
+    G = (torch.triu(G, 1) + torch.triu(G, 1).T).contiguous()
+    print(f"[hub rows] n={n} nnz={g.nnz}", flush=True)
+    got = ops.ppr_matrix_backward(csr, ALPHA, T, None, G).double()
+    W, d, Q, rows, cols = _walk64(g)
+    pi = torch.zeros_like(Q)
+    A = torch.zeros_like(Q)
+    for _ in range(T):
+        pi = ALPHA * torch.eye(n, dtype=torch.float64, device="cuda") + pi @ Q
+        A = d[:, None] * G.double() + Q.T.contiguous() @ A
+    dq = (A @ pi.T.contiguous())[rows, cols]
+    row = torch.zeros(n, dtype=torch.float64, device="cuda").index_add_(0, rows, W[rows, cols] / d[rows] * dq)
+    both = torch.zeros_like(Q)
+    both[rows, cols] = (1 - ALPHA) / d[rows] * (dq - row[rows]) + (G.double() * pi).sum(1)[rows]
+    want = (both + both.T)[rows, cols]
+    # as above: an entry of A is a sum of n FP32 terms, the rest FP64
+    assert ((got - want).norm() / want.norm()).item() <= 2e-5
+
+
 def _series_plan(n, nnz, T):
     """The number of products and the pieces of the all-pairs series (the rule
     of csrc/ppr_dense.hpp)."""
