@@ -9,7 +9,9 @@
 //     X_{t+1}[v] = alpha [v == s] + sum_{u in N(v)} w_vu Y_t[u].
 //
 // Preparation (once per call, on the device):
-//  - rows are sorted by degree, largest first, ties by id (stable scatter);
+//  - rows are sorted by degree, largest first, ties by id (stable scatter); a
+//    node's place in that order is its row of the LDS tile, so that the rows of
+//    a slice lie next to each other there;
 //  - rows longer than a wave's fair share are cut into parts whose partial
 //    sums are added back in a fixed order (mid_split_kernel);
 //  - the rows are cut into slices of 64, one row per lane, so the rows of a
@@ -19,14 +21,27 @@
 //    group g of the slice holds arcs 4g .. 4g+3 of each of its 64 rows, 4
 //    16-bit entries per lane, so one 8-byte load per lane reads 4 arcs of its
 //    row and a wave load is one contiguous 512-byte segment.  An entry is the
-//    LDS float index u * C of the neighbour's row; rows shorter than the
+//    LDS float index (row * C) of the neighbour; rows shorter than the
 //    slice point at a zero row.  Within a row, arcs are placed by LDS bank
 //    class so that the lanes of one LDS pass read different banks
 //    (mid_fill_kernel).  Each wave's slices are stored one after another, so
 //    a wave reads one contiguous stream per push.
 // A lane keeps the sums of its KS rows in registers until every wave has
 // finished gathering, then writes them back (synchronous update).
+//
+// Bound: instruction issue for one and two columns per block (four waves per
+// SIMD; a push without its LDS reads, its stream loads or half its additions
+// takes the same time to a few percent), the stream's way through the caches
+// for four weighted columns (38 bytes per cycle and CU; without the stream 8.7
+// of 13 ms).  So what counts is instructions per arc: slot ends found by count
+// inside one loop over the wave's groups, one wait per group, scales in
+// registers and contiguous writes (a slot's write-back took 25 instructions,
+// it takes 10), waves that yield as they get on.  n = 20000, 3.95e5 arcs, all
+// sources, 99 pushes: 75.6 ms before, 63.6 now; n = 8192, 1.95e5 weighted arcs:
+// 14.5 and 12.8 ms.  Bank conflicts hardly matter: free of them, 2% less.
 #pragma once
+
+#include <type_traits>
 
 #include "ppr_core.hpp"
 #include "ppr_stream.hpp"
@@ -38,7 +53,8 @@ constexpr int kMidWaves = kMidThreads / kWave;
 constexpr int kMidLdsFloats = 40832;  // 160 KB less the residual reduction scratch
 constexpr int kMidSlotCap = 48;       // slot table stride per wave (largest KS)
 constexpr int kMidGroup = 256;        // stream entries per group: 64 lanes x 4 arcs
-constexpr int kMidPrefetch = 2;       // groups each lane reads ahead
+constexpr int kMidPrefetch = 2;       // spare groups behind the stream
+constexpr int kMidAhead = 4;          // groups each lane's entries are read ahead
 constexpr int kMidKeys = 65536;       // exact degree classes of the row order
 constexpr int kMidMaxParts = 1024;    // parts of split rows: they fill at most the first 16 slices
 
@@ -163,12 +179,13 @@ static __global__ __launch_bounds__(1024) void mid_split_kernel(const RowEnt* __
             const int b = (int)min((int64_t)e.re, (int64_t)e.rs + (j + 1) * D);
             vrows[pb + j] = RowEnt{a, b, e.v, pb + j + 1};
         }
-        comb[h] = make_int4(e.v * C * 4, __float_as_int((1.0f - alpha) * invd[e.v]), part0 + pb * C * 4, m);
-        rowpos[e.v] = -1;
+        comb[h] = make_int4(h * C * 4, __float_as_int((1.0f - alpha) * invd[e.v]), part0 + pb * C * 4, m);
+        rowpos[e.v] = h;
     }
     for (int i = H + tid; i < n; i += 1024) {
         const RowEnt e = rows[i];
         vrows[P + i - H] = RowEnt{e.rs, e.re, e.v, 0};
+        rowpos[e.v] = i;
     }
     for (int i = tid; i < kMidWaves * kWave; i += 1024) part_dst[i] = -1;
 }
@@ -305,16 +322,25 @@ static __global__ __launch_bounds__(1024) void mid_plan_kernel(const RowEnt* __r
     }
 }
 
+// Slice lane of lane i of LDS pass p.  8-byte reads are served 32 lanes in
+// order at a time; 16-byte reads 16 at a time, lanes grouped by lane bit 5 and
+// the parity of lane bits 2..4 (a probe of the pairs of lanes that conflict).
+__device__ __forceinline__ int mid_pass_lane(int C, int p, int i) {
+    if (C != 4) return p * (kWave / C) + i;
+    const int quads = (p & 1) ? 0x7421 : 0x6530;  // the four quads of 8, one per hex digit
+    return 32 * (p >> 1) + 4 * ((quads >> (4 * ((i >> 2) & 3))) & 15) + (i & 3);
+}
+
 // One wave per LDS pass of a slice (C waves per slice, M = 64 / C rows
 // each): the arc stream of its rows, as LDS float indices
-// u * C (weights alongside), padded with the zero row n * C; a row without
+// row * C (weights alongside), padded with the zero row n * C; a row without
 // arcs gets one arc to itself of weight 1 (the implicit self-loop).  Also the
-// rows' LDS byte addresses (u * 4 C) and scales (1-alpha)/d in their slot's table.
+// rows' scales (1-alpha)/d in their slot's table.
 //
 // Arcs are dealt to stream positions by LDS bank class.  Row u of the tile
 // starts at bank (u * C) mod 64, so its class is u mod M, M = 64 / C, and one
-// LDS pass of the gather serves M lanes (256 bytes).  For each position k and
-// each pass, the pass's lanes that still have arcs choose in turn (starting
+// LDS pass of the gather serves M lanes (256 bytes, mid_pass_lane).  For each
+// position k and each pass, the pass's lanes that still have arcs choose in turn (starting
 // at a lane that moves with k) an arc from a class used least so far in that
 // pass (0, 1, 2 or more times; the zero row read by finished lanes counts
 // once), ties broken from a preferred class that moves with lane and k.  Each
@@ -326,9 +352,9 @@ static __global__ __launch_bounds__(64) void mid_fill_kernel(
     const float* __restrict__ invd, int32_t n, int32_t C, float alpha, const int32_t* __restrict__ plan,
     const int32_t* __restrict__ slice_goff, const int32_t* __restrict__ slice_slot, int32_t* __restrict__ tmp_u,
     float* __restrict__ tmp_w, uint16_t* __restrict__ sell, float* __restrict__ sellw, int2* __restrict__ vtab,
-    int32_t* __restrict__ part_dst, int32_t* __restrict__ rowpos) {
-    __shared__ int32_t beg[kWave][kWave];  // per lane and class: first bucketed arc
-    __shared__ int32_t pos[kWave][kWave];  // per lane and class: one past the last remaining arc
+    int32_t* __restrict__ part_dst, const int32_t* __restrict__ rowpos) {
+    __shared__ int32_t beg[kWave][kWave + 1];  // per lane and class: first bucketed arc
+    __shared__ int32_t pos[kWave][kWave + 1];  // per lane and class: one past the last remaining arc
     const int lane = threadIdx.x;
     if (plan[kPlanFlag] != 0) return;
     const int nv = plan[kPlanRows];  // rows after splitting
@@ -337,7 +363,7 @@ static __global__ __launch_bounds__(64) void mid_fill_kernel(
     const int64_t sl = blockIdx.x / passes;
     if (sl >= mid_slices(nv)) return;
     const int q0 = (int)(blockIdx.x % passes) * M;  // first slice lane of this pass
-    const int q = q0 + lane;                         // this lane's position in the slice
+    const int q = mid_pass_lane(C, (int)(blockIdx.x % passes), lane);  // this lane's position in the slice
     const uint64_t full = M == 64 ? ~0ull : ((1ull << M) - 1);
     const int slot = slice_slot[sl];
     const int64_t goff = slice_goff[sl];
@@ -351,11 +377,13 @@ static __global__ __launch_bounds__(64) void mid_fill_kernel(
         re = e.re;
         tag = e.pad;
     }
-    const bool self = v >= 0 && re == rs;
+    const int self = v >= 0 && re == rs ? rowpos[v] : -1;  // a row without arcs: its own place in the tile
     // bucket the row's arcs by class
     for (int c = 0; c < M; ++c) pos[lane][c] = 0;
     if (v >= 0)
-        for (int e = rs; e < re; ++e) ++pos[lane][col_idx[e] & (M - 1)];
+        for (int e = rs; e < re; ++e) ++pos[lane][rowpos[col_idx[e]] & (M - 1)];
+    uint2* d = reinterpret_cast<uint2*>(sell) + goff * 64 + q;
+    float4* dw = sellw ? reinterpret_cast<float4*>(sellw) + goff * 64 + q : nullptr;
     uint64_t avail = 0;
     int run = 0;
     for (int c = 0; c < M; ++c) {
@@ -367,16 +395,14 @@ static __global__ __launch_bounds__(64) void mid_fill_kernel(
     }
     if (v >= 0)
         for (int e = rs; e < re; ++e) {
-            const int u = col_idx[e];
+            const int u = rowpos[col_idx[e]];
             const int at = pos[lane][u & (M - 1)]++;
             tmp_u[rs + at] = u;
             if (weight) tmp_w[rs + at] = weight[e];
         }
-    if (self) avail = 1ull << (v & (M - 1));
+    if (self >= 0) avail = 1ull << (self & (M - 1));
     const int zc = n & (M - 1);
     const uint32_t zero = (uint32_t)n * (uint32_t)C;
-    uint2* d = reinterpret_cast<uint2*>(sell) + goff * 64 + q;
-    float4* dw = sellw ? reinterpret_cast<float4*>(sellw) + goff * 64 + q : nullptr;
     uint32_t pk[4];
     float pw[4];
     // the deal runs on the scalar unit: every value below except my_c and
@@ -429,8 +455,8 @@ static __global__ __launch_bounds__(64) void mid_fill_kernel(
         uint32_t u = zero;
         float w = 0.f;
         if (my_c >= 0) {
-            if (self) {
-                u = (uint32_t)v * (uint32_t)C;
+            if (self >= 0) {
+                u = (uint32_t)self * (uint32_t)C;
                 w = 1.f;
                 avail = 0;
             } else {
@@ -448,24 +474,22 @@ static __global__ __launch_bounds__(64) void mid_fill_kernel(
         }
     }
     if (lane < M) {
-        // a part of a split row is written through its partial slot, not here
-        vtab[(int64_t)slot * 64 + q] = (v >= 0 && tag == 0)
-                                           ? make_int2(v * C * 4, __float_as_int((1.0f - alpha) * invd[v]))
-                                           : make_int2(-1, 0);
+        vtab[(int64_t)slot * 64 + q] = make_int2((int)sl, v >= 0 ? __float_as_int((1.0f - alpha) * invd[v]) : 0);
+        // a part of a split row is written through its partial slot
         if (tag > 0 && slot % kMidSlotCap == 0)
             part_dst[(slot / kMidSlotCap) * kWave + q] = (n + 1) * C * 4 + (tag - 1) * C * 4;
-        if (v >= 0 && tag == 0) rowpos[v] = slot * 64 + q;
     }
 }
 
 struct MidArgs {
     const int32_t* plan;
-    const int32_t* rowpos;    // per node: its slot and lane, -1 when split
+    const int32_t* rowpos;    // per node: its row of the tile
+    const int32_t* slice_slot;
     const int32_t* part_dst;  // per wave and lane: LDS byte address of its slot-0 partial, or -1
     const int4* comb;         // per split row: row address, scale, first partial address, parts
     const uint16_t* sell;
     const float* sellw;  // nullptr: unit weights
-    const int2* vtab;
+    const int2* vtab;  // per slot and lane: slice, row's scale (1 - alpha) / d
     const float* invd;
     const float* deg;
     const int32_t* src;  // nullptr: column s is node s
@@ -480,35 +504,29 @@ struct MidArgs {
     double* resid;
 };
 
-// acc += w * Y[idx .. idx + C) (w = 1: plain sum).
-template <int C, bool WEIGHTED>
-__device__ __forceinline__ void mid_arc(const float* L, uint32_t idx, float w, float (&acc)[C]) {
+// Y[idx .. idx + C), and acc += w * y (unit weights: plain sum).
+template <int C>
+struct MidY {
+    float v[C];
+};
+
+template <int C>
+__device__ __forceinline__ MidY<C> mid_read(const float* L, uint32_t idx) {
+    MidY<C> y;
     if constexpr (C == 4) {
-        const float4 y = *reinterpret_cast<const float4*>(L + idx);
-        if (WEIGHTED) {
-            acc[0] = fmaf(w, y.x, acc[0]);
-            acc[1] = fmaf(w, y.y, acc[1]);
-            acc[2] = fmaf(w, y.z, acc[2]);
-            acc[3] = fmaf(w, y.w, acc[3]);
-        } else {
-            acc[0] += y.x;
-            acc[1] += y.y;
-            acc[2] += y.z;
-            acc[3] += y.w;
-        }
+        const float4 t = *reinterpret_cast<const float4*>(L + idx);
+        y.v[0] = t.x;
+        y.v[1] = t.y;
+        y.v[2] = t.z;
+        y.v[3] = t.w;
     } else if constexpr (C == 2) {
-        const float2 y = *reinterpret_cast<const float2*>(L + idx);
-        if (WEIGHTED) {
-            acc[0] = fmaf(w, y.x, acc[0]);
-            acc[1] = fmaf(w, y.y, acc[1]);
-        } else {
-            acc[0] += y.x;
-            acc[1] += y.y;
-        }
+        const float2 t = *reinterpret_cast<const float2*>(L + idx);
+        y.v[0] = t.x;
+        y.v[1] = t.y;
     } else {
-        const float y = L[idx];
-        acc[0] = WEIGHTED ? fmaf(w, y, acc[0]) : acc[0] + y;
+        y.v[0] = L[idx];
     }
+    return y;
 }
 
 template <int C, bool WEIGHTED>
@@ -528,16 +546,18 @@ __global__ __launch_bounds__(kMidThreads) void ppr_mid_kernel(MidArgs a) {
     for (int c = 0; c < C; ++c) sn[c] = s0 + c < a.n_src ? (a.src ? a.src[s0 + c] : s0 + c) : -1;
     const int wvu = __builtin_amdgcn_readfirstlane(wv);
     int sa[C];  // LDS byte address of each source's row (-8: no source)
-#pragma unroll
-    for (int c = 0; c < C; ++c) sa[c] = sn[c] >= 0 ? sn[c] * C * 4 : -8;
-    // slot and lane holding each source's row (-1: none, or a split row,
-    // which its combining lane handles)
-    int sslot[C], slane[C];  // slot of this wave (-1: another wave's or none) and lane
+    // slot (of this wave, else -1) and lane holding each source's row (none for
+    // a split row, which its combining lane handles)
+    int sslot[C], slane[C];
+    const int hubs = __builtin_amdgcn_readfirstlane(a.plan[kPlanHubs]);
+    const int shift = __builtin_amdgcn_readfirstlane(a.plan[kPlanRows]) - n;  // row index - tile row
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        const int sp = __builtin_amdgcn_readfirstlane(sn[c] >= 0 ? a.rowpos[sn[c]] : -1);
-        sslot[c] = (sp >= 0 && (sp >> 6) / kMidSlotCap == wvu) ? (sp >> 6) % kMidSlotCap : -1;
-        slane[c] = sp & 63;
+        const int at = __builtin_amdgcn_readfirstlane(sn[c] >= 0 ? a.rowpos[sn[c]] : -1);
+        sa[c] = at >= 0 ? at * C * 4 : -8;
+        const int sp = at >= hubs ? __builtin_amdgcn_readfirstlane(a.slice_slot[(at + shift) >> 6]) : -1;
+        sslot[c] = (sp >= 0 && sp / kMidSlotCap == wvu) ? sp % kMidSlotCap : -1;
+        slane[c] = (at + shift) & 63;
     }
 
     if (a.plan[kPlanFlag] != 0) {  // stream bound exceeded (repeated arcs): no result
@@ -562,7 +582,7 @@ __global__ __launch_bounds__(kMidThreads) void ppr_mid_kernel(MidArgs a) {
 #pragma unroll
     for (int c = 0; c < C; ++c)
         if (tid == c && T >= 1 && sn[c] >= 0)
-            L[sn[c] * C + c] = T == 1 ? alpha : alpha * (1.0f - alpha) * a.invd[sn[c]];
+            L[(sa[c] >> 2) + c] = T == 1 ? alpha : alpha * (1.0f - alpha) * a.invd[sn[c]];
     __syncthreads();
 
     const int gtab = lane < KS ? a.plan[wv * kMidSlotCap + lane] : 0;
@@ -570,104 +590,211 @@ __global__ __launch_bounds__(kMidThreads) void ppr_mid_kernel(MidArgs a) {
     int4 cmb = make_int4(-1, 0, 0, 0);  // split row this lane combines, if any
     if (tid < a.plan[kPlanHubs]) cmb = a.comb[tid];
     const int64_t start = a.plan[kPlanStart + wv];
-    using f4v = float __attribute__((ext_vector_type(4)));
-    const gcptr<uint64_t> sbase = as_global(reinterpret_cast<const uint64_t*>(a.sell)) + start * 64 + lane;
-    const gcptr<f4v> wbase = WEIGHTED ? as_global(reinterpret_cast<const f4v*>(a.sellw)) + start * 64 + lane : nullptr;
-    // slot table of this wave: a scalar base per 8 slots plus the lane's
-    // byte offset, so that its addresses take no vector registers
+    // this wave's slots in use and their groups; its part of the stream as a
+    // buffer that ends with it (reads past it return zeros)
+    const int slots = __builtin_popcountll(__ballot(gtab > 0));
+    int groups = 0;
+#pragma unroll
+    for (int p = 0; p < KS; ++p) groups += __builtin_amdgcn_readlane(gtab, p);
+    const __amdgpu_buffer_rsrc_t sbuf = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(a.sell) + __builtin_amdgcn_readfirstlane((int)start) * (int64_t)kMidGroup, 0,
+        groups * (kMidGroup * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(
+        WEIGHTED ? const_cast<float*>(a.sellw) + __builtin_amdgcn_readfirstlane((int)start) * (int64_t)kMidGroup
+                 : nullptr,
+        0, WEIGHTED ? groups * (kMidGroup * 4) : 0, 0x00020000);
+    // Each slot's first row of the tile in lane p of stab, and its rows' scales: in registers,
+    // except in a one-column tile, whose 48 slots leave no room for them; there
+    // they are read in each push, through a scalar base per 8 slots.
+    constexpr bool SCREG = KS <= 24;
+    const int stab = lane < KS && gtab > 0 ? a.vtab[(int64_t)(wv * kMidSlotCap + lane) * 64].x * kWave - shift : 0;
     const int64_t vt_wave = (int64_t)reinterpret_cast<uintptr_t>(a.vtab) + (int64_t)wvu * kMidSlotCap * 64 * 8;
+    float sc[SCREG ? KS : 1];
+    if (SCREG) {
+#pragma unroll
+        for (int p = 0; p < KS; ++p)
+            sc[p] = __builtin_amdgcn_readlane(gtab, p) > 0
+                        ? __int_as_float(a.vtab[(int64_t)(wv * kMidSlotCap + p) * 64 + lane].y)
+                        : 0.f;
+    }
 
-    float acc[KS][C];
+    using f12v = float __attribute__((ext_vector_type(12)));
+    using u2v = uint32_t __attribute__((ext_vector_type(2)));
+    using u4v = uint32_t __attribute__((ext_vector_type(4)));
+    f12v sums[KS / 12][C];  // finished slots, written by index
+#pragma unroll
+    for (int b = 0; b < KS / 12; ++b)
+#pragma unroll
+        for (int c = 0; c < C; ++c) sums[b][c] = f12v{};
     for (int it = 1; it < T; ++it) {
-        // ring of the next kMidPrefetch groups of this wave's stream (it runs
-        // on across slot boundaries: the wave's slices are stored in order)
-        constexpr int D = kMidPrefetch;
-        gcptr<uint64_t> sp = sbase + D * 64;
-        uint64_t q[D];
+        // One loop over the wave's groups, slot ends found by count; entries travel
+        // R groups ahead of their use and the Y values one group ahead of theirs.
+        // Groups past the last one (up to R - 1) read zeros from the stream and
+        // end up nowhere.
+        constexpr int R = kMidAhead;
+        // Registers: a plain tile of up to two columns reads a group's four Y
+        // values (last first, so that one wait covers them) before it adds the
+        // previous group's; the others re-read them two by two.
+        constexpr bool PAIRS = C == 4 || (C == 2 && WEIGHTED);
+        u2v q[R];
+        constexpr int RW = C == 1 ? R : R / 2;  // weights: half as far ahead
+        u4v r[RW];
+        MidY<C> y[PAIRS ? 1 : 2][4];
+        auto load_q = [&](int base, int j) {
+            return __builtin_amdgcn_raw_buffer_load_b64(sbuf, lane * 8 + j * (kMidGroup * 2), base * (kMidGroup * 2),
+                                                        0);
+        };
+        auto load_r = [&](int base, int j) {
+            return __builtin_amdgcn_raw_buffer_load_b128(wbuf, lane * 16 + j * (kMidGroup * 4),
+                                                         base * (kMidGroup * 4), 0);
+        };
+        auto read_hi = [&](const u2v& e, MidY<C>(&d)[4]) {
+            d[3] = mid_read<C>(L, e.y >> 16);
+            d[2] = mid_read<C>(L, e.y & 0xffffu);
+        };
+        auto read_lo = [&](const u2v& e, MidY<C>(&d)[4]) {
+            d[1] = mid_read<C>(L, e.x >> 16);
+            d[0] = mid_read<C>(L, e.x & 0xffffu);
+        };
 #pragma unroll
-        for (int j = 0; j < D; ++j) q[j] = sbase[j * 64];
-        gcptr<f4v> wp = nullptr;
-        f4v r[D];
-#pragma unroll
-        for (int j = 0; j < D; ++j) r[j] = f4v{1.f, 1.f, 1.f, 1.f};
-        if (WEIGHTED) {
-            wp = wbase + D * 64;
-#pragma unroll
-            for (int j = 0; j < D; ++j) r[j] = wbase[j * 64];
+        for (int j = 0; j < R; ++j) {
+            q[j] = load_q(0, j);
+            if (WEIGHTED && j < RW) r[j] = load_r(0, j);
+            __builtin_amdgcn_sched_barrier(0);  // in the loop's order, or its head waits for all of them
         }
+        if (PAIRS) read_lo(q[0], y[0]);
+        read_hi(q[0], y[0]);
+        if (!PAIRS) read_lo(q[0], y[0]);
+        q[0] = load_q(R, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        float cur[C];
 #pragma unroll
-        for (int p = 0; p < KS; ++p) {
+        for (int c = 0; c < C; ++c) cur[c] = 0.f;
+        int p = 0, rem = __builtin_amdgcn_readlane(gtab, 0);
+        auto chunk = [&](int g) {
 #pragma unroll
-            for (int c = 0; c < C; ++c) acc[p][c] = 0.f;
-            const int gp = __builtin_amdgcn_readlane(gtab, p);
-            for (int i = 0; i < gp; ++i) {
-                const uint64_t cur = q[0];
-#pragma unroll
-                for (int j = 0; j + 1 < D; ++j) q[j] = q[j + 1];
-                q[D - 1] = *sp;
-                sp += 64;
-                f4v cw = r[0];
-                if (WEIGHTED) {
-#pragma unroll
-                    for (int j = 0; j + 1 < D; ++j) r[j] = r[j + 1];
-                    r[D - 1] = *wp;
-                    wp += 64;
-                }
-                const uint32_t lo = (uint32_t)cur, hi = (uint32_t)(cur >> 32);
-                mid_arc<C, WEIGHTED>(L, lo & 0xffffu, cw.x, acc[p]);
-                mid_arc<C, WEIGHTED>(L, lo >> 16, cw.y, acc[p]);
-                mid_arc<C, WEIGHTED>(L, hi & 0xffffu, cw.z, acc[p]);
-                mid_arc<C, WEIGHTED>(L, hi >> 16, cw.w, acc[p]);
-            }
-            if (p == 0 && pdst >= 0) {  // a part of a split row: its sum goes to its partial slot
-                float* dst = reinterpret_cast<float*>(reinterpret_cast<char*>(L) + pdst);
-#pragma unroll
-                for (int c = 0; c < C; ++c) dst[c] = acc[0][c];
-            }
-        }
-        // write-back: the slot table (LDS byte address of the row, scale
-        // (1-alpha)/d) is read in batches of 8 slots, each batch loaded one
-        // batch ahead; the first batch is in flight across the barrier
-        const bool fin = it == T - 1;
-        const uint32_t lane8 = (uint32_t)opaque(lane * 8);
-        constexpr int NB = (KS + 7) / 8;
-        uint64_t e[2][8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (j < KS)
-                e[0][j] = *reinterpret_cast<gcptr<uint64_t>>(reinterpret_cast<gcptr<char>>(opaque_s(vt_wave)) +
-                                                             lane8 + j * 512);
-        __syncthreads();
-#pragma unroll
-        for (int bt = 0; bt < NB; ++bt) {
-            if (bt + 1 < NB) {
-                const int64_t vsb = opaque_s(vt_wave + (int64_t)(bt + 1) * 8 * 512);
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if ((bt + 1) * 8 + j < KS)
-                        e[(bt + 1) & 1][j] =
-                            *reinterpret_cast<gcptr<uint64_t>>(reinterpret_cast<gcptr<char>>(vsb) + lane8 + j * 512);
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int p = bt * 8 + j;
-                if (p < KS && __builtin_amdgcn_readlane(gtab, p) > 0) {
-                    // the restart term alpha at the block's source rows: a
-                    // wave-uniform test of the slot, then the one lane
+            for (int j = 0; j < R; ++j) {
+                u2v& qe = q[(j + 1) % R];
+                MidY<C>(&yj)[4] = y[PAIRS ? 0 : j & 1];
+                auto add = [&](int k) {
 #pragma unroll
                     for (int c = 0; c < C; ++c)
-                        if (opaque_s32(sslot[c]) == p)
-                            if (lane == slane[c]) acc[p][c] += alpha;
-                    const int addr = (int)(uint32_t)e[bt & 1][j];
-                    if (addr >= 0) {
-                        const float sc = fin ? 1.0f : __int_as_float((int)(uint32_t)(e[bt & 1][j] >> 32));
-                        float* dst = reinterpret_cast<float*>(reinterpret_cast<char*>(L) + addr);
+                        cur[c] = WEIGHTED ? fmaf(__uint_as_float(r[j % RW][k]), yj[k].v[c], cur[c]) : cur[c] + yj[k].v[c];
+                };
+                if (!PAIRS) {
+                    MidY<C>(&yn)[4] = y[PAIRS ? 0 : (j + 1) & 1];
+                    read_hi(qe, yn);
+                    read_lo(qe, yn);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                add(0);
+                add(1);
+                if (PAIRS) {
+                    read_lo(qe, yj);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                add(2);
+                add(3);
+                if (PAIRS) {
+                    read_hi(qe, yj);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                qe = load_q(g + 1 + R, j);
+                if (WEIGHTED) r[j % RW] = load_r(g + RW, j);
+                __builtin_amdgcn_sched_barrier(0);
+                if (--rem == 0) {
 #pragma unroll
-                        for (int c = 0; c < C; ++c) dst[c] = acc[p][c] * sc;
+                    for (int b = 0; b < KS / 12; ++b)
+                        if (p / 12 == b) {
+                            asm volatile("");  // a branch, not selects over all of sums
+#pragma unroll
+                            for (int c = 0; c < C; ++c) sums[b][c][p - 12 * b] = cur[c];
+                        }
+#pragma unroll
+                    for (int c = 0; c < C; ++c) cur[c] = 0.f;
+                    ++p;
+                    rem = __builtin_amdgcn_readlane(gtab, p);  // 0 behind the last slot
+                }
+            }
+        };
+        // A SIMD issues its oldest wave first: left alone, the block's first waves
+        // finish in two thirds of the last ones' time, which then run with no
+        // other wave to fill their waits.  So a wave gives way as it gets on.
+        const int chunks = (groups + R - 1) / R;
+        int g = 0;
+        __builtin_amdgcn_s_setprio(3);
+        for (; g < chunks / 2 * R; g += R) chunk(g);
+        __builtin_amdgcn_s_setprio(2);
+        for (; g < chunks * 3 / 4 * R; g += R) chunk(g);
+        __builtin_amdgcn_s_setprio(1);
+        for (; g < chunks * 7 / 8 * R; g += R) chunk(g);
+        __builtin_amdgcn_s_setprio(0);
+        for (; g < groups; g += R) chunk(g);
+        if (pdst >= 0) {  // a part of a split row: its sum goes to its partial slot
+            float* dst = reinterpret_cast<float*>(reinterpret_cast<char*>(L) + pdst);
+#pragma unroll
+            for (int c = 0; c < C; ++c) dst[c] = sums[0][c][0];
+        }
+        // the restart term alpha at the block's source rows
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int b = 0; b < KS / 12; ++b)
+                if (sslot[c] >= 12 * b && sslot[c] < 12 * (b + 1)) {
+                    asm volatile("");
+                    sums[b][c][sslot[c] - 12 * b] += lane == slane[c] ? alpha : 0.f;
+                }
+        // write-back: a slot's rows follow each other in the tile, so that its
+        // writes are free of bank conflicts
+        const bool fin = it == T - 1;
+        constexpr int NB = (KS + 7) / 8;
+        const uint32_t lane8 = (uint32_t)opaque(lane * 8 + 4);
+        float e[2][8];
+        auto load_sc = [&](int bt, int j) {
+            const int64_t vsb = opaque_s(vt_wave + (int64_t)bt * 8 * 512);
+            e[bt & 1][j] = *reinterpret_cast<gcptr<float>>(reinterpret_cast<gcptr<char>>(vsb) + lane8 + j * 512);
+        };
+        if (!SCREG) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) load_sc(0, j);  // in flight across the barrier
+        }
+        __syncthreads();
+        // taken anew in each push, not kept in scalar registers per slot
+        const int first_row = opaque(stab);
+        const int used = opaque_s32(slots);
+        auto write_back = [&](auto last) {
+#pragma unroll
+            for (int bt = 0; bt < NB; ++bt) {
+                if (!SCREG && bt + 1 < NB) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if ((bt + 1) * 8 + j < KS) load_sc(bt + 1, j);
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int p = bt * 8 + j;
+                    if (p >= KS) break;
+                    if (p >= used) return;
+                    const int row0 = __builtin_amdgcn_readlane(first_row, p);
+                    float x[C];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        x[c] = sums[p / 12][c][p % 12];
+                        if (!decltype(last)::value) x[c] *= SCREG ? sc[SCREG ? p : 0] : e[bt & 1][j];
+                    }
+                    float* dst = L + (row0 + lane) * C;
+                    if ((unsigned)(row0 - hubs) <= (unsigned)(n - kWave - hubs)) {
+#pragma unroll
+                        for (int c = 0; c < C; ++c) dst[c] = x[c];
+                    } else if (row0 + lane >= hubs && row0 + lane < n) {
+                        // parts of split rows and lanes past the last row have no row
+#pragma unroll
+                        for (int c = 0; c < C; ++c) dst[c] = x[c];
                     }
                 }
             }
-        }
+        };
+        if (fin) write_back(std::true_type{}); else write_back(std::false_type{});
         if (cmb.x >= 0) {  // split row: its parts' partial sums in part order, in FP64
             double x[C];
 #pragma unroll
@@ -713,8 +840,7 @@ __global__ __launch_bounds__(kMidThreads) void ppr_mid_kernel(MidArgs a) {
         const int64_t row = (int64_t)(s0 + c) * a.n_tgt;
         const float ds = a.dppr_out ? a.deg[sn[c]] : 0.f;
         for (int j = tid; j < a.n_tgt; j += kMidThreads) {
-            const int t = a.tgt ? a.tgt[j] : j;
-            const float x = L[t * C + c];
+            const float x = L[a.rowpos[a.tgt ? a.tgt[j] : j] * C + c];
             if (a.ppr_out) a.ppr_out[row + j] = x;
             if (a.dppr_out) a.dppr_out[row + j] = x * ds;
         }
@@ -728,7 +854,7 @@ struct MidWs {
     int32_t* plan;        // kPlanInts
     int32_t* slice_goff;  // mid_slices(n)
     int32_t* slice_slot;  // mid_slices(n)
-    int2* vtab;           // kMidWaves * kMidSlotCap * 64: (LDS byte address of the row, scale)
+    int2* vtab;           // kMidWaves * kMidSlotCap * 64: (slice, scale)
     uint16_t* sell;       // mid_stream_groups * kMidGroup
     float* sellw;         // same, weighted graphs only
     int32_t* tmp_u;       // nnz: arcs bucketed by bank class
@@ -736,7 +862,7 @@ struct MidWs {
     RowEnt* vrows;        // n + kMidMaxParts: rows after splitting long rows
     int4* comb;           // kMidMaxParts: one entry per split row
     int32_t* part_dst;    // kMidWaves * 64: slot-0 partial targets
-    int32_t* rowpos;      // n: (wave * kMidSlotCap + slot) * 64 + lane of each row, -1 for split rows
+    int32_t* rowpos;      // n: each node's row of the tile (its place in degree order)
 };
 
 template <int C, bool W>
@@ -768,6 +894,7 @@ inline void mid_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, con
     a.plan = w.plan;
     a.part_dst = w.part_dst;
     a.rowpos = w.rowpos;
+    a.slice_slot = w.slice_slot;
     a.comb = w.comb;
     a.sell = w.sell;
     a.sellw = weighted ? w.sellw : nullptr;

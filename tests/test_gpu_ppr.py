@@ -287,3 +287,34 @@ def test_chung_lu_20000_all_pairs_sampled(ops):
     want500 = O.jacobi_rows(X499, Drows, sample)
     got500 = x500[sidx].double().cpu().numpy()
     assert np.abs(got500 - want500).max() <= STEP_REL * np.abs(X499).max()
+
+
+# the mid-size kernel with more sources than the few-source route takes: 4, 2
+# and 1 columns per block and the sizes where they change, weighted and not,
+# split rows (the power-law graphs) and none, short and odd series, an isolated
+# node and the longest row among the sources
+@pytest.mark.parametrize("n,T,kind", [(2305, 1, "w"), (2311, 2, "cl"), (5000, 25, "clw"), (10207, 14, "w"), (10208, 9, "cl"),
+                                      (12000, 60, "clw"), (20415, 7, ""), (20416, 12, "cl"), (25000, 30, "clw"),
+                                      (40831, 5, "")])
+def test_mid_many_sources(ops, n, T, kind):
+    rng = np.random.default_rng(n + T)
+    g0 = synth.chung_lu(n, 2.1, 24, 700 + n) if "cl" in kind else synth.erdos_renyi(n, 11, 700 + n)
+    keep = (g0.eu != 9) & (g0.ev != 9)  # an isolated node
+    w = (0.5 + 1.5 * rng.random(g0.m_und)).astype(np.float32)[keep] if "w" in kind else None
+    g = synth.build_graph(n, g0.eu[keep], g0.ev[keep], w)
+    src = rng.permutation(n)[:301]
+    src[0] = int(np.argmax(np.diff(g.row_ptr)))
+    src[1] = 9
+    src = np.array(list(dict.fromkeys(src.tolist())))
+    tgt = rng.permutation(n)[:1000] if T % 2 else None
+    print(f"[mid] n={n} nnz={g.nnz} sources={len(src)} T={T} {kind}", flush=True)
+    ppr, dppr, Tg, resid = ops.ppr_matrix(_csr(ops, g), src, tgt=tgt, tol=0.0, max_iter=T, check_residual=True)
+    assert Tg == T
+    some = np.array([0, 1, 2, 3, 150, 151, len(src) - 2, len(src) - 1])
+    est, dppr_o, _, res_o, d = oracle_ppr(g, src[some], T=T)
+    if tgt is not None:
+        est, dppr_o = est[:, tgt], dppr_o[:, tgt]
+    pick = torch.as_tensor(some, device="cuda")
+    assert_ppr_close(ppr[pick], dppr[pick], est, dppr_o, d[src[some]])
+    assert np.abs(resid[some] - res_o).max() <= 2e-6
+    assert np.isfinite(resid).all() and bool(torch.isfinite(dppr).all())
