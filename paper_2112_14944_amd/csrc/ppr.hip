@@ -194,7 +194,7 @@ __device__ __forceinline__ void res_deal_set(const ResDealSet& d, const int rr[4
             }
         }
     }
-    // entries past L up to the end of the last chunk (never read)
+    // entries past L up to the end of the last chunk (read where wider groups hold the dealt one)
 #pragma unroll
     for (int i = 0; i < M; ++i) {
         if (fixed[i]) continue;
@@ -203,6 +203,18 @@ __device__ __forceinline__ void res_deal_set(const ResDealSet& d, const int rr[4
 }
 
 constexpr int kResSortThreads = 512;
+
+// A graph by itself takes 16-column tiles at any size, so that its sources make
+// as many blocks as they can (pushes of n = 500, all sources: 8 blocks 275 us,
+// 32 blocks 111 us; n = 1000, weighted: 386 and 238 us): its rows then
+// stand in groups of 16, with each row's arcs in the order that its own size's
+// groups of 4 or 8 would give them, so that its sums are the batch's to the
+// bit.  Only repeated arcs can make the wider groups too long for the arc
+// copy; such a graph keeps its own size's tile.  The tile width chosen stands
+// in the last entry of the slot table.
+__device__ __forceinline__ bool res_narrow(const int64_t* node_off, int cols) {
+    return node_off == nullptr && cols > 16;
+}
 
 __global__ __launch_bounds__(kResSortThreads) void res_sort_kernel(const int32_t* __restrict__ row_ptr,
                                                                   const float* __restrict__ invd,
@@ -218,7 +230,6 @@ __global__ __launch_bounds__(kResSortThreads) void res_sort_kernel(const int32_t
     const int n = node_off ? (int)(node_off[g + 1] - base) : n_single;
     const int cols = n > 0 ? res_cols_for(n) : 0;
     if (cols == 0) return;  // larger graphs never use the resident tile
-    const int GW = 256 / cols;  // group size, Res<cols>::RPW
     TileTask tb;
     res_graph_bases(base, row_ptr[base], row_ptr[base + n], g, n, tb);
 
@@ -249,35 +260,49 @@ __global__ __launch_bounds__(kResSortThreads) void res_sort_kernel(const int32_t
             __syncthreads();
         }
     }
-    const int ng = (n + GW - 1) / GW;
-    if (threadIdx.x < 256) {
-        const int gi = threadIdx.x;
-        int64_t words = 0;
-        if (gi < ng) {
-            int dmax = 1;
-            for (int r = 0; r < GW; ++r) {
-                const int p = gi * GW + r;
-                if (p < n) {
-                    const int64_t gv = base + (int)(key[p] & 4095u);
-                    dmax = max(dmax, row_ptr[gv + 1] - row_ptr[gv]);
+    // the groups of GW rows: their lengths and places; returns the arc copy's size
+    auto place_groups = [&](int GW) -> int64_t {
+        const int ng = (n + GW - 1) / GW;
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            const int gi = threadIdx.x;
+            int64_t words = 0;
+            if (gi < ng) {
+                int dmax = 1;
+                for (int r = 0; r < GW; ++r) {
+                    const int p = gi * GW + r;
+                    if (p < n) {
+                        const int64_t gv = base + (int)(key[p] & 4095u);
+                        dmax = max(dmax, row_ptr[gv + 1] - row_ptr[gv]);
+                    }
                 }
+                const int h = (int)(((int64_t)dmax + 7) / 8);
+                ghalves[gi] = h;
+                words = (int64_t)((h + 1) / 2) * 16 * GW;
             }
-            const int h = (int)(((int64_t)dmax + 7) / 8);
-            ghalves[gi] = h;
-            words = (int64_t)((h + 1) / 2) * 16 * GW;
+            goff[gi] = words;
         }
-        goff[gi] = words;
-    }
-    __syncthreads();
-    // exclusive prefix sum of the groups' sizes
-    for (int o = 1; o < 256; o <<= 1) {
-        int64_t x = 0;
-        if (threadIdx.x < 256 && (int)threadIdx.x >= o) x = goff[threadIdx.x - o];
         __syncthreads();
-        if (threadIdx.x < 256) goff[threadIdx.x] += x;
-        __syncthreads();
+        // exclusive prefix sum of the groups' sizes
+        for (int o = 1; o < 256; o <<= 1) {
+            int64_t x = 0;
+            if (threadIdx.x < 256 && (int)threadIdx.x >= o) x = goff[threadIdx.x - o];
+            __syncthreads();
+            if (threadIdx.x < 256) goff[threadIdx.x] += x;
+            __syncthreads();
+        }
+        return goff[ng - 1];
+    };
+    int GW = Res<16>::RPW;
+    int64_t words = 0;
+    if (cols == 16 || res_narrow(node_off, cols)) words = place_groups(GW);
+    if (cols != 16 && (!res_narrow(node_off, cols) || words > (int64_t)tb.cwords)) {
+        GW = 256 / cols;  // group size, Res<cols>::RPW
+        words = place_groups(GW);
     }
-    const bool over = goff[ng - 1] > (int64_t)tb.cwords;
+    if (res_narrow(node_off, cols) && threadIdx.x == 0) slots[tb.tbase + n + kResTabPad - 1].off = 256 / GW;
+    const int ng = (n + GW - 1) / GW;
+    const bool over = words > (int64_t)tb.cwords;
     // slot table
     for (int p = threadIdx.x; p < ng * GW; p += kResSortThreads) {
         const int gi = p / GW;
@@ -312,14 +337,16 @@ __global__ __launch_bounds__(kResDealThreads) void res_deal_kernel(const int32_t
     const int n = node_off ? (int)(node_off[g + 1] - base) : n_single;
     const int cols = n > 0 ? res_cols_for(n) : 0;
     if (cols == 0) return;
-    const int GW = 256 / cols;
-    const int ng = (n + GW - 1) / GW;
-    if (g0 >= ng) return;
-    const int M = cols == 16 ? 4 : (cols == 32 ? 2 : 1);  // bank classes = rows per LDS pass
-    const int stride = cols * 4;                          // LDS bytes per row
     TileTask tb;
     res_graph_bases(base, row_ptr[base], row_ptr[base + n], g, n, tb);
     const ResSlot* tab = slots + tb.tbase;
+    const int width = res_narrow(node_off, cols) ? tab[n + kResTabPad - 1].off : cols;  // of the tile
+    const int GW = 256 / width;
+    const int ng = (n + GW - 1) / GW;
+    if (g0 >= ng) return;
+    const int M = cols == 16 ? 4 : (cols == 32 ? 2 : 1);  // bank classes = rows per LDS pass
+    const int DW = 256 / cols;                            // rows dealt as one group, in sets of M
+    const int stride = width * 4;                         // LDS bytes per row
     const float s0 = tab[0].invd;
     const bool over = s0 != s0;
     const int gn = min(kResDealGroups, ng - g0);
@@ -353,13 +380,26 @@ __global__ __launch_bounds__(kResDealThreads) void res_deal_kernel(const int32_t
         }
     }
     __syncthreads();
-    // one lane per set of M rows of a group whose reads share LDS cycles (4
-    // sets per group)
-    if (lane < gn * 4) {
-        const int gi = g0 + (lane >> 2);
+    // one lane per set of M rows of a group of DW whose reads share LDS cycles
+    // (4 sets per group)
+    const int parts = GW / DW;
+    if (lane < gn * parts * 4) {
+        const int gl = lane / (4 * parts);
+        const int gi = g0 + gl;
+        const int sub = (lane >> 2) % parts * DW;  // the dealt group's first row in its group
         const ResSlot e = tab[gi * GW];
+        const int first = gi * GW + sub;
+        int len = e.halves;  // of the dealt group
+        if (parts > 1) {
+            int dmax = 1;
+            for (int p = first; p < min(first + DW, n); ++p) {
+                const int fv = tab[p].v;
+                dmax = max(dmax, row_ptr[base + fv + 1] - row_ptr[base + fv]);
+            }
+            len = (dmax + 7) / 8;
+        }
         ResDealSet d;
-        d.L = e.halves * 8;
+        d.L = len * 8;
         d.words = (e.halves + 1) / 2 * 16;
         d.ca = arcs + tb.cbase + e.off;
         d.wa = warcs ? warcs + tb.cbase + e.off : nullptr;
@@ -370,12 +410,13 @@ __global__ __launch_bounds__(kResDealThreads) void res_deal_kernel(const int32_t
         d.over = over;
         d.row_ptr = row_ptr;
         d.cstart = cstart;
-        d.row0 = (lane >> 2) * GW;
+        d.row0 = gl * GW;
         int rr[4];
         res_conflict_set(M, lane & 3, rr);
         int v[4];
-    #pragma unroll
+#pragma unroll
         for (int i = 0; i < 4; ++i) {
+            rr[i] += sub;
             const int p = gi * GW + rr[i];
             v[i] = (i < M && p < n) ? tab[p].v : -1;
         }
@@ -423,8 +464,9 @@ void launch_res_layout(const int32_t* row_ptr, const int32_t* col_idx, const flo
 template <int COLS, bool WEIGHTED>
 __global__ __launch_bounds__(kResThreads) void ppr_resident_kernel(ResArgs a, int32_t n, int64_t nnz,
                                                                  int32_t n_src, int32_t n_tgt, int32_t T,
-                                                                 int32_t m, int32_t r) {
+                                                                 int32_t m, int32_t r, bool chosen) {
     __shared__ ResLds L;
+    if (chosen && a.slots[n + kResTabPad - 1].off != COLS) return;  // the other width's launch does it
     TileTask t;
     t.n = n;
     t.s0 = blockIdx.x * COLS;
@@ -448,23 +490,23 @@ void launch_degree(const int32_t* row_ptr, const float* weight, int64_t n, float
 
 template <int COLS>
 static void launch_resident(bool weighted, const ResArgs& a, int n, int64_t nnz, int n_src, int n_tgt, int T, int m,
-                            int r, hipStream_t s) {
+                            int r, bool chosen, hipStream_t s) {
     dim3 grid((n_src + COLS - 1) / COLS);
     if (weighted)
         hipLaunchKernelGGL((ppr_resident_kernel<COLS, true>), grid, dim3(kResThreads), 0, s, a, n, nnz, n_src, n_tgt,
-                           T, m, r);
+                           T, m, r, chosen);
     else
         hipLaunchKernelGGL((ppr_resident_kernel<COLS, false>), grid, dim3(kResThreads), 0, s, a, n, nnz, n_src,
-                           n_tgt, T, m, r);
+                           n_tgt, T, m, r, chosen);
 }
 
 static void launch_resident_any(bool weighted, const ResArgs& a, int n, int64_t nnz, int n_src, int n_tgt, int T,
                                 int m, int r, hipStream_t s) {
-    switch (res_cols_for(n)) {
-        case 64: launch_resident<64>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, s); break;
-        case 32: launch_resident<32>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, s); break;
-        default: launch_resident<16>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, s); break;
-    }
+    // up to 1152 nodes the layout's width decides which launch does the work (res_narrow)
+    const int cols = res_cols_for(n);
+    launch_resident<16>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, cols != 16, s);
+    if (cols == 32) launch_resident<32>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, true, s);
+    if (cols == 64) launch_resident<64>(weighted, a, n, nnz, n_src, n_tgt, T, m, r, true, s);
 }
 
 // One product of the all-pairs series (ppr_dense.hpp), one 64-wide tile per

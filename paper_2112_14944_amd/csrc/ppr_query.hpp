@@ -435,8 +435,8 @@ inline size_t query_gram_floats(int n, int k) { return (size_t)query_pieces(n, k
 // Whether a query on a graph that fits LDS is faster here, by the time of
 // either route in microseconds.  Measured: a push here 5.5 us and 3.2e-7 us per
 // arc and column held (20000 nodes, 4e5 arcs, 48 sources: 14 us; 39000, 7.8e5,
-// 200: 63 us); the resident tile 2.5 us per push and 1.1e-5 us per arc and
-// column of a block (n = 2048, 1.3e5 arcs: 23 us); the mid-size kernel 4.4e-5
+// 200: 63 us); the resident tile, 16 columns per block in a graph by itself, 2.5
+// us per push and 1.1e-5 us per arc and column (n = 2048, 1.3e5 arcs: 23 us); the mid-size kernel 4.4e-5
 // us per arc (6.9e-5 with 1 or 4 columns per block), and its preparation,
 // which one-block kernels dominate, 0.07 us per node.  48 sources of 20000
 // nodes, T = 86: 2.97 ms there, 1.25 ms here, 0.71 ms with halved pushes.
@@ -446,8 +446,7 @@ inline bool query_faster(int n, int64_t nnz, int n_src, int T, bool halved) {
     const double here = 60.0 + steps * (5.5 + 3.2e-7 * (double)nnz * (double)query_ld(n_src));
     double there;
     if (res_cols_for(n) != 0) {
-        const int cols = res_cols_for(n);
-        there = 40.0 + 0.1 * n + T * (2.5 + 1.1e-5 * (double)nnz * cols);
+        there = 40.0 + 0.1 * n + T * (2.5 + 1.1e-5 * (double)nnz * 16);
     } else {
         const int C = mid_cols_for(n);
         const int rounds = ((n_src + C - 1) / C + 255) / 256;

@@ -318,3 +318,24 @@ def test_mid_many_sources(ops, n, T, kind):
     assert_ppr_close(ppr[pick], dppr[pick], est, dppr_o, d[src[some]])
     assert np.abs(resid[some] - res_o).max() <= 2e-6
     assert np.isfinite(resid).all() and bool(torch.isfinite(dppr).all())
+
+
+# a graph by itself takes 16-column tiles: 300 repeated arcs fit the wider
+# groups, 2000 only those of its own size's tile (64 columns), 2600 neither
+@pytest.mark.parametrize("reps", [300, 2000, 2600])
+def test_single_tile_width(ops, reps):
+    csr = _repeated_arc_csr(ops, 300, reps)
+    T = 12  # too short for the series
+    ppr, _, _, resid = ops.ppr_matrix(csr, np.arange(300), tol=0.0, max_iter=T, check_residual=reps != 2600)
+    if reps == 2600:
+        assert torch.isnan(ppr).all().item()
+        return
+    est, _, _, _, _ = oracle_ppr(synth.build_graph(2, [0], [1]), [0, 1], T=T)
+    p = ppr.double().cpu().numpy()
+    # as above: each row sums its equal terms one after another in FP32
+    rel = reps * 2.0 ** -24 / ALPHA
+    assert np.abs(p[:2, :2] - est[:, :2]).max() <= rel * est.max()
+    want = np.diag(np.full(300, 1 - (1 - ALPHA) ** T))
+    want[:2, :2] = p[:2, :2]
+    assert np.abs(p - want).max() <= 1e-6
+    assert np.abs(resid - (1 - ALPHA) ** T).max() <= 2e-6 + rel
