@@ -73,10 +73,11 @@ def ppr_matrix(g: Csr, src, tgt=None, alpha=0.15, tol=1e-6, max_iter=100000, wan
     Returns (ppr, dppr, pushes, resid) with resid an FP64 numpy array when
     check_residual is set (that synchronizes)."""
     dev = g.row_ptr.device
+    among = tgt is src and tgt is not None  # one array for both: the library may halve the pushes
     src = torch.as_tensor(src, dtype=torch.int32, device=dev).contiguous()
     n_src = int(src.numel())
     if tgt is not None:
-        tgt = torch.as_tensor(tgt, dtype=torch.int32, device=dev).contiguous()
+        tgt = src if among else torch.as_tensor(tgt, dtype=torch.int32, device=dev).contiguous()
         n_tgt = int(tgt.numel())
     else:
         n_tgt = g.n
@@ -101,10 +102,11 @@ def ppr_matrix_noalloc(g: Csr, src, tgt=None, alpha=0.15, tol=1e-6, max_iter=100
     ``dppr`` are caller-owned [n_src, n_tgt] FP32 outputs (either may be
     None).  Returns (pushes, resid)."""
     dev = g.row_ptr.device
+    among = tgt is src and tgt is not None  # one array for both: the library may halve the pushes
     src = torch.as_tensor(src, dtype=torch.int32, device=dev).contiguous()
     n_src = int(src.numel())
     if tgt is not None:
-        tgt = torch.as_tensor(tgt, dtype=torch.int32, device=dev).contiguous()
+        tgt = src if among else torch.as_tensor(tgt, dtype=torch.int32, device=dev).contiguous()
         n_tgt = int(tgt.numel())
     else:
         n_tgt = g.n
