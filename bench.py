@@ -50,6 +50,7 @@ def source_hash(files):
 
 KERNEL_SOURCES = {
     "batch_ppr_kernel": ["paper_2112_14944_amd/csrc/ppr_core.hpp", "paper_2112_14944_amd/csrc/ppr.hip",
+                         "paper_2112_14944_amd/csrc/ppr_dense.hpp", "paper_2112_14944_amd/csrc/dense.hpp",
                          "paper_2112_14944_amd/csrc/batch.hip"],
     "batch_pair_kernel": ["paper_2112_14944_amd/csrc/layout_core.hpp", "paper_2112_14944_amd/csrc/batch.hip"],
 }
@@ -141,15 +142,31 @@ def cpu_baseline(graphs, sample_count=32, max_procs=16):
                 cpu_model=host_cpu_model())
 
 
+def series_plan(n, nnz, T):
+    """Pushes and dense products of the library's all-pairs series for one
+    subgraph (the rule of csrc/ppr_dense.hpp)."""
+    best, cost = (T - 1, 0), 90 * T * nnz
+    if 192 <= n <= 2304 and 24 <= T <= 4096:
+        for k in (1, 2, 3):
+            m = (T + k) // (k + 1)
+            c = 100 * (m + 4) * nnz + 22 * k * n * (n + 64)
+            if c < cost:
+                best, cost = (m, k), c
+    return best
+
+
 def stage_rooflines(gb, T, ms):
     """Roofline records of the batched stages from the library's stage times.
 
-    PPR (three persistent launches, one per tile class, timed together): the
-    tile keeps X in LDS and is bound by VALU issue, so its roofline is FP32
-    adds (one per arc, source column and push) against the plain FP32 add
-    peak, 256 CUs x 64 lanes x 2.4 GHz (no packed FP32).  The bytes a
-    streaming SpMM would move are kept beside it (hbm_model): per push and
-    subgraph 8 n^2 (read X_t, write X_t+1, S = n sources) + 4 nnz + 8 n + 4
+    PPR (three persistent push launches, one per tile class, and up to three
+    launches of dense products, timed together): the tile keeps X in LDS and is
+    bound by VALU issue, the products by the matrix cores, so the stage's
+    roofline is the time of its FP32 adds (one per arc, source column and push
+    made) at the plain FP32 add peak, 256 CUs x 64 lanes x 2.4 GHz (no packed
+    FP32), plus that of the products (n^3 FLOP each: the upper triangle) at the
+    FP32 matrix peak; `peak` is the rate at which both would take just that.
+    The bytes a streaming SpMM of all T - 1 pushes would move are kept beside it
+    (hbm_model): per push and subgraph 8 n^2 (read X_t, write X_t+1, S = n sources) + 4 nnz + 8 n + 4
     (column indices, row pointers, 1/d); T - 1 pushes follow the initial
     iterate.
     Layout (a pair-tile launch plus a combine launch per sweep): Delta is
@@ -165,16 +182,22 @@ def stage_rooflines(gb, T, ms):
     arcs = np.add.reduceat(nnz, gb.node_off[:-1].astype(np.int64)).astype(np.float64)
     pushes = max(T - 1, 0)
     ppr_bytes = pushes * float((8.0 * sizes * sizes + 4.0 * arcs + 8.0 * sizes + 4.0).sum())
-    ppr_adds = pushes * float((arcs * sizes).sum())
+    plans = [series_plan(int(n), int(a), T) for n, a in zip(sizes, arcs)]
+    ppr_adds = float(sum(m * a * n for (m, _), a, n in zip(plans, arcs, sizes)))
+    ppr_flops = float(sum(k * n ** 3 for (_, k), n in zip(plans, sizes)))
     layout_bytes = float((2.0 * sizes * (sizes + 1.0) + 20.0 * sizes).sum())
     ppr_ms, layout_ms = ms[1], ms[3]
     lay_launch_ms = layout_ms / (STRESS_ITERS + 1)
     adds_per_s = ppr_adds / (ppr_ms * 1e-3)
     hbm_ach = ppr_bytes / (ppr_ms * 1e-3) / 1e9
-    st_ppr = dict(kernel="batch_ppr_kernel", ms=ppr_ms, launches=3, bound="alu", unit="TFLOP/s",
-                  achieved=adds_per_s / 1e12, peak=PEAK_FP32_ADDS / 1e12, frac=adds_per_s / PEAK_FP32_ADDS,
-                  work=f"{ppr_adds:.4g} FP32 adds over {pushes} pushes (one per arc, source column and push)",
-                  adds_per_s=adds_per_s, adds=ppr_adds,
+    ideal_s = ppr_adds / PEAK_FP32_ADDS + ppr_flops / (PEAK_FP32_TFLOPS * 1e12)
+    ops_total = ppr_adds + ppr_flops
+    st_ppr = dict(kernel="batch_ppr_kernel", ms=ppr_ms, launches=6, bound="alu", unit="TFLOP/s",
+                  achieved=ops_total / (ppr_ms * 1e-3) / 1e12, peak=ops_total / ideal_s / 1e12,
+                  frac=ideal_s / (ppr_ms * 1e-3),
+                  work=f"{ppr_adds:.4g} FP32 adds of the pushes (one per arc, source column and push) and "
+                       f"{ppr_flops:.4g} FLOP of dense products",
+                  adds_per_s=adds_per_s, adds=ppr_adds, product_flops=ppr_flops,
                   hbm_model=dict(unit="GB/s", achieved=hbm_ach, peak=PEAK_HBM_GBS, frac=hbm_ach / PEAK_HBM_GBS,
                                  work=f"{ppr_bytes:.4g} B over {pushes} pushes (X read and written once per "
                                       f"push, plus CSR), the bytes a streaming SpMM would move"))
@@ -246,7 +269,7 @@ def spmm_all_pairs(ops, dev, n=20000, gamma=2.5, avg_degree=20, tol=1e-7, reps=2
                 work=f"{alg:.4g} B over {T - 1} pushes", nnz=nnz,
                 pdist=dict(kernel="pdist_kernel", ms=t_pd, bound="hbm", unit="GB/s",
                            achieved=pd_bytes / (t_pd * 1e-3) / 1e9, frac=pd_bytes / (t_pd * 1e-3) / 1e9 / PEAK_HBM_GBS),
-                layout=dict(kernel="layout_rows_kernel", sweeps=sweeps, ms=t_lay, ms_per_sweep=t_lay / sweeps,
+                layout=dict(kernel="layout_split_kernel", sweeps=sweeps, ms=t_lay, ms_per_sweep=t_lay / sweeps,
                             bound="hbm", unit="GB/s", achieved=lay_bytes / (t_lay * 1e-3) / 1e9,
                             frac=lay_bytes / (t_lay * 1e-3) / 1e9 / PEAK_HBM_GBS,
                             tflops=lay_flops / (t_lay * 1e-3) / 1e12, stress_before=s0, stress_after=s1),
@@ -258,8 +281,9 @@ def spmm_large(ops, dev, n=1_000_000, gamma=2.2, avg_degree=30, n_src=4096, tol=
     2.2, mean degree 30 (about 3e7 arcs), PPR from 4096 seeded sources to L1
     1e-6, accumulated at the 4096 sources as targets, one whole ppr_matrix call.
     The iterate (4096 columns of 10^6 nodes, 16.4 GB per buffer) lives in HBM
-    (stream_step_kernel, one launch per push).  Algorithmic bytes per push:
-    8 n S + 4 nnz + 8 (n + 1)."""
+    (query_step_kernel, one launch per push; the targets are the sources, so
+    T / 2 pushes after the first iterate and one product of two iterates).
+    Algorithmic bytes per push: 8 n S + 4 nnz + 8 (n + 1)."""
     import torch
     import synth
 
@@ -280,12 +304,13 @@ def spmm_large(ops, dev, n=1_000_000, gamma=2.2, avg_degree=30, n_src=4096, tol=
     delta = ops.pdist(dppr, n)  # PDist among the sources, n_clamp = |V|
     del dppr
     nnz = int(g.col_idx.shape[0])
-    alg = (T - 1) * (8.0 * n * n_src + 4.0 * nnz + 8.0 * (n + 1))
+    pushes = T // 2
+    alg = pushes * (8.0 * n * n_src + 4.0 * nnz + 8.0 * (n + 1))
     return dict(workload=f"chung_lu n={n} gamma={gamma} mean degree {avg_degree}, {n_src} sources, "
                          f"L1 {tol:g} (T={T}), DPPR among the sources, whole ppr_matrix call",
-                kernel="stream_step_kernel", ms=best, bound="hbm", unit="GB/s",
+                kernel="query_step_kernel", ms=best, bound="hbm", unit="GB/s",
                 achieved=alg / (best * 1e-3) / 1e9, peak=PEAK_HBM_GBS,
-                frac=alg / (best * 1e-3) / 1e9 / PEAK_HBM_GBS, work=f"{alg:.4g} B over {T - 1} pushes",
+                frac=alg / (best * 1e-3) / 1e9 / PEAK_HBM_GBS, work=f"{alg:.4g} B over {pushes} pushes",
                 nnz=nnz), (g, csr, delta, src)
 
 
@@ -664,8 +689,8 @@ def main():
         roof = dict(kernel=dom["kernel"], bound=dom["bound"], achieved=dom["achieved"], peak=dom["peak"],
                     unit=dom["unit"], frac=dom["frac"], traffic=traffic)
         log(f"stages ms: plan {ms[0]:.2f} ppr {ms[1]:.2f} pdist {ms[2]:.2f} layout {ms[3]:.2f}; "
-            f"ppr {stages['ppr']['adds_per_s'] / 1e12:.2f} T adds/s ({100 * stages['ppr']['frac']:.0f}% of the "
-            f"FP32 add peak; {stages['ppr']['hbm_model']['achieved']:.0f} GB/s by the SpMM byte model), "
+            f"ppr {stages['ppr']['achieved']:.2f} TFLOP/s ({100 * stages['ppr']['frac']:.0f}% of the rate of its "
+            f"adds and products at their peaks; {stages['ppr']['hbm_model']['achieved']:.0f} GB/s by the SpMM byte model), "
             f"layout {stages['layout']['achieved']:.0f} GB/s, {stages['layout']['tflops']:.1f} TFLOP/s FP32 "
             f"({100 * stages['layout']['flop_frac']:.0f}% of the vector peak)")
 
@@ -683,17 +708,18 @@ def main():
         max_n = int(sizes.max())
         ws_layout = torch.empty(lib.layout_workspace(max_n), dtype=torch.uint8, device=dev)
         csrs = []
+        wsz = 1  # one workspace for all calls (they run one after another)
         for g in graphs:
             csr = ops.Csr.from_graph(g, dev)
             cg = csr.c()
             src = torch.arange(g.n, dtype=torch.int32, device=dev)
-            wsz = lib.ppr_matrix_workspace(C.byref(cg), g.n, g.n)
-            ws = torch.empty(max(wsz, 1), dtype=torch.uint8, device=dev)
+            wsz = max(wsz, lib.ppr_matrix_workspace_fast(C.byref(cg), g.n, g.n))
             dppr = torch.empty((g.n, g.n), dtype=torch.float32, device=dev)
             delta = torch.empty_like(dppr)
             xa = torch.empty((g.n, 2), dtype=torch.float32, device=dev)
             xb = torch.empty_like(xa)
-            csrs.append((csr, cg, src, ws, dppr, delta, xa, xb))
+            csrs.append((csr, cg, src, dppr, delta, xa, xb))
+        ws = torch.empty(wsz, dtype=torch.uint8, device=dev)
         a0 = gb.node_off
         torch.cuda.synchronize()
         p0 = time.perf_counter()
@@ -701,7 +727,7 @@ def main():
         pe1 = torch.cuda.Event(enable_timing=True)
         pe0.record(stream)
         it = C.c_int32()
-        for gi, (csr, cg, src, ws, dppr, delta, xa, xb) in enumerate(csrs):
+        for gi, (csr, cg, src, dppr, delta, xa, xb) in enumerate(csrs):
             n = graphs[gi].n
             st = lib.ppr_matrix(C.byref(cg), C.c_void_p(src.data_ptr()), n, None, n, ALPHA, TOL, 100000, None,
                                 C.c_void_p(dppr.data_ptr()), None, C.byref(it), C.c_void_p(ws.data_ptr()),
@@ -723,9 +749,9 @@ def main():
         # sums each unordered pair once over tiles, the plain step sweeps rows)
         gi = int(np.argmax(sizes))
         lo, hi_ = int(a0[gi]), int(a0[gi + 1])
-        res = csrs[gi][6] if STRESS_ITERS % 2 == 0 else csrs[gi][7]
-        same_bits = bool(torch.equal(csrs[gi][4], ops.graph_block(gb, bufs["dppr"], gi)) and
-                         torch.equal(csrs[gi][5], ops.graph_block(gb, bufs["delta"], gi)))
+        res = csrs[gi][5] if STRESS_ITERS % 2 == 0 else csrs[gi][6]
+        same_bits = bool(torch.equal(csrs[gi][3], ops.graph_block(gb, bufs["dppr"], gi)) and
+                         torch.equal(csrs[gi][4], ops.graph_block(gb, bufs["delta"], gi)))
         xb = bufs["x_out"][lo:hi_]
         lay_diff = float((res - xb).abs().max().item() / max(1.0, res.abs().max().item()))
         assert same_bits and lay_diff <= 1e-2, (same_bits, lay_diff)
