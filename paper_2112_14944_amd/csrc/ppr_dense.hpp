@@ -14,9 +14,9 @@
 // mass (3% of it for m = 22), so their rounding hardly shows in the result.
 //
 // Measured (MI355X): 512 block-model subgraphs of 32 to 2048 nodes (T = 86),
-// PPR stage 43.7 ms by pushes alone, 25.3 ms as 14.6 ms of pushes and 10.7 ms
-// of products; one graph of 2048 nodes, all pairs, 2.01 ms against 0.53 ms of
-// pushes and three products.
+// PPR stage 43.7 ms by pushes alone, 23.0 ms as 13.6 ms of pushes and 9.4 ms
+// of products; one graph of 2048 nodes, all pairs, 2.01 ms against 0.49 ms of
+// pushes and three products of 0.13.
 //
 // A 32x32 block on or above the diagonal is stored as computed, one below it
 // is the mirror image of its partner, whatever the tile size: the batch and
