@@ -41,7 +41,7 @@ __global__ void degree_kernel(const int32_t* __restrict__ row_ptr, const float* 
 //     16-byte reads serves M rows at once (M = 4, 2, 1 for 16, 32, 64
 //     columns: 64 bytes of each of 4 rows, 128 of 2, 256 of 1;
 //     res_conflict_set names them), and row u starts in bank class u mod M.
-//     Each lane first groups the arcs of one row by class.  Then one lane
+//     Four lanes first group the arcs of one row by class.  Then one lane
 //     takes such a set of M rows and fills their positions m = 0, 1, ...
 //     together: each row takes, among the classes no other row has
 //     taken at m, the one it holds most arcs of; a row with no such arc pads
@@ -59,7 +59,9 @@ __global__ void degree_kernel(const int32_t* __restrict__ row_ptr, const float* 
 // Bound: latency.  One block per graph for all of it left a graph's rows to
 // 256 threads, each with its own chain of dependent loads (n = 2048, 1.3e5
 // arcs: 1190 us, more than its push series); with four groups per block
-// 182 us (28 the sort, 154 the deal).
+// 182 us (28 the sort, 154 the deal); with four lanes per row in the grouping
+// by class 116 to 131 the deal (of n = 2048, a quarter the grouping before, two
+// thirds the serial choice).
 // The rows of a group whose LDS reads are served in the same cycles.  A
 // 16-byte LDS read by a wave is served 16 lanes at a time, lanes grouped by
 // lane bit 5 and the parity of lane bits 2..4 (a probe of the patterns
@@ -352,31 +354,37 @@ __global__ __launch_bounds__(kResDealThreads) void res_deal_kernel(const int32_t
     const int gn = min(kResDealGroups, ng - g0);
     // each row's arcs as LDS offsets, grouped by bank class (CSR order within
     // a class), and where each class starts
-    for (int q = lane; q < gn * GW; q += kResDealThreads) {
+    // (four lanes per row, a quarter of its arcs each)
+    const int part = lane & 3;
+    for (int q = lane >> 2; q < gn * GW; q += kResDealThreads / 4) {
         const int v = tab[g0 * GW + q].v;
         if (v >= n || over) continue;
         const int rs = row_ptr[base + v], re = row_ptr[base + v + 1];
-        int c0 = 0, c1 = 0, c2 = 0, c3 = 0;
+        const int share = (re - rs + 3) / 4;
+        const int e0 = min(re, rs + part * share), e1 = min(re, e0 + share);
+        int cn[4] = {0, 0, 0, 0};
 #pragma unroll 8
-        for (int e = rs; e < re; ++e) {
+        for (int e = e0; e < e1; ++e) {
             const int c = (int)((col_idx[e] - base) & (M - 1));
-            c0 += c == 0;
-            c1 += c == 1;
-            c2 += c == 2;
-            c3 += c == 3;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) cn[k] += c == k;
         }
-        int pos[4] = {rs, rs + c0, rs + c0 + c1, rs + c0 + c1 + c2};
-        cstart[q][0] = 0;
-        cstart[q][1] = c0;
-        cstart[q][2] = c0 + c1;
-        cstart[q][3] = c0 + c1 + c2;
+        int pos[4], at = rs;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int a0 = quad_bcast<0>(cn[k]), a1 = quad_bcast<1>(cn[k]), a2 = quad_bcast<2>(cn[k]),
+                      a3 = quad_bcast<3>(cn[k]);
+            pos[k] = at + (part > 0 ? a0 : 0) + (part > 1 ? a1 : 0) + (part > 2 ? a2 : 0);
+            if (part == 0) cstart[q][k] = at - rs;
+            at += a0 + a1 + a2 + a3;
+        }
 #pragma unroll 8
-        for (int e = rs; e < re; ++e) {
+        for (int e = e0; e < e1; ++e) {
             const int u = (int)(col_idx[e] - base);
             const int c = u & (M - 1);
-            const int at = c == 0 ? pos[0]++ : (c == 1 ? pos[1]++ : (c == 2 ? pos[2]++ : pos[3]++));
-            sorted[at] = u * stride;
-            if (wsorted) wsorted[at] = weight[e];
+            const int to = c == 0 ? pos[0]++ : (c == 1 ? pos[1]++ : (c == 2 ? pos[2]++ : pos[3]++));
+            sorted[to] = u * stride;
+            if (wsorted) wsorted[to] = weight[e];
         }
     }
     __syncthreads();
