@@ -675,8 +675,11 @@ static ppr_status batch_enqueue(const ppr_batch* b, float alpha, int32_t T, int3
     launch_degree(b->row_ptr, nullptr, b->n_nodes, w.deg, w.invd, s);
     launch_res_layout(b->row_ptr, b->col_idx, nullptr, w.invd, b->node_off, 0, G, w.slots, w.col_r, nullptr,
                       w.sorted_r, nullptr, s);
-    // with room for its pool, subgraphs may take the all-pairs series
-    const int series_T = w.series != nullptr ? T : 0;
+    // with room for its pool, subgraphs may take the all-pairs series; it keeps
+    // iterates in the DPPR and the Delta pool at once, so a caller that gives one
+    // array for both (and keeps Delta alone) gets all pushes
+    const bool apart = dppr_pool + b->pool_size <= delta_pool || delta_pool + b->pool_size <= dppr_pool;
+    const int series_T = w.series != nullptr && apart ? T : 0;
     hipLaunchKernelGGL(batch_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, b->node_off, b->row_ptr, G, series_T,
                        w.plan);
     if (ev) PPRVIZ_HIP_TRY(hipEventRecord(ev[1], s));

@@ -169,3 +169,40 @@ def test_batch_sweep_task_queue():
         D = delta[m:m + n * n].reshape(n, n).astype(np.float64)
         want = O.jacobi_step(X, D)
         assert np.abs(got - want).max() <= STEP_REL * np.abs(want).max(), (gi, n)
+
+
+# Without room for the products' pool, and with one array for the DPPR and the
+# Delta pool, the batch takes all pushes; sizes around the smallest that takes
+# products (192), and of every tile width.
+def test_batch_all_pushes():
+    ops = get_ops()
+    sizes = [40, 191, 192, 193, 600, 1200, 2304]
+    graphs = [synth.sbm(synth.equal_blocks(n, 4), 0.2, 0.02, 6000 + n) for n in sizes]
+    gb = synth.concat_graphs(graphs)
+    b = ops.Batch(gb, "cuda")
+    x0 = torch.as_tensor(synth.uniform_layout(b.n_nodes, 13), device="cuda")
+    full = b.buffers(x0)
+    print(f"[all pushes] graphs={b.n_graphs} nodes={b.n_nodes} nnz={b.nnz}", flush=True)
+    ops.pprviz_batch(b, full, tol=1e-6, stress_iters=0)
+    small = b.buffers(x0)
+    small["ws"] = torch.empty(full["ws"].numel() - 4 * b.pool, dtype=torch.uint8, device="cuda")
+    ops.pprviz_batch(b, small, tol=1e-6, stress_iters=0)
+    one = b.buffers(x0)
+    one["dppr"] = one["delta"]
+    ops.pprviz_batch(b, one, tol=1e-6, stress_iters=0)
+    torch.cuda.synchronize()
+    # the same pushes, whatever the pools
+    assert torch.equal(one["delta"], small["delta"])
+    for gi, g in enumerate(graphs):
+        src = np.sort(np.random.default_rng(gi).choice(g.n, 24, replace=False))
+        _, want, T, _, d = oracle_ppr(g, src, tol=1e-6)
+        got = ops.graph_block(gb, small["dppr"], gi).double().cpu().numpy()[src]
+        # the package's bar: DPPR 1e-6 max(1, d(s))
+        assert (np.abs(got - want) / np.maximum(1.0, d[src])[:, None]).max() <= 1e-6, (gi, g.n)
+        # the two routes round each value about T times by u = 2^-24 at random
+        # (1e-6 of the norm bounds it with room), and are the same below 192 nodes
+        a, c = ops.graph_block(gb, full["dppr"], gi), ops.graph_block(gb, small["dppr"], gi)
+        assert ((a - c).norm() / c.norm()).item() <= 1e-6, (gi, g.n)
+        assert g.n >= 192 or torch.equal(a, c)
+        # PDist of the pushes' DPPR, clamped at n
+        assert torch.equal(ops.graph_block(gb, small["delta"], gi), ops.pdist(c.contiguous(), g.n))
