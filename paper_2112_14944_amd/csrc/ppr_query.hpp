@@ -196,9 +196,14 @@ static __global__ void query_init_kernel(const int32_t* __restrict__ src, const 
 
 // part[c] = (hi - lo)[:, S]^T D b[:, S] / (alpha (1-alpha)) over the c-th
 // piece of the rows, b = lo or hi; tiles (I, J), I <= J, of 64 x 64 sources.
+// The terms are positive, so a chain of FP32 sums rounds the more the longer it
+// is: the running sums are set aside in FP64 every kGramChunk rows, whatever the
+// length of a piece (few pieces are left when there are many tiles).
 // It reads the iterate's columns once per tile and is a small part of a query
 // (64 sources, 10^6 nodes: 0.4 ms of
 // 38 ms).
+constexpr int kGramChunk = 128;
+
 static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
     const float* __restrict__ lo, const float* __restrict__ hi, int use_hi, const float* __restrict__ deg,
     float scale, int32_t n, int W, int32_t ld, int32_t k, int32_t rows, float* __restrict__ part) {
@@ -219,8 +224,12 @@ static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
     const int64_t bi = oki ? qidx(0, ci, n, W) : 0, bj = okj ? qidx(0, cj, n, W) : 0;
     const float* __restrict__ b = use_hi ? hi : lo;
     DenseAcc c;
+    double sum[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) c[r] = 0.f;
+    for (int r = 0; r < 16; ++r) {
+        c[r] = 0.f;
+        sum[r] = 0.0;
+    }
     float ra[NP], rb[NP];
     auto fetch = [&](int v) {
 #pragma unroll
@@ -234,6 +243,7 @@ static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
         }
     };
     fetch(v0);
+    static_assert(kGramChunk % KB == 0, "whole steps");
     for (int v = v0; v < v1; v += KB) {
         __syncthreads();
 #pragma unroll
@@ -248,14 +258,21 @@ static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
         for (int kk = 0; kk < KB; kk += 2)
             c = __builtin_amdgcn_mfma_f32_32x32x2f32(L.a[0][kk + half][(wi ^ (32 * half)) + l32],
                                                      L.b[0][kk + half][(wj ^ (32 * half)) + l32], c, 0, 0, 0);
+        if ((v - v0) % kGramChunk == kGramChunk - KB || v + KB >= v1) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                sum[r] += (double)c[r];
+                c[r] = 0.f;
+            }
+        }
     }
     float* out = part + (int64_t)blockIdx.y * k * k;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int i = I * 64 + wi + dense_row(r, lane), j = J * 64 + wj + l32;
         if (i >= k || j >= k) continue;
-        out[(int64_t)i * k + j] = c[r];
-        if (I != J) out[(int64_t)j * k + i] = c[r];
+        out[(int64_t)i * k + j] = (float)sum[r];
+        if (I != J) out[(int64_t)j * k + i] = (float)sum[r];
     }
 }
 

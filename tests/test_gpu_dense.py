@@ -195,3 +195,67 @@ def test_few_sources(n, sources, T, targets):
     dw = d[src][:, None] * want
     assert (np.abs(dppr.double().cpu().numpy() - dw) / np.maximum(1.0, d[src])[:, None]).max() <= 1e-6
     assert np.abs(resid - res).max() <= 2e-6
+
+
+def _push64(g, src, T, alpha):
+    """X[v, s] after T pushes in FP64, and the degrees; alpha as FP32 holds it."""
+    rows = torch.repeat_interleave(torch.arange(g.n), torch.as_tensor(np.diff(g.row_ptr)).long()).cuda()
+    cols = torch.as_tensor(g.col_idx, device="cuda").long()
+    w = torch.ones(g.nnz, dtype=torch.float64, device="cuda") if g.arc_weight is None else \
+        torch.as_tensor(g.arc_weight, device="cuda").double()
+    d = torch.zeros(g.n, dtype=torch.float64, device="cuda").index_add_(0, rows, w)
+    alone = torch.nonzero(d == 0).flatten()
+    v = torch.cat([w / d[cols], torch.ones(alone.numel(), dtype=torch.float64, device="cuda")])
+    a = float(np.float32(alpha))
+    q = torch.sparse_coo_tensor(torch.stack([torch.cat([rows, alone]), torch.cat([cols, alone])]), (1 - a) * v,
+                                (g.n, g.n)).coalesce().to_sparse_csr()
+    e = torch.zeros((g.n, len(src)), dtype=torch.float64, device="cuda")
+    e[torch.as_tensor(src, device="cuda").long(), torch.arange(len(src), device="cuda")] = a
+    x = e.clone()
+    for _ in range(T - 1):
+        x = torch.sparse.mm(q, x)
+        x += e
+    return x, d
+
+
+def _query(ops, csr, src, tgt, T, alpha, fast):
+    """ppr_matrix with the fast or the general workspace: (ppr, dppr)."""
+    import ctypes as C
+    from paper_2112_14944_amd import _lib as L
+    lib, cg = L.lib(), csr.c()
+    k, m = src.numel(), csr.n if tgt is None else tgt.numel()
+    size = lib.ppr_matrix_workspace_fast if fast else lib.ppr_matrix_workspace
+    ws = torch.empty(size(C.byref(cg), k, m), dtype=torch.uint8, device="cuda")
+    ppr, dppr = torch.empty((k, m), device="cuda"), torch.empty((k, m), device="cuda")
+    p = lambda t: None if t is None else C.c_void_p(t.data_ptr())
+    st = lib.ppr_matrix(C.byref(cg), p(src), k, p(tgt), m, alpha, 0.0, T, p(ppr), p(dppr), None, None, p(ws),
+                        ws.numel(), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0
+    return ppr, dppr
+
+
+# Many sources of a large graph, few pushes: the product that halves them holds
+# half of the mass and sums over 200000 rows in few pieces.
+def test_many_sources_short_series():
+    ops = get_ops()
+    n, k, T = 200000, 500, 8
+    g = synth.chung_lu(n, 2.4, 24, 91)
+    rng = np.random.default_rng(92)
+    src = torch.as_tensor(np.sort(rng.choice(np.nonzero(np.diff(g.row_ptr))[0], k, replace=False)).astype(np.int32),
+                          device="cuda")
+    csr = ops.Csr.from_graph(g, "cuda")
+    print(f"[short series] n={n} nnz={g.nnz} sources={k} T={T}", flush=True)
+    half = _query(ops, csr, src, src, T, ALPHA, True)[0].double()
+    full = _query(ops, csr, src, src[torch.arange(k)], T, ALPHA, False)[0].double()
+    x, _ = _push64(g, src.cpu().numpy(), T, ALPHA)
+    want = x[src.long()].T
+    live = want > 0
+    rel = lambda a, b: ((a - b)[live] / b[live]).pow(2).mean().sqrt().item()
+    # One rounding of u = 2^-24 or so per push and value, and a row's sum of
+    # positive terms: T u against FP64.  The two routes share the first half;
+    # what is left are four pushes of one, and of the other a product whose FP32
+    # sums have at most 128 terms (64 additions, sqrt(64 / 3) / 2 u of half the
+    # mass) and a difference of two iterates: 6 u apart.
+    assert rel(full, want) <= T * 2.0 ** -24
+    assert rel(half, want) <= T * 2.0 ** -24
+    assert rel(half, full) <= 6 * 2.0 ** -24
