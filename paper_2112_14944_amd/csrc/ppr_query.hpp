@@ -18,10 +18,23 @@
 //
 // A query among its own sources (the targets are the source list) needs only
 // the block [sources x sources] of the result, and Y is symmetric:
-//     Y_{a+b}[S, S] = Y_a[S, S] + (Y_{a+1} - Y_a)[:, S]^T D Y_b[:, S] / (alpha (1-alpha)),
-// so about T / 2 pushes and one tall product on the matrix cores replace T
-// pushes.  The product carries (1-alpha)^(T/2) of the mass (1e-3 at T = 86).
+//     Y_{a+b}[S, S] = Y_a[S, S] + (Y_{a+1} - Y_a)[:, S]^T D Y_b[:, S] / (alpha (1-alpha)).
+// A push passes from one factor of the product to the other, (Q V)^T D Y = V^T D
+// (Q Y), and Q Y_b = Y_{b+1} - E with E the sources' own term (alpha (1-alpha) / d
+// at each source), so with a = P = T / 2 + 1
+//     Y_T[S, S] = Y_P[S, S] + (Y_P - Y_{P-1})[:, S]^T D (Y_{T-P+1} - E)[:, S] / (alpha (1-alpha)),
+// T - P + 1 = P - 1 or P: about T / 2 pushes and one tall product on the matrix
+// cores replace T pushes.  The product carries (1-alpha)^(T/2) of the mass (1e-3
+// at T = 86).  Without E, an entry of the difference, which holds the rounding of
+// two iterates, meets no entry near 1 of the other factor; and X_P is summed anew
+// from Y_{P-1} at the sources' rows, so that its rounding to Y's scale does not
+// reach the result.  The result is then no further from 64 bits than T pushes
+// (block of 250 sources of 12000 nodes, T = 86, norm of the error: 3.0e-8 by the
+// LDS kernels and 3.0e-8 so; 4.8e-8 with (Y_{P} - Y_{P-1})^T D Y_{T-P+1} added to
+// Y_{P-1}).
 #pragma once
+
+#include <type_traits>
 
 #include "dense.hpp"
 #include "ppr_dense.hpp"
@@ -119,8 +132,21 @@ __device__ __forceinline__ float4 query_gather(__amdgpu_buffer_rsrc_t rin, const
     return acc;
 }
 
-// One push.  hist: the class ends of the row order (stream_row_order).
-template <int Q, bool WEIGHTED>
+// Adds a wave's lane groups of Q lanes, in FP64 like the parts of a split row of
+// the mid-size kernel, into every lane.
+template <int Q>
+__device__ __forceinline__ float4 query_group_sum(const float4& a) {
+    double s[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+    for (int o = Q; o < kWave; o <<= 1)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[c] += __shfl_xor(s[c], o, kWave);
+    return make_float4((float)s[0], (float)s[1], (float)s[2], (float)s[3]);
+}
+
+// One push.  hist: the class ends of the row order (stream_row_order).  FINAL:
+// the last push leaves X itself, as no factor follows its sums.
+template <int Q, bool WEIGHTED, bool FINAL>
 __global__ __launch_bounds__(256) void query_step_kernel(const RowEnt* __restrict__ rows,
                                                          const int32_t* __restrict__ hist,
                                                          const int32_t* __restrict__ col_idx,
@@ -164,18 +190,10 @@ __global__ __launch_bounds__(256) void query_step_kernel(const RowEnt* __restric
         const int skip = whole ? 8 * grp : 0;
         float4 acc = query_gather<Q, WEIGHTED>(rin, col_idx, weight, rs + skip, max(dg - skip, 0), whole ? 8 * G : 8,
                                                lane);
-        if (whole) {
-#pragma unroll
-            for (int o = Q; o < kWave; o <<= 1) {
-                acc.x += __shfl_xor(acc.x, o, kWave);
-                acc.y += __shfl_xor(acc.y, o, kWave);
-                acc.z += __shfl_xor(acc.z, o, kWave);
-                acc.w += __shfl_xor(acc.w, o, kWave);
-            }
-        }
+        if (whole) acc = query_group_sum<Q>(acc);
         if (has && dg == 0) acc = slab_load(rin, (uint32_t)v * (16u * Q) | (uint32_t)q * 16u);
         if (has && (!whole || grp == 0)) {
-            const float sv = (1.0f - alpha) * invd[v];
+            const float sv = FINAL ? 1.0f : (1.0f - alpha) * invd[v];
             acc.x = (acc.x + (v == sn[0] ? alpha : 0.f)) * sv;
             acc.y = (acc.y + (v == sn[1] ? alpha : 0.f)) * sv;
             acc.z = (acc.z + (v == sn[2] ? alpha : 0.f)) * sv;
@@ -185,16 +203,16 @@ __global__ __launch_bounds__(256) void query_step_kernel(const RowEnt* __restric
     }
 }
 
-// Y_1 at the source rows (the rest is zero).
+// Y_1 (X_1 when final) at the source rows (the rest is zero).
 static __global__ void query_init_kernel(const int32_t* __restrict__ src, const float* __restrict__ invd, int32_t n,
-                                         int32_t ncols, float alpha, int W, float* __restrict__ y) {
+                                         int32_t ncols, float alpha, int W, int final_, float* __restrict__ y) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= ncols) return;
     const int v = src ? src[s] : s;
-    y[qidx(v, s, n, W)] = alpha * ((1.0f - alpha) * invd[v]);
+    y[qidx(v, s, n, W)] = final_ ? alpha : alpha * ((1.0f - alpha) * invd[v]);
 }
 
-// part[c] = (hi - lo)[:, S]^T D b[:, S] / (alpha (1-alpha)) over the c-th
+// part[c] = (hi - lo)[:, S]^T D (b - E)[:, S] / (alpha (1-alpha)) over the c-th
 // piece of the rows, b = lo or hi; tiles (I, J), I <= J, of 64 x 64 sources.
 // The terms are positive, so a chain of FP32 sums rounds the more the longer it
 // is: the running sums are set aside in FP64 every kGramChunk rows, whatever the
@@ -206,7 +224,8 @@ constexpr int kGramChunk = 128;
 
 static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
     const float* __restrict__ lo, const float* __restrict__ hi, int use_hi, const float* __restrict__ deg,
-    float scale, int32_t n, int W, int32_t ld, int32_t k, int32_t rows, float* __restrict__ part) {
+    const float* __restrict__ invd, const int32_t* __restrict__ src, float alpha, int32_t n, int W, int32_t ld,
+    int32_t k, int32_t rows, float* __restrict__ part) {
     constexpr int KB = kDenseK;
     constexpr int NP = KB / 4;
     __shared__ DenseLds<64> L;
@@ -223,6 +242,10 @@ static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
     const bool oki = ci < ld, okj = cj < ld;
     const int64_t bi = oki ? qidx(0, ci, n, W) : 0, bj = okj ? qidx(0, cj, n, W) : 0;
     const float* __restrict__ b = use_hi ? hi : lo;
+    const float scale = 1.0f / (alpha * (1.0f - alpha));
+    // E's one entry in this thread's column of b
+    const int sj = cj < k ? src[cj] : -1;
+    const float ej = sj >= 0 ? alpha * ((1.0f - alpha) * invd[sj]) : 0.f;
     DenseAcc c;
     double sum[16];
 #pragma unroll
@@ -239,7 +262,7 @@ static __global__ __launch_bounds__(kDenseThreads) void query_gram_kernel(
             const int64_t o = (int64_t)(in ? u : 0) * W;
             const float d = in ? deg[u] : 0.f;
             ra[p] = in && oki ? hi[bi + o] - lo[bi + o] : 0.f;
-            rb[p] = in && okj ? b[bj + o] * (scale * (d > 0.f ? d : 1.0f)) : 0.f;
+            rb[p] = in && okj ? (b[bj + o] - (u == sj ? ej : 0.f)) * (scale * (d > 0.f ? d : 1.0f)) : 0.f;
         }
     };
     fetch(v0);
@@ -300,35 +323,69 @@ static __global__ __launch_bounds__(256) void query_gram_sum_kernel(const float*
     if (w == 0 && e < kk) prod[e] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
-// Outputs: row i of pi_hat / DPPR over the targets, from Y (64 targets x one
-// slab through LDS), plus the product when there is one.
+// Outputs: row i of pi_hat / DPPR over the targets, from X (64 targets x one slab
+// through LDS).
 static __global__ __launch_bounds__(256) void query_out_kernel(
-    const float* __restrict__ y, int32_t n, int W, int32_t ncols, const int32_t* __restrict__ src,
-    const int32_t* __restrict__ tgt, int32_t n_tgt, const float* __restrict__ deg, const float* __restrict__ invd,
-    float alpha, const double* __restrict__ prod, const int32_t* __restrict__ refuse, float* __restrict__ ppr_out,
-    float* __restrict__ dppr_out) {
+    const float* __restrict__ x, int32_t n, int W, int32_t ncols, const int32_t* __restrict__ src,
+    const int32_t* __restrict__ tgt, int32_t n_tgt, const float* __restrict__ deg,
+    const int32_t* __restrict__ refuse, float* __restrict__ ppr_out, float* __restrict__ dppr_out) {
     __shared__ float tile[64][kSlab + 1];
     const int64_t j0 = (int64_t)blockIdx.x * 64;
     const int c0 = blockIdx.y * W;
+    const bool none = refuse && *refuse;
     for (int e = threadIdx.x; e < 64 * W; e += 256) {
         const int jj = e / W, c = e % W;
         const int64_t j = j0 + jj;
-        tile[jj][c] = j < n_tgt ? y[qidx(tgt ? tgt[j] : j, c0 + c, n, W)] : 0.f;
+        tile[jj][c] = none ? __int_as_float(0x7fc00000) : (j < n_tgt ? x[qidx(tgt ? tgt[j] : j, c0 + c, n, W)] : 0.f);
     }
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int64_t j = j0 + lane;
     if (j >= n_tgt) return;
-    const double un = dense_unscale(invd[tgt ? tgt[j] : j], alpha);
     for (int c = threadIdx.x >> 6; c < W; c += 4) {
         const int i = c0 + c;
         if (i >= ncols) break;
-        double s = (double)tile[lane][c];
-        if (prod) s += prod[(int64_t)i * ncols + j];
-        if (refuse && *refuse) s = (double)__int_as_float(0x7fc00000);
-        const float x = (float)(s * un);
-        if (ppr_out) ppr_out[(int64_t)i * n_tgt + j] = x;
-        if (dppr_out) dppr_out[(int64_t)i * n_tgt + j] = x * deg[src ? src[i] : i];
+        const float v = tile[lane][c];
+        if (ppr_out) ppr_out[(int64_t)i * n_tgt + j] = v;
+        if (dppr_out) dppr_out[(int64_t)i * n_tgt + j] = v * deg[src ? src[i] : i];
+    }
+}
+
+// Outputs of a query among its sources: X_P at each source's row, the push of
+// Y_{P-1} over that row by one wave per slab, plus the product; one rounding.
+template <int Q, bool WEIGHTED>
+__global__ __launch_bounds__(256) void query_block_out_kernel(
+    const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, const float* __restrict__ weight,
+    const float* __restrict__ deg, const float* __restrict__ invd, const int32_t* __restrict__ src, int32_t n,
+    int32_t k, float alpha, const float* __restrict__ y, const double* __restrict__ prod,
+    const int32_t* __restrict__ refuse, float* __restrict__ ppr_out, float* __restrict__ dppr_out) {
+    constexpr int W = 4 * Q;
+    constexpr int G = kWave / Q;
+    const int lane = threadIdx.x & 63;
+    const int q = lane % Q, grp = lane / Q;
+    const int slab = blockIdx.y;
+    const int j = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
+    if (j >= k) return;
+    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(y + (int64_t)slab * n * W), 0, (int)((uint32_t)n * (W * 4)), 0x00020000);
+    const int v = src[j];
+    const int rs = row_ptr[v], dg = row_ptr[v + 1] - rs;
+    const int skip = 8 * grp;
+    float4 acc = query_gather<Q, WEIGHTED>(rin, col_idx, weight, rs + skip, max(dg - skip, 0), 8 * G, lane);
+    acc = query_group_sum<Q>(acc);
+    if (dg == 0) acc = slab_load(rin, (uint32_t)v * (16u * Q) | (uint32_t)q * 16u);
+    if (grp != 0) return;
+    const double un = dense_unscale(invd[v], alpha);
+    const float s[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int i = slab * W + q * 4 + c;
+        if (i >= k) continue;
+        const int si = src[i];
+        double x = (double)s[c] + (si == v ? (double)alpha : 0.0) + prod[(int64_t)i * k + j] * un;
+        if (refuse && *refuse) x = (double)__int_as_float(0x7fc00000);
+        if (ppr_out) ppr_out[(int64_t)i * k + j] = (float)x;
+        if (dppr_out) dppr_out[(int64_t)i * k + j] = (float)(x * (double)deg[si]);
     }
 }
 
@@ -404,10 +461,8 @@ static __global__ __launch_bounds__(1024) void query_refuse_kernel(const RowEnt*
 }
 
 // Column sums of X over pieces of the rows in FP64 (the residual's first pass).
-static __global__ __launch_bounds__(256) void query_colsum_kernel(const float* __restrict__ y,
-                                                                  const float* __restrict__ invd, float alpha,
-                                                                  int32_t n, int W, int64_t ld,
-                                                                  const int32_t* __restrict__ refuse,
+static __global__ __launch_bounds__(256) void query_colsum_kernel(const float* __restrict__ x, int32_t n, int W,
+                                                                  int64_t ld, const int32_t* __restrict__ refuse,
                                                                   double* __restrict__ part) {
     __shared__ double red[256];
     const int c = threadIdx.x % W, g = threadIdx.x / W, ng = 256 / W;
@@ -415,8 +470,7 @@ static __global__ __launch_bounds__(256) void query_colsum_kernel(const float* _
     const int64_t r1 = min((int64_t)n, r0 + kStreamResidRows);
     const int64_t col = (int64_t)blockIdx.y * W + c;
     double s = 0.0;
-    for (int64_t r = r0 + g; r < r1; r += ng)
-        s += (double)(float)((double)y[qidx(r, col, n, W)] * dense_unscale(invd[r], alpha));
+    for (int64_t r = r0 + g; r < r1; r += ng) s += (double)x[qidx(r, col, n, W)];
     red[threadIdx.x] = s;
     __syncthreads();
     if (g == 0) {
@@ -472,7 +526,7 @@ inline bool query_faster(int n, int64_t nnz, int n_src, int T, bool halved) {
     return here < there;
 }
 
-template <int Q>
+template <int Q, bool FINAL>
 inline void query_step(const ppr_csr* g, const RowEnt* rows, const int32_t* hist, const float* invd,
                        const int32_t* src, int n_src, float alpha, const float* in, float* out, hipStream_t s) {
     constexpr int G = kWave / Q;
@@ -480,11 +534,24 @@ inline void query_step(const ppr_csr* g, const RowEnt* rows, const int32_t* hist
     const dim3 grid((unsigned)std::min<int64_t>((upper + 3) / 4, kQueryMaxBlocks),
                     (unsigned)(query_ld(n_src) / (4 * Q)));
     if (g->weight)
-        hipLaunchKernelGGL((query_step_kernel<Q, true>), grid, dim3(256), 0, s, rows, hist, g->col_idx, g->weight,
+        hipLaunchKernelGGL((query_step_kernel<Q, true, FINAL>), grid, dim3(256), 0, s, rows, hist, g->col_idx, g->weight,
                            invd, src, g->n, n_src, alpha, in, out);
     else
-        hipLaunchKernelGGL((query_step_kernel<Q, false>), grid, dim3(256), 0, s, rows, hist, g->col_idx, nullptr,
+        hipLaunchKernelGGL((query_step_kernel<Q, false, FINAL>), grid, dim3(256), 0, s, rows, hist, g->col_idx, nullptr,
                            invd, src, g->n, n_src, alpha, in, out);
+}
+
+template <int Q>
+inline void query_block_out(const ppr_csr* g, const int32_t* src, int n_src, float alpha, const float* y,
+                            const float* deg, const float* invd, const QueryWs& w, float* ppr_out, float* dppr_out,
+                            hipStream_t s) {
+    const dim3 grid((unsigned)((n_src + 3) / 4), (unsigned)(query_ld(n_src) / (4 * Q)));
+    if (g->weight)
+        hipLaunchKernelGGL((query_block_out_kernel<Q, true>), grid, dim3(256), 0, s, g->row_ptr, g->col_idx, g->weight,
+                           deg, invd, src, g->n, n_src, alpha, y, w.prod, w.refuse, ppr_out, dppr_out);
+    else
+        hipLaunchKernelGGL((query_block_out_kernel<Q, false>), grid, dim3(256), 0, s, g->row_ptr, g->col_idx, nullptr,
+                           deg, invd, src, g->n, n_src, alpha, y, w.prod, w.refuse, ppr_out, dppr_out);
 }
 
 // T pushes from every source; halved when the targets are the sources and the
@@ -502,39 +569,44 @@ inline void query_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, c
     fill<float>(w.ya, 0.0f, (int64_t)n * ld, s);
     float* in = w.ya;
     float* out = w.yb;
-    // iterates to reach: Y_T, or with P = T / 2 + 1 both Y_{P-1} and Y_P
+    // iterates to reach: X_T, or with P = T / 2 + 1 both Y_{P-1} and Y_P
     const int last = w.gram ? T / 2 + 1 : T;
     if (T >= 1)
         hipLaunchKernelGGL(query_init_kernel, dim3((unsigned)((n_src + 255) / 256)), dim3(256), 0, s, src, invd, n,
-                           n_src, alpha, W, in);
-    for (int t = 1; t < last; ++t) {
-        if (W == 8) query_step<2>(g, rows, w.hist, invd, src, n_src, alpha, in, out, s);
-        else if (W == 16) query_step<4>(g, rows, w.hist, invd, src, n_src, alpha, in, out, s);
-        else query_step<8>(g, rows, w.hist, invd, src, n_src, alpha, in, out, s);
+                           n_src, alpha, W, last == 1, in);
+    auto push = [&](auto final_) {
+        constexpr bool F = decltype(final_)::value;
+        if (W == 8) query_step<2, F>(g, rows, w.hist, invd, src, n_src, alpha, in, out, s);
+        else if (W == 16) query_step<4, F>(g, rows, w.hist, invd, src, n_src, alpha, in, out, s);
+        else query_step<8, F>(g, rows, w.hist, invd, src, n_src, alpha, in, out, s);
         std::swap(in, out);
+    };
+    for (int t = 1; t < last; ++t) {
+        if (t == last - 1 && !w.gram) push(std::true_type{});
+        else push(std::false_type{});
     }
-    const float* y = in;
     if (w.gram) {
-        // in = Y_P, out = Y_{P-1}.  T = 2 (P-1): Y_T = Y_{P-1} + (Y_P - Y_{P-1}) D Y_{P-1} / ..;
-        // T = 2 (P-1) + 1: the product is with Y_P
-        y = out;
+        // in = Y_P, out = Y_{P-1}
         const int64_t nt = (n_src + 63) / 64;
         const int rows_per = (n + w.pieces - 1) / w.pieces;
         hipLaunchKernelGGL(query_gram_kernel, dim3((unsigned)(nt * (nt + 1) / 2), (unsigned)w.pieces),
-                           dim3(kDenseThreads), 0, s, out, in, T & 1, deg, 1.0f / (alpha * (1.0f - alpha)), n, W,
-                           (int32_t)ld, n_src, rows_per, w.gram);
+                           dim3(kDenseThreads), 0, s, out, in, T & 1, deg, invd, src, alpha, n, W, (int32_t)ld, n_src,
+                           rows_per, w.gram);
         const int64_t kk = (int64_t)n_src * n_src;
         hipLaunchKernelGGL(query_gram_sum_kernel, dim3((unsigned)((kk + 63) / 64)), dim3(256), 0, s, w.gram, kk,
                            w.pieces, w.prod);
+        if (W == 8) query_block_out<2>(g, src, n_src, alpha, out, deg, invd, w, ppr_out, dppr_out, s);
+        else if (W == 16) query_block_out<4>(g, src, n_src, alpha, out, deg, invd, w, ppr_out, dppr_out, s);
+        else query_block_out<8>(g, src, n_src, alpha, out, deg, invd, w, ppr_out, dppr_out, s);
+        return;
     }
     if (ppr_out || dppr_out)
         hipLaunchKernelGGL(query_out_kernel, dim3((unsigned)((n_tgt + 63) / 64), (unsigned)(ld / W)), dim3(256), 0, s,
-                           y, n, W, n_src, src, tgt, n_tgt, deg, invd, alpha, w.gram ? w.prod : nullptr, w.refuse,
-                           ppr_out, dppr_out);
+                           in, n, W, n_src, src, tgt, n_tgt, deg, w.refuse, ppr_out, dppr_out);
     if (resid) {
         const int64_t chunks = stream_resid_chunks(n);
-        hipLaunchKernelGGL(query_colsum_kernel, dim3((unsigned)chunks, (unsigned)(ld / W)), dim3(256), 0, s, y, invd,
-                           alpha, n, W, ld, w.refuse, w.part);
+        hipLaunchKernelGGL(query_colsum_kernel, dim3((unsigned)chunks, (unsigned)(ld / W)), dim3(256), 0, s, in, n, W,
+                           ld, w.refuse, w.part);
         hipLaunchKernelGGL(stream_resid_kernel, dim3((unsigned)((n_src + 255) / 256)), dim3(256), 0, s, w.part,
                            chunks, ld, n_src, resid);
     }
