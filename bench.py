@@ -151,7 +151,7 @@ def series_plan(n, nnz, T):
             m = (T + k) // (k + 1)
             c = 100 * (m + 4) * nnz + 22 * k * n * (n + 64)
             if c < cost:
-                best, cost = (m, k), c
+                best, cost = (m + (T == (k + 1) * m), k), c
     return best
 
 

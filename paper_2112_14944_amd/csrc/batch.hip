@@ -280,12 +280,12 @@ struct BatchArgs {
 };
 
 // The pools of the all-pairs series (subgraph blocks at mat_off, ld = n): V in
-// the 1/Delta pool, Y_m in the Delta pool (both are written after PPR only);
+// the 1/Delta pool, X_m in the Delta pool (both are written after PPR only);
 // W_p alternates between the DPPR pool and one of its own, so that the last,
 // W_k as DPPR, lands in the former.
 struct SeriesPools {
     float* v;
-    float* ym;
+    float* xm;
     float* w[2];  // DPPR pool, the other
 };
 
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(kResThreads) void batch_ppr_kernel(BatchArgs b, Bat
             t.m = d.m;
             t.r = d.r;
             a.yr = series_pool(d.k, 0) ? sp.w[1] : sp.w[0];
-            a.ym = sp.ym;
+            a.xm = sp.xm;
             a.vd = sp.v;
         }
         res_tile<COLS, false>(t, a, L);
@@ -365,19 +365,19 @@ __global__ __launch_bounds__(kDenseThreads, 2) void batch_product_kernel(BatchAr
         const DensePlan d = dense_plan(n, b.row_ptr[base + n] - b.row_ptr[base], b.series_T);
         const int64_t off = b.mat_off[g];
         const float* V = uniform_ptr(sp.v + off);
-        const float* Ym = uniform_ptr(sp.ym + off);
-        const float* W = phase == 1 && d.r == d.m ? Ym : uniform_ptr(sp.w[series_pool(d.k, phase - 1)] + off);
+        const float* xm = uniform_ptr(sp.xm + off);
+        const float* W = uniform_ptr(sp.w[series_pool(d.k, phase - 1)] + off);
         float* out = uniform_ptr(sp.w[series_pool(d.k, phase)] + off);
         const float* deg = uniform_ptr(b.r.deg + base);
         const float* invd = uniform_ptr(b.invd + base);
         const int64_t t = task - pre[pos];
         const bool last = phase == d.k;
         if (dense_bt(n) == 64) {
-            if (last) dense_product_tile<64, true>(V, Ym, W, deg, invd, b.r.alpha, n, t, L.narrow, out);
-            else dense_product_tile<64, false>(V, Ym, W, deg, invd, b.r.alpha, n, t, L.narrow, out);
+            if (last) dense_product_tile<64, kDenseDppr>(V, xm, W, deg, invd, b.r.alpha, n, t, L.narrow, out);
+            else dense_product_tile<64, kDenseNext>(V, xm, W, deg, invd, b.r.alpha, n, t, L.narrow, out);
         } else {
-            if (last) dense_product_tile<128, true>(V, Ym, W, deg, invd, b.r.alpha, n, t, L.wide, out);
-            else dense_product_tile<128, false>(V, Ym, W, deg, invd, b.r.alpha, n, t, L.wide, out);
+            if (last) dense_product_tile<128, kDenseDppr>(V, xm, W, deg, invd, b.r.alpha, n, t, L.wide, out);
+            else dense_product_tile<128, kDenseNext>(V, xm, W, deg, invd, b.r.alpha, n, t, L.wide, out);
         }
     }
 }
@@ -702,7 +702,7 @@ static ppr_status batch_enqueue(const ppr_batch* b, float alpha, int32_t T, int3
     ba.r.ppr_out = nullptr;
     ba.r.dppr_out = dppr_pool;
     ba.r.resid = nullptr;
-    ba.r.yr = ba.r.ym = ba.r.vd = nullptr;
+    ba.r.yr = ba.r.xm = ba.r.vd = nullptr;
     const SeriesPools sp{w.inv, delta_pool, {dppr_pool, w.series}};
     const int cus = device_cu_count();
     hipLaunchKernelGGL((batch_ppr_kernel<16, 0>), dim3(cus), dim3(kResThreads), 0, s, ba, w.plan, sp);

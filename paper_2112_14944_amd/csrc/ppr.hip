@@ -522,18 +522,19 @@ static void launch_resident_any(bool weighted, const ResArgs& a, int n, int64_t 
 // 136 of them, 204 us a product; 528 64-wide ones, 136 us then, 125 us now).
 constexpr int kSingleBT = 64;
 
-__global__ __launch_bounds__(kDenseThreads, 2) void ppr_product_kernel(const float* V, const float* Ym,
+template <DenseOut OUT>
+__global__ __launch_bounds__(kDenseThreads, 2) void ppr_product_kernel(const float* V, const float* xm,
                                                                      const float* W, const float* deg,
-                                                                     float alpha, int32_t n, float* out) {
+                                                                     const float* invd, float alpha, int32_t n,
+                                                                     float* out) {
     __shared__ DenseLds<kSingleBT> L;
-    dense_product_tile<kSingleBT, false>(V, Ym, W, deg, nullptr, alpha, n, blockIdx.x, L, out);
+    dense_product_tile<kSingleBT, OUT>(V, xm, W, deg, invd, alpha, n, blockIdx.x, L, out);
 }
 
-// Outputs from Y_T, one block per source: pi_hat(s, t) = Y(s, t) d(t) / (1-alpha),
-// DPPR, and the FP64 residual over all nodes of the FP32 estimates.
-__global__ __launch_bounds__(256) void ppr_series_out_kernel(const float* __restrict__ Y,
-                                                             const float* __restrict__ deg,
-                                                             const float* __restrict__ invd, float alpha, int32_t n,
+// Outputs from X_T, one block per source: pi_hat(s, t), DPPR, and the FP64
+// residual over all nodes.
+__global__ __launch_bounds__(256) void ppr_series_out_kernel(const float* __restrict__ X,
+                                                             const float* __restrict__ deg, int32_t n,
                                                              const int32_t* __restrict__ src,
                                                              const int32_t* __restrict__ tgt, int32_t n_tgt,
                                                              float* __restrict__ ppr_out,
@@ -542,17 +543,16 @@ __global__ __launch_bounds__(256) void ppr_series_out_kernel(const float* __rest
     __shared__ double red[4];
     const int i = blockIdx.x;
     const int s = src ? src[i] : i;
-    const float* y = Y + (int64_t)s * n;
+    const float* row = X + (int64_t)s * n;
     const float ds = deg[s];
     for (int j = threadIdx.x; j < n_tgt; j += 256) {
-        const int t = tgt ? tgt[j] : j;
-        const float x = (float)((double)y[t] * dense_unscale(invd[t], alpha));
+        const float x = row[tgt ? tgt[j] : j];
         if (ppr_out) ppr_out[(int64_t)i * n_tgt + j] = x;
         if (dppr_out) dppr_out[(int64_t)i * n_tgt + j] = x * ds;
     }
     if (resid == nullptr) return;
     double sum = 0.0;
-    for (int v = threadIdx.x; v < n; v += 256) sum += (double)(float)((double)y[v] * dense_unscale(invd[v], alpha));
+    for (int v = threadIdx.x; v < n; v += 256) sum += (double)row[v];
     sum = wave_sum(sum);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
     __syncthreads();
@@ -560,7 +560,7 @@ __global__ __launch_bounds__(256) void ppr_series_out_kernel(const float* __rest
 }
 
 // All pairs by the series: a short run of pushes from every node, k products,
-// outputs.  buf: 4 n^2 floats (V, Y_m, and two that the W_p alternate between).
+// outputs.  buf: 4 n^2 floats (V, X_m, and two that the W_p alternate between).
 static void ppr_series(const ppr_csr* g, const DensePlan& p, const int32_t* src, const int32_t* tgt, int32_t n_tgt,
                        ResArgs a, const float* invd, float* ppr_out, float* dppr_out, double* resid, float* buf,
                        hipStream_t s) {
@@ -572,19 +572,22 @@ static void ppr_series(const ppr_csr* g, const DensePlan& p, const int32_t* src,
     a.ppr_out = a.dppr_out = nullptr;
     a.resid = nullptr;
     a.vd = buf;
-    a.ym = buf + n2;
+    a.xm = buf + n2;
     a.yr = w[0];
     launch_resident_any(g->weight != nullptr, a, n, g->nnz, n, n, p.m + 1, p.m, p.r, s);
-    const float* from = p.r == p.m ? a.ym : w[0];
+    const dim3 grid((unsigned)dense_tiles(n, kSingleBT));
     for (int i = 0; i < p.k; ++i) {
+        const float* from = w[i & 1];
         float* to = w[(i + 1) & 1];
-        const dim3 grid((unsigned)dense_tiles(n, kSingleBT));
-        hipLaunchKernelGGL(ppr_product_kernel, grid, dim3(kDenseThreads), 0, s, a.vd, a.ym, from, a.deg, a.alpha, n,
-                           to);
-        from = to;
+        if (i + 1 < p.k)
+            hipLaunchKernelGGL(ppr_product_kernel<kDenseNext>, grid, dim3(kDenseThreads), 0, s, a.vd, a.xm, from,
+                               a.deg, invd, a.alpha, n, to);
+        else
+            hipLaunchKernelGGL(ppr_product_kernel<kDensePpr>, grid, dim3(kDenseThreads), 0, s, a.vd, a.xm, from,
+                               a.deg, invd, a.alpha, n, to);
     }
-    hipLaunchKernelGGL(ppr_series_out_kernel, dim3(n), dim3(256), 0, s, from, a.deg, invd, a.alpha, n, src, tgt,
-                       n_tgt, ppr_out, dppr_out, resid);
+    hipLaunchKernelGGL(ppr_series_out_kernel, dim3(n), dim3(256), 0, s, w[p.k & 1], a.deg, n, src, tgt, n_tgt,
+                       ppr_out, dppr_out, resid);
 }
 
 ppr_status validate_csr(const ppr_csr* g) {
@@ -630,7 +633,7 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
         a.ppr_out = ppr_out;
         a.dppr_out = dppr_out;
         a.resid = resid;
-        a.yr = a.ym = a.vd = nullptr;
+        a.yr = a.xm = a.vd = nullptr;
         // every node a source (sources are distinct): all pairs
         const DensePlan p = dense_plan(n, g->nnz, n_src == n && w.series != nullptr ? T : 0);
         if (p.k > 0)

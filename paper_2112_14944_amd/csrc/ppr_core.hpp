@@ -122,7 +122,7 @@ struct TileTask {
     int64_t cbase;    // first arc-copy entry of the graph
     int32_t cwords;   // arc-copy entries of the graph (res_arc_words)
     int32_t T;        // pushes
-    int32_t m, r;     // series form (m > 0): T = m + 1, the iterates Y_r, Y_m and Y_{m+1} - Y_m go out
+    int32_t m, r;     // series form (0 < r < m): T = m + 1, Y_r, X_m and Y_{m+1} - Y_m go out
 };
 
 // Where graph g's slot table and arc copy start, for a graph whose nodes start
@@ -145,8 +145,8 @@ struct ResArgs {
     float* ppr_out;          // nullable
     float* dppr_out;         // nullable
     double* resid;           // nullable, indexed by source index
-    float* yr;               // series form: Y_r, Y_m and Y_{m+1} - Y_m of every graph, [source][node] at
-    float* ym;               // out_off with ld columns (yr is not written when r == m)
+    float* yr;               // series form: Y_r, X_m without the sources' own alpha, and Y_{m+1} - Y_m
+    float* xm;               // of every graph, [source][node] at out_off with ld columns
     float* vd;
 };
 
@@ -396,8 +396,9 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
         }
         // the source bits are re-read each step, so that their tests stay in
         // vector registers instead of being hoisted into scalar masks
-        const uint32_t sl = (uint32_t)opaque((int)sbits_lo);
-        const uint32_t sh = (uint32_t)opaque((int)sbits_hi);
+        const bool bare = series && it + 1 == t.m;  // X_m without the sources' own alpha
+        const uint32_t sl = (uint32_t)opaque(bare ? 0 : (int)sbits_lo);
+        const uint32_t sh = (uint32_t)opaque(bare ? 0 : (int)sbits_hi);
 #pragma unroll
         for (int k = 0; k < kResMaxK; ++k) {
             const int gk = wave + kResWaves * k;
@@ -452,20 +453,37 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
             }
         }
         __syncthreads();
-        if (series && it == t.T - 1) {
-            // the last push of a series: what it adds
+        if (series && it == t.m) break;  // V, from here on in registers
+        if (bare) {
+            // X_m goes out.  What the push added, Y_m - Y_{m-1}, takes the iterate's
+            // place for one more push without the sources' term, which gives
+            // Y_{m+1} - Y_m: the rounding of the two iterates, which their difference
+            // holds, is then averaged over each row's neighbours.
 #pragma unroll
             for (int k = 0; k < kResMaxK; ++k) {
                 if ((wave + kResWaves * k) * RPW < nn) {
-                    const float4 y = lds_load4(lds, vaddr[k]);
-                    *reinterpret_cast<float4*>(reinterpret_cast<char*>(lds) + vaddr[k]) =
-                        make_float4(xr[k].x * sc[k] - y.x, xr[k].y * sc[k] - y.y, xr[k].z * sc[k] - y.z,
-                                    xr[k].w * sc[k] - y.w);
+                    float4* p = reinterpret_cast<float4*>(reinterpret_cast<char*>(lds) + vaddr[k]);
+                    const float4 y = *p;
+                    const float4 x = xr[k];
+                    *p = x;
+                    const uint32_t sb = (k < 8 ? sbits_lo >> (4 * k) : sbits_hi >> (4 * (k - 8))) & 15u;
+                    xr[k] = make_float4((x.x + (sb & 1u ? alpha : 0.f)) * sc[k] - y.x,
+                                        (x.y + (sb & 2u ? alpha : 0.f)) * sc[k] - y.y,
+                                        (x.z + (sb & 4u ? alpha : 0.f)) * sc[k] - y.z,
+                                        (x.w + (sb & 8u ? alpha : 0.f)) * sc[k] - y.w);
                 }
             }
             __syncthreads();
-            res_dump<COLS>(t, lds, a.vd);
-            break;
+            res_dump<COLS>(t, lds, a.xm);
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kResMaxK; ++k) {
+                if ((wave + kResWaves * k) * RPW < nn)
+                    *reinterpret_cast<float4*>(reinterpret_cast<char*>(lds) + vaddr[k]) = xr[k];
+            }
+            __syncthreads();
+            sbits_lo = sbits_hi = 0;
+            continue;
         }
 #pragma unroll
         for (int k = 0; k < kResMaxK; ++k) {
@@ -476,17 +494,12 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
         __syncthreads();
         // Y_{it+1} is whole; the next push overwrites it only after its own
         // first barrier
-        if (series && (it + 1 == t.r || it + 1 == t.m)) res_dump<COLS>(t, lds, it + 1 == t.m ? a.ym : a.yr);
-    }
-    if (series) {
-        __syncthreads();
-        return;
+        if (series && it + 1 == t.r) res_dump<COLS>(t, lds, a.yr);
     }
 
-    // Epilogue.  FP64 residual 1 - sum_v pi_hat(s, v): per-column partial sums
-    // go through the (no longer needed) iterate area; then the unscaled
-    // iterate is written column-swizzled so that the transposed read below is
-    // conflict-free.  Dummy slots hold zeros and add nothing.
+    // Epilogue.  Sums of the unscaled values over the rows, per column, in FP64:
+    // per-wave sums go through the (no longer needed) iterate area.  Dummy slots
+    // hold zeros and add nothing.
     double part[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < kResMaxK; ++k) {
@@ -510,12 +523,42 @@ __device__ __forceinline__ void res_tile(const TileTask& t, const ResArgs& a, Re
         for (int i = 0; i < 4; ++i) red[wave * COLS + col0 + i] = part[i];
     }
     __syncthreads();
+    if (series) {
+        // V = Y_{m+1} - Y_m.  What push m + 1 adds holds alpha (1-alpha)^m of the
+        // source's mass; the rounding of the iterates moved that by a few u / alpha,
+        // alike for all nodes the source reaches after so many pushes, which is
+        // what the products would pass on.  So each column is brought to it.
+        double mass = (double)alpha, step = 1.0 - (double)alpha;
+        for (int e = t.m; e > 0; e >>= 1, step *= step)
+            if (e & 1) mass *= step;
+        float f[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double s = 0.0;
+            for (int w = 0; w < kResWaves; ++w) s += red[w * COLS + col0 + i];
+            f[i] = s > 0.0 ? (float)fmin(mass / s, 2.0) : 0.f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kResMaxK; ++k) {
+            if ((wave + kResWaves * k) * RPW < n)
+                *reinterpret_cast<float4*>(reinterpret_cast<char*>(lds) + vaddr[k]) =
+                    make_float4(xr[k].x * sc[k] * f[0], xr[k].y * sc[k] * f[1], xr[k].z * sc[k] * f[2],
+                                xr[k].w * sc[k] * f[3]);
+        }
+        __syncthreads();
+        res_dump<COLS>(t, lds, a.vd);
+        __syncthreads();
+        return;
+    }
     if (tid < t.ncols && a.resid) {
         double s = 0.0;
         for (int w = 0; w < kResWaves; ++w) s += red[w * COLS + tid];
         as_global_w(a.resid)[t.s0 + tid] = 1.0 - s;
     }
     __syncthreads();
+    // the unscaled iterate, column-swizzled so that the transposed read below is
+    // conflict-free
 #pragma unroll
     for (int k = 0; k < kResMaxK; ++k) {
         if ((wave + kResWaves * k) * RPW < n) {

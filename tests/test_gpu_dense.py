@@ -296,3 +296,33 @@ def test_few_sources_precision(n, gamma, weighted, targets):
         ef, es = _errors(f, v), _errors(s, v)
         print("norm %.3g %.3g  entries %.3g %.3g" % (ef[0], es[0], ef[1], es[1]), flush=True)
         assert ef[0] <= 1.2 * es[0] and ef[1] <= 1.2 * es[1]
+
+
+# All pairs by the series and by all pushes (the general workspace): the one is
+# no further from FP64 than the other; every tile width, 1 to 3 products,
+# weights, an isolated node.
+@pytest.mark.parametrize("n,degree,T,k", [(300, 24, 86, 3), (500, 8, 86, 2), (513, 6, 86, 1), (1000, 24, 100, 2),
+                                          (1000, 50, 86, 3), (1500, 40, 86, 2), (2304, 60, 86, 2)])
+def test_all_pairs_precision(n, degree, T, k):
+    ops = get_ops()
+    g0 = synth.sbm(synth.equal_blocks(n, 4), min(1.0, 3.2 * degree / n), 0.27 * degree / n, 170 + n,
+                   weighted=(0.5, 2.0, 171 + n))
+    # every node on a ring as well: an isolated one holds all of its mass in one
+    # entry, whose rounding alone would be the norm
+    ring = np.stack([np.arange(n), (np.arange(n) + 1) % n])
+    e = np.unique(np.sort(np.concatenate([np.stack([g0.eu, g0.ev]), ring], 1), axis=0), axis=1)
+    w = (0.5 + 1.5 * np.random.default_rng(n).random(e.shape[1])).astype(np.float32)
+    g = synth.build_graph(n, e[0], e[1], w if n % 500 else None)
+    assert _series_plan(n, g.nnz, T)[0] == k, _series_plan(n, g.nnz, T)
+    csr = ops.Csr.from_graph(g, "cuda")
+    src = torch.as_tensor(np.random.default_rng(n).permutation(n).astype(np.int32), device="cuda")
+    print(f"[precision] n={n} nnz={g.nnz} T={T} products={k}", flush=True)
+    fast = _query(ops, csr, src, None, T, ALPHA, True)
+    slow = _query(ops, csr, src, None, T, ALPHA, False)
+    x, d = _push64(g, src.cpu().numpy(), T, ALPHA)
+    # the n diagonal entries make most of the norm: their error is known to about
+    # 1 / sqrt(2 n) of itself, 4.1% at n = 300; three times that
+    for f, s, v in ((fast[0], slow[0], x.T), (fast[1], slow[1], d[src.long()][:, None] * x.T)):
+        ef, es = _errors(f, v), _errors(s, v)
+        print("norm %.3g %.3g  entries %.3g %.3g" % (ef[0], es[0], ef[1], es[1]), flush=True)
+        assert ef[0] <= 1.12 * es[0] and ef[1] <= 1.12 * es[1]
