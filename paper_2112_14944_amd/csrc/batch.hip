@@ -679,7 +679,7 @@ static ppr_status batch_enqueue(const ppr_batch* b, float alpha, int32_t T, int3
     // iterates in the DPPR and the Delta pool at once, so a caller that gives one
     // array for both (and keeps Delta alone) gets all pushes
     const bool apart = dppr_pool + b->pool_size <= delta_pool || delta_pool + b->pool_size <= dppr_pool;
-    const int series_T = w.series != nullptr && apart ? T : 0;
+    const int series_T = w.series != nullptr && apart && dense_alpha(alpha) ? T : 0;
     hipLaunchKernelGGL(batch_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, b->node_off, b->row_ptr, G, series_T,
                        w.plan);
     if (ev) PPRVIZ_HIP_TRY(hipEventRecord(ev[1], s));

@@ -613,7 +613,7 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
     // pushes where the product costs less than the pushes it saves (60
     // TFLOP/s against 7 TB/s of gathers); a residual needs every node.
     QueryWs q = w.query;
-    const bool halve = q.gram != nullptr && tgt == src && n_tgt == n_src && resid == nullptr && T >= kQueryMinT &&
+    const bool halve = q.gram != nullptr && alpha >= kDenseMinAlpha && tgt == src && n_tgt == n_src && resid == nullptr && T >= kQueryMinT &&
                        (double)n * n_src / 60e12 < 0.5 * T * (double)g->nnz * 4 / 7e12;
     if (!halve) q.gram = nullptr;
     const bool lds = use_resident(n) || mid_cols_for(n) != 0;
@@ -635,7 +635,8 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
         a.resid = resid;
         a.yr = a.xm = a.vd = nullptr;
         // every node a source (sources are distinct): all pairs
-        const DensePlan p = dense_plan(n, g->nnz, n_src == n && w.series != nullptr ? T : 0);
+        const bool products = n_src == n && w.series != nullptr && dense_alpha(alpha);
+        const DensePlan p = dense_plan(n, g->nnz, products ? T : 0);
         if (p.k > 0)
             ppr_series(g, p, src, tgt, n_tgt, a, invd, ppr_out, dppr_out, resid, w.series, s);
         else

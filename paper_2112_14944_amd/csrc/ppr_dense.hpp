@@ -40,6 +40,17 @@ constexpr int kDenseMinN = 192;   // below it a product's tiles are mostly paddi
 constexpr int kDenseMinT = 24;    // the pieces have at least 4 pushes
 constexpr int kDenseMaxT = 4096;  // keeps the cost comparison below 2^63
 constexpr int kDenseMaxK = 3;     // products
+// alpha from which on pushes are replaced by products, here and for few sources
+// (ppr_query.hpp): the rounding that the difference of two iterates holds reaches
+// the result over alpha.  Error against 64 bits over that of all pushes, T for a
+// residual of 1e-6, graphs of 300 to 2048 nodes here: 0.95 to 1.1 at alpha = 0.1
+// and above, 0.5 to 1.6 at 0.05, up to 2.6 at 0.01; few sources 0.7 to 1.05 from
+// 0.05 on, 1.1 to 1.3 at 0.01.  At 0.5 (few pushes matter, an entry's error is that
+// of few roundings, and X_m and the sum are one more than pushes have) 1.14 here, at
+// 0.3 1.02.
+constexpr float kDenseMinAlpha = 0.1f;
+constexpr float kDenseMaxAlpha = 0.4f;  // all pairs
+__host__ __device__ inline bool dense_alpha(float alpha) { return alpha >= kDenseMinAlpha && alpha <= kDenseMaxAlpha; }
 constexpr int kDenseWideN = 512;  // batch: 128-wide tiles from this size on
 
 struct DensePlan {

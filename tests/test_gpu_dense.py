@@ -326,3 +326,40 @@ def test_all_pairs_precision(n, degree, T, k):
         ef, es = _errors(f, v), _errors(s, v)
         print("norm %.3g %.3g  entries %.3g %.3g" % (ef[0], es[0], ef[1], es[1]), flush=True)
         assert ef[0] <= 1.12 * es[0] and ef[1] <= 1.12 * es[1]
+
+
+# The routes that replace pushes by products, at other alphas.  Where they are
+# taken (all pairs 0.1 to 0.4, few sources from 0.1 on) they are no further from
+# FP64 than all pushes; elsewhere the faster workspace changes nothing.
+@pytest.mark.parametrize("alpha,T", [(0.5, 40), (0.3, 50), (0.1, 132), (0.0999, 132), (0.05, 270), (0.01, 300)])
+def test_other_alphas(alpha, T):
+    ops = get_ops()
+    g = synth.sbm(synth.equal_blocks(1000, 4), 0.1, 0.02, 61)
+    csr = ops.Csr.from_graph(g, "cuda")
+    src = torch.arange(g.n, dtype=torch.int32, device="cuda")
+    assert _series_plan(g.n, g.nnz, T)[0] > 0
+    h = synth.chung_lu(42000, 2.4, 20, 62)
+    hsr = ops.Csr.from_graph(h, "cuda")
+    live = np.nonzero(np.diff(h.row_ptr))[0]
+    hs = torch.as_tensor(np.random.default_rng(63).choice(live, 250, replace=False).astype(np.int32), device="cuda")
+    print(f"[alpha] {alpha} T={T}", flush=True)
+    for c, gr, s, t in ((csr, g, src, None), (hsr, h, hs, hs)):
+        fast, slow = _query(ops, c, s, t, T, alpha, True), _query(ops, c, s, t, T, alpha, False)
+        if alpha < 0.1 or (alpha > 0.4 and t is None):
+            assert torch.equal(fast[0], slow[0]) and torch.equal(fast[1], slow[1])
+            continue
+        x, d = _push64(gr, s.cpu().numpy(), T, alpha)
+        want = (x if t is None else x[t.long()]).T
+        # as in the tests at 0.15: the diagonal's 1000 and 250 entries make the norm,
+        # three times 1 / sqrt(2 k)
+        bar = 1 + 3 / (2 * s.numel()) ** 0.5
+        for f, r, v in ((fast[0], slow[0], want), (fast[1], slow[1], d[s.long()][:, None] * want)):
+            ef, es = _errors(f, v), _errors(r, v)
+            print("norm %.3g %.3g  entries %.3g %.3g" % (ef[0], es[0], ef[1], es[1]), flush=True)
+            assert ef[0] <= bar * es[0] and ef[1] <= bar * es[1]
+    if not 0.1 <= alpha <= 0.4:
+        gb = synth.concat_graphs([g])
+        b = ops.Batch(gb, "cuda")
+        bufs = ops.pprviz_batch(b, b.buffers(torch.zeros((g.n, 2), device="cuda")), alpha=alpha, tol=0.0, max_iter=T,
+                                stress_iters=0)
+        assert torch.equal(ops.graph_block(gb, bufs["dppr"], 0), _query(ops, csr, src, None, T, alpha, False)[1])
