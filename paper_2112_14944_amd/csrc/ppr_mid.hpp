@@ -53,7 +53,6 @@ constexpr int kMidWaves = kMidThreads / kWave;
 constexpr int kMidLdsFloats = 40832;  // 160 KB less the residual reduction scratch
 constexpr int kMidSlotCap = 48;       // slot table stride per wave (largest KS)
 constexpr int kMidGroup = 256;        // stream entries per group: 64 lanes x 4 arcs
-constexpr int kMidPrefetch = 2;       // spare groups behind the stream
 constexpr int kMidAhead = 4;          // groups each lane's entries are read ahead
 constexpr int kMidKeys = 65536;       // exact degree classes of the row order
 constexpr int kMidMaxParts = 1024;    // parts of split rows: they fill at most the first 16 slices
@@ -83,8 +82,7 @@ __host__ __device__ inline int64_t mid_slices(int n) { return (n + 63) / 64; }
 // gets NaN outputs.
 inline int64_t mid_stream_groups(int n, int64_t nnz) {
     const int64_t maxdeg = nnz < (int64_t)n ? nnz : (int64_t)n;
-    return (64 * 17 * (maxdeg + 4) + nnz + kMidGroup * mid_slices(n + kMidMaxParts) + kMidGroup - 1) / kMidGroup +
-           kMidPrefetch;
+    return (64 * 17 * (maxdeg + 4) + nnz + kMidGroup * mid_slices(n + kMidMaxParts) + kMidGroup - 1) / kMidGroup;
 }
 
 // Plan (int32 words): group counts of each wave's slots, the first group of
@@ -312,7 +310,7 @@ static __global__ __launch_bounds__(1024) void mid_plan_kernel(const RowEnt* __r
                 off += width[sl];
             }
         }
-        flag = off + kMidPrefetch > cap_groups ? 1 : 0;
+        flag = off > cap_groups ? 1 : 0;
         plan[kPlanFlag] = flag;
     }
     __syncthreads();
@@ -629,8 +627,9 @@ __global__ __launch_bounds__(kMidThreads) void ppr_mid_kernel(MidArgs a) {
     for (int it = 1; it < T; ++it) {
         // One loop over the wave's groups, slot ends found by count; entries travel
         // R groups ahead of their use and the Y values one group ahead of theirs.
-        // Groups past the last one (up to R - 1) read zeros from the stream and
-        // end up nowhere.
+        // Groups past the last one (up to 2 R of entries, R of sums) are zeros and end
+        // up nowhere: a load's group stands in its vector offset, which the buffer's
+        // end bounds (a scalar offset is not checked against it).
         constexpr int R = kMidAhead;
         // Registers: a plain tile of up to two columns reads a group's four Y
         // values (last first, so that one wait covers them) before it adds the
@@ -641,12 +640,10 @@ __global__ __launch_bounds__(kMidThreads) void ppr_mid_kernel(MidArgs a) {
         u4v r[RW];
         MidY<C> y[PAIRS ? 1 : 2][4];
         auto load_q = [&](int base, int j) {
-            return __builtin_amdgcn_raw_buffer_load_b64(sbuf, lane * 8 + j * (kMidGroup * 2), base * (kMidGroup * 2),
-                                                        0);
+            return __builtin_amdgcn_raw_buffer_load_b64(sbuf, lane * 8 + (base + j) * (kMidGroup * 2), 0, 0);
         };
         auto load_r = [&](int base, int j) {
-            return __builtin_amdgcn_raw_buffer_load_b128(wbuf, lane * 16 + j * (kMidGroup * 4),
-                                                         base * (kMidGroup * 4), 0);
+            return __builtin_amdgcn_raw_buffer_load_b128(wbuf, lane * 16 + (base + j) * (kMidGroup * 4), 0, 0);
         };
         auto read_hi = [&](const u2v& e, MidY<C>(&d)[4]) {
             d[3] = mid_read<C>(L, e.y >> 16);

@@ -455,7 +455,7 @@ static __global__ __launch_bounds__(1024) void query_refuse_kernel(const RowEnt*
             for (int64_t a = 0; a < deg_sorted[h]; a += D) row(min(D, (int64_t)deg_sorted[h] - a));
         for (int i = H; i < n; ++i) row(deg_sorted[i]);
         if (in > 0) groups += (width + 3) / 4;
-        over = groups + kMidPrefetch > cap_groups;
+        over = groups > cap_groups;
     }
     *refuse = over ? 1 : 0;
 }
