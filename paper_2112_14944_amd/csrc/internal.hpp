@@ -128,6 +128,13 @@ void ppr_ws_layout(Cursor& c, int n, int64_t nnz, bool weighted, int n_src, PprW
     if (w) *w = t;
 }
 
+// Scratch memory of ppr_matrix_noalloc (noalloc.hip): kScratchBytes for the
+// workspace proper, then room for the buffers of the faster routes (as much as
+// the all-pairs series of the resident range's largest size needs).
+constexpr size_t kScratchBytes = size_t(8) << 20;
+constexpr size_t kScratchExtraBytes = size_t(4) * Res<16>::NMAX * Res<16>::NMAX * sizeof(float);
+ppr_status scratch_address(hipStream_t s, void** out);
+
 ppr_status validate_csr(const ppr_csr* g);
 bool use_resident(int n);
 void launch_degree(const int32_t* row_ptr, const float* weight, int64_t n, float* deg, float* invd,

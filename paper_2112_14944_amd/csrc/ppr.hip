@@ -3,7 +3,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <mutex>
 
 #include "internal.hpp"
 #include "ppr_core.hpp"
@@ -646,46 +645,6 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
     }
 }
 
-
-// Scratch memory of ppr_matrix_noalloc: a fixed device array, one copy per
-// GPU, that replaces the caller's workspace for callers that cannot allocate
-// (graph capture, tight serving loops): kScratchBytes for the workspace
-// proper, then room for the buffers of the faster routes (the all-pairs series
-// of the resident range's largest size needs the most of those a graph whose
-// workspace fits can take).  Host code never passes the array's
-// name to a kernel: scratch_address resolves it once per device, with that
-// device current, and keeps the device address.
-constexpr size_t kScratchBytes = size_t(8) << 20;
-constexpr size_t kScratchExtraBytes = size_t(4) * Res<16>::NMAX * Res<16>::NMAX * sizeof(float);
-static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchExtraBytes];
-constexpr int kMaxDevices = 64;
-
-static ppr_status scratch_address(hipStream_t s, void** out) {
-    static std::mutex mu;
-    static void* addr[kMaxDevices] = {};
-    int dev = 0;
-    if (s != nullptr) {
-        hipDevice_t d = 0;
-        PPRVIZ_HIP_TRY(hipStreamGetDevice(s, &d));
-        dev = (int)d;
-    } else {
-        PPRVIZ_HIP_TRY(hipGetDevice(&dev));
-    }
-    if (dev < 0 || dev >= kMaxDevices) return PPR_EUNSUPPORTED;
-    std::lock_guard<std::mutex> lock(mu);
-    if (addr[dev] == nullptr) {
-        int cur = 0;
-        PPRVIZ_HIP_TRY(hipGetDevice(&cur));
-        if (cur != dev) PPRVIZ_HIP_TRY(hipSetDevice(dev));
-        void* p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (cur != dev) PPRVIZ_HIP_TRY(hipSetDevice(cur));
-        if (e != hipSuccess || p == nullptr) return PPR_EHIP;
-        addr[dev] = p;
-    }
-    *out = addr[dev];
-    return PPR_OK;
-}
 
 // ppr_matrix with the workspace given (the caller's, or this GPU's scratch).
 static ppr_status ppr_matrix_impl(const ppr_csr* g, const int32_t* src, int32_t n_src, const int32_t* tgt,

@@ -58,3 +58,49 @@ def test_noalloc_rejects_oversized_workspace(ops):
     with pytest.raises(L.PprvizError) as ei:
         ops.ppr_matrix_noalloc(csr, np.arange(g.n), ppr=torch.empty((g.n, g.n), device="cuda"))
     assert ei.value.status == L.PPR_EUNSUPPORTED
+
+
+# Run in a process of its own: the first uses of the library there.
+_FIRST_USE = """
+import numpy as np, torch, synth
+from gpu_util import get_ops
+ops = get_ops()
+g = synth.erdos_renyi(300, 8, 1)
+csr = ops.Csr.from_graph(g, "cuda")
+src = torch.arange(g.n, dtype=torch.int32, device="cuda")
+out = torch.zeros((g.n, g.n), device="cuda")
+spare = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+del spare  # stays with the allocator for the calls below
+torch.cuda.synchronize()
+free = lambda: torch.cuda.mem_get_info()[0]
+before = free()
+want = ops.ppr_matrix(csr, src)[0]
+torch.cuda.synchronize()
+held = before - free()
+s = torch.cuda.Stream()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph, stream=s):  # the first call that needs the array is a captured one
+    ops.ppr_matrix_noalloc(csr, src, ppr=out)
+for _ in range(3):
+    out.zero_()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+print("HELD", held)
+"""
+
+
+def test_noalloc_array_is_held_by_its_callers_only():
+    # The array (93 MB) comes with the first call that uses it, which may be a
+    # captured one; code alone is a few MB.
+    import os
+    import subprocess
+    import sys
+    here = os.path.dirname(os.path.abspath(__file__))
+    env = dict(os.environ, PYTHONPATH=os.pathsep.join([os.path.dirname(here), here]))
+    r = subprocess.run([sys.executable, "-c", _FIRST_USE], capture_output=True, text=True, timeout=100, env=env)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+    words = r.stdout.split()
+    held = int(words[words.index("HELD") + 1])
+    print(f"[memory] ppr_matrix holds {held / 1e6:.1f} MB", flush=True)
+    assert held < 50e6
