@@ -134,17 +134,18 @@ ppr_status ppr_matrix(const ppr_csr* g, const int32_t* src, int32_t n_src,
 /*
  * ppr_matrix for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same computation, kernels and results as ppr_matrix with the workspace of
- * ppr_matrix_workspace_fast(), taken from a fixed scratch array inside the library instead of a caller
- * buffer.  Inputs and outputs are still the caller's.  The call allocates
- * nothing (no hipMalloc/hipFree, no allocating library routine).
+ * same computation as ppr_matrix, with the workspace taken from a fixed scratch
+ * array inside the library instead of a caller buffer; the same kernels and bits
+ * as with the workspace of ppr_matrix_workspace_fast() wherever what that adds
+ * fits the array's room for it (85 MB), else a route that needs less.  Inputs
+ * and outputs are still the caller's.  The call allocates nothing (no
+ * hipMalloc/hipFree, no allocating library routine).
  *
  * Limit: the workspace ppr_matrix_workspace(g, n_src, n_tgt) would ask for
  * must fit ppr_matrix_noalloc_max_scratch() bytes (8 MiB), else the call
  * returns PPR_EUNSUPPORTED before any launch.  That covers, for example, the
  * LDS-resident path (n <= 2304) up to about 1 million arcs unweighted.  What
- * ppr_matrix_workspace_fast() adds has room of its own (85 MB) and does not
- * count.
+ * ppr_matrix_workspace_fast() adds does not count.
  *
  * The scratch is one array per GPU, held from the first call on that GPU
  * until the process ends (its device address is looked up once per device).

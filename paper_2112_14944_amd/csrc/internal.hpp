@@ -74,15 +74,18 @@ void ppr_extra_layout(Cursor& c, int n, int n_src, bool same, PprWs* w) {
         w->query = q;
     }
 }
-// The extra buffers where the workspace has room for them.
+// The extra buffers where the workspace has room for them: all, those without the
+// product that halves the pushes, or none.
 inline void ppr_extra_take(WsCursor& c, int n, int n_src, bool same, PprWs* w) {
-    WsCursor t = c;
-    ppr_extra_layout(t, n, n_src, same, w);
-    if (t.used <= t.cap) {
-        c = t;
-    } else {
-        ppr_extra_layout(c, n, 0, false, w);  // none of them
+    for (const bool product : {same, false}) {
+        WsCursor t = c;
+        ppr_extra_layout(t, n, n_src, product, w);
+        if (t.used <= t.cap) {
+            c = t;
+            return;
+        }
     }
+    ppr_extra_layout(c, n, 0, false, w);
 }
 
 template <typename Cursor>
@@ -129,8 +132,10 @@ void ppr_ws_layout(Cursor& c, int n, int64_t nnz, bool weighted, int n_src, PprW
 }
 
 // Scratch memory of ppr_matrix_noalloc (noalloc.hip): kScratchBytes for the
-// workspace proper, then room for the buffers of the faster routes (as much as
-// the all-pairs series of the resident range's largest size needs).
+// workspace proper, then room for the buffers of the faster routes.  It fits the
+// all-pairs series of the resident range's largest size; a query that needs more
+// (a few sources of a nearly edgeless graph of 30000 nodes and up) goes without
+// the product, or takes a general route.
 constexpr size_t kScratchBytes = size_t(8) << 20;
 constexpr size_t kScratchExtraBytes = size_t(4) * Res<16>::NMAX * Res<16>::NMAX * sizeof(float);
 ppr_status scratch_address(hipStream_t s, void** out);

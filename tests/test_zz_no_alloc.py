@@ -104,3 +104,24 @@ def test_noalloc_array_is_held_by_its_callers_only():
     held = int(words[words.index("HELD") + 1])
     print(f"[memory] ppr_matrix holds {held / 1e6:.1f} MB", flush=True)
     assert held < 50e6
+
+
+# The iterates of 250 sources of 32000 and 39000 nodes, 65 and 80 MB, fit the
+# array's room for the faster routes' buffers, the product's pieces do not as well;
+# of 3000 nodes all of them fit.
+@pytest.mark.parametrize("n,arcs,k", [(32000, 2000, 250), (39000, 2000, 250), (3000, 40000, 64)])
+def test_noalloc_query_among_its_sources(ops, n, arcs, k):
+    from paper_2112_14944_amd import _lib as L
+    rng = np.random.default_rng(n)
+    g = synth.build_graph(n, rng.integers(0, n, arcs // 2), rng.integers(0, n, arcs // 2))
+    csr = ops.Csr.from_graph(g, "cuda")
+    src = torch.as_tensor(np.sort(rng.choice(n, k, replace=False)).astype(np.int32), device="cuda")
+    cg = csr.c()
+    assert L.lib().ppr_matrix_workspace(C.byref(cg), k, k) <= L.lib().ppr_matrix_noalloc_max_scratch()
+    print(f"[noalloc] n={n} nnz={g.nnz} {k} sources", flush=True)
+    want = ops.ppr_matrix(csr, src, tgt=src)[1].double()
+    got = torch.full((k, k), float("nan"), device="cuda")
+    ops.ppr_matrix_noalloc(csr, src, tgt=src, dppr=got)
+    # the same T pushes, halved or not: each value rounded about T = 86 times by
+    # 2^-24 at random
+    assert ((got.double() - want).norm() / want.norm()).item() <= 1e-6
