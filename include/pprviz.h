@@ -92,8 +92,9 @@ size_t ppr_matrix_workspace(const ppr_csr* g, int32_t n_src, int32_t n_tgt);
  *    the push series is cut into a shorter one and dense products;
  *  - up to 256 sources of a graph of n <= 40831 nodes: the iterate in HBM
  *    (about 8 n n_src bytes), each push over the whole GPU;
- *  - n_tgt == n_src, for calls whose tgt is the src array itself: the buffers
- *    of a product of about n_src^2 entries that halves the pushes.
+ *  - n_tgt == n_src, for calls whose tgt is the src array itself (others of as
+ *    many targets ask with n_tgt = 0): the buffers of a product of about n_src^2
+ *    entries that halves the pushes.
  * Each is taken where it is faster; pushes are replaced by products only at an
  * alpha of at least 0.1 (all pairs: to 0.4).  The routes agree to FP32 rounding; with a
  * smaller workspace (at least ppr_matrix_workspace()) a call takes a general

@@ -34,6 +34,15 @@ def _ws(nbytes, device):
     return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
 
 
+def _ws_fast(fast, need, device):
+    """A workspace with the faster routes' buffers, or, where the device has no
+    room for them, the one that the call needs."""
+    try:
+        return _ws(fast, device)
+    except torch.OutOfMemoryError:
+        return _ws(need, device)
+
+
 @dataclass
 class Csr:
     """Symmetric CSR on the device (int32 row_ptr/col_idx, optional FP32
@@ -82,7 +91,8 @@ def ppr_matrix(g: Csr, src, tgt=None, alpha=0.15, tol=1e-6, max_iter=100000, wan
     else:
         n_tgt = g.n
     cg = g.c()
-    ws = _ws(L.lib().ppr_matrix_workspace_fast(C.byref(cg), n_src, n_tgt), dev)
+    ws = _ws_fast(L.lib().ppr_matrix_workspace_fast(C.byref(cg), n_src, n_tgt if among else 0),
+                  L.lib().ppr_matrix_workspace(C.byref(cg), n_src, n_tgt), dev)
     ppr = torch.empty((n_src, n_tgt), dtype=torch.float32, device=dev) if want_ppr else None
     dppr = torch.empty((n_src, n_tgt), dtype=torch.float32, device=dev) if want_dppr else None
     resid = np.zeros(max(n_src, 1), dtype=np.float64) if check_residual else None
@@ -351,13 +361,14 @@ class Batch:
     def buffers(self, x0):
         dev = self.device
         cb = self.c()
+        ws = L.lib().pprviz_batch_workspace(C.byref(cb))
         return dict(
             x0=x0.contiguous(),
             x_out=torch.empty_like(x0),
             dppr=torch.empty(self.pool, dtype=torch.float32, device=dev),
             delta=torch.empty(self.pool, dtype=torch.float32, device=dev),
             stress=torch.empty(self.n_graphs, dtype=torch.float64, device=dev),
-            ws=_ws(L.lib().pprviz_batch_workspace(C.byref(cb)), dev),
+            ws=_ws_fast(ws, ws - 4 * self.pool if self.max_n >= 192 else ws, dev),  # without the products' pool
         )
 
 

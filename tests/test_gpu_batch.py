@@ -206,3 +206,55 @@ def test_batch_all_pushes():
         assert g.n >= 192 or torch.equal(a, c)
         # PDist of the pushes' DPPR, clamped at n
         assert torch.equal(ops.graph_block(gb, small["delta"], gi), ops.pdist(c.contiguous(), g.n))
+
+
+def test_no_room_for_the_faster_routes(monkeypatch):
+    # a device without room for the faster routes' buffers still gets the workspace
+    # that the calls need
+    ops = get_ops()
+    from paper_2112_14944_amd import _lib as L
+    g = synth.sbm(synth.equal_blocks(700, 4), 0.1, 0.02, 6600)
+    gb = synth.concat_graphs([g])
+    b = ops.Batch(gb, "cuda")
+    csr = ops.Csr.from_graph(g, "cuda")
+    x0 = torch.as_tensor(synth.uniform_layout(g.n, 14), device="cuda")
+    src = np.arange(g.n)
+    full = ops.pprviz_batch(b, b.buffers(x0), tol=1e-6, stress_iters=0)["dppr"].clone()
+    cg, cb = csr.c(), b.c()
+    import ctypes as C
+    room = max(L.lib().ppr_matrix_workspace(C.byref(cg), g.n, g.n),
+               L.lib().pprviz_batch_workspace(C.byref(cb)) - 4 * b.pool)
+    assert room < min(L.lib().ppr_matrix_workspace_fast(C.byref(cg), g.n, g.n),
+                      L.lib().pprviz_batch_workspace(C.byref(cb)))
+    plain = ops._ws
+
+    def little(nbytes, device):
+        if nbytes > room:
+            raise torch.OutOfMemoryError("no room")
+        return plain(nbytes, device)
+
+    monkeypatch.setattr(ops, "_ws", little)
+    print(f"[no room] n={g.n} nnz={g.nnz}", flush=True)
+    got = ops.pprviz_batch(b, b.buffers(x0), tol=1e-6, stress_iters=0)["dppr"]
+    one = ops.ppr_matrix(csr, src, tol=1e-6, want_ppr=False)[1]
+    torch.cuda.synchronize()
+    assert torch.equal(ops.graph_block(gb, got, 0), one)  # the same pushes
+    assert ((one.flatten() - full).norm() / full.norm()).item() <= 1e-6  # the routes' bar
+
+
+def test_workspace_of_other_targets():
+    # as many targets as sources, but not the sources: no buffers for their product
+    ops = get_ops()
+    from paper_2112_14944_amd import _lib as L
+    import ctypes as C
+    g = synth.chung_lu(42000, 2.4, 8, 6700)
+    csr = ops.Csr.from_graph(g, "cuda")
+    cg = csr.c()
+    asked = []
+    plain = ops._ws
+    ops._ws = lambda nbytes, device: (asked.append(nbytes), plain(nbytes, device))[1]
+    try:
+        ops.ppr_matrix(csr, np.arange(600), tgt=np.arange(600, 1200), tol=1e-2)
+    finally:
+        ops._ws = plain
+    assert asked == [L.lib().ppr_matrix_workspace(C.byref(cg), 600, 600)]
