@@ -609,11 +609,10 @@ void ppr_forward(const ppr_csr* g, const int32_t* src, int32_t n_src, const int3
     const int n = g->n;
     // The iterate in HBM: always for graphs that do not fit LDS, else for few
     // sources where it is faster.  The targets being the sources halves the
-    // pushes where the product costs less than the pushes it saves (60
-    // TFLOP/s against 7 TB/s of gathers); a residual needs every node.
+    // pushes where that is faster (query_halves); a residual needs every node.
     QueryWs q = w.query;
-    const bool halve = q.gram != nullptr && alpha >= kDenseMinAlpha && tgt == src && n_tgt == n_src && resid == nullptr && T >= kQueryMinT &&
-                       (double)n * n_src / 60e12 < 0.5 * T * (double)g->nnz * 4 / 7e12;
+    const bool halve = q.gram != nullptr && alpha >= kDenseMinAlpha && tgt == src && n_tgt == n_src &&
+                       resid == nullptr && query_halves(n, g->nnz, n_src, T);
     if (!halve) q.gram = nullptr;
     const bool lds = use_resident(n) || mid_cols_for(n) != 0;
     if (!lds || (q.ya != nullptr && query_faster(n, g->nnz, n_src, T, halve))) {

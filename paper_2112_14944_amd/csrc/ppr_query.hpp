@@ -494,7 +494,8 @@ struct QueryWs {
     int32_t pieces;
 };
 
-// Pieces of the product's rows: about 1024 blocks in all, at least 256 rows each.
+// Pieces of the product's rows: about 1024 blocks in all, which the 256 CUs hold at
+// once (1088 instead of 952 blocks take half as long again), at least 256 rows each.
 inline int query_pieces(int n, int k) {
     const int64_t nt = (k + 63) / 64;
     const int64_t tiles = nt * (nt + 1) / 2;
@@ -502,6 +503,17 @@ inline int query_pieces(int n, int k) {
     return (int)std::min(most, std::max<int64_t>(1, 1024 / tiles));
 }
 inline size_t query_gram_floats(int n, int k) { return (size_t)query_pieces(n, k) * k * k; }
+
+// Whether the product costs less than the pushes it saves, a push at 9 TB/s of
+// gathered values (7.2 to 10), the product at 15 TFLOP/s of n k^2 (13 at 64 sources,
+// 26 to 30 at 256, 1000 and 4000, 15 to 17 at 2000, whose 528 tiles are two or three
+// to a CU).  Measured, n = 200000, all pushes and halved: 8 arcs per node, T = 8, 64
+// sources 0.48 and 0.35 ms, 1000 sources 6.3 and 10.5; 24 arcs per node, T = 20, 1000
+// sources 36.8 and 26.3 ms, 2000 sources 72 and 85; T = 86, 4000 sources 641 and 432.
+inline bool query_halves(int n, int64_t nnz, int n_src, int T) {
+    return T >= kQueryMinT &&
+           (double)n * n_src / 15e12 < (double)(T - 1 - T / 2) * (double)nnz * 4 / 9e12;
+}
 
 // Whether a query on a graph that fits LDS is faster here, by the time of
 // either route in microseconds.  Measured: a push here 5.5 us and 3.2e-7 us per

@@ -238,7 +238,7 @@ def _query(ops, csr, src, tgt, T, alpha, fast):
 # half of the mass and sums over 200000 rows in few pieces.
 def test_many_sources_short_series():
     ops = get_ops()
-    n, k, T = 200000, 500, 8
+    n, k, T = 200000, 400, 8
     g = synth.chung_lu(n, 2.4, 24, 91)
     rng = np.random.default_rng(92)
     src = torch.as_tensor(np.sort(rng.choice(np.nonzero(np.diff(g.row_ptr))[0], k, replace=False)).astype(np.int32),
@@ -256,6 +256,7 @@ def test_many_sources_short_series():
     # what is left are four pushes of one, and of the other a product whose FP32
     # sums have at most 128 terms (64 additions, sqrt(64 / 3) / 2 u of half the
     # mass) and a difference of two iterates: 6 u apart.
+    assert not torch.equal(half, full)  # the halved route was taken
     assert rel(full, want) <= T * 2.0 ** -24
     assert rel(half, want) <= T * 2.0 ** -24
     assert rel(half, full) <= 6 * 2.0 ** -24
@@ -363,3 +364,22 @@ def test_other_alphas(alpha, T):
         bufs = ops.pprviz_batch(b, b.buffers(torch.zeros((g.n, 2), device="cuda")), alpha=alpha, tol=0.0, max_iter=T,
                                 stress_iters=0)
         assert torch.equal(ops.graph_block(gb, bufs["dppr"], 0), _query(ops, csr, src, None, T, alpha, False)[1])
+
+
+# Either side of the rule that halves a query's pushes: the product of k sources
+# costs n k^2, the pushes it saves as much as their arcs and k.
+@pytest.mark.parametrize("k,T,halved", [(120, 8, True), (250, 8, False), (400, 20, True), (600, 20, False)])
+def test_few_sources_halved_where_faster(k, T, halved):
+    ops = get_ops()
+    n = 42000
+    g = synth.chung_lu(n, 2.4, 8, 95)
+    # 15 TFLOP/s against 9 TB/s of 4-byte values
+    assert halved == (n * k / 15e12 < (T - 1 - T // 2) * g.nnz * 4 / 9e12)
+    csr = ops.Csr.from_graph(g, "cuda")
+    live = np.nonzero(np.diff(g.row_ptr))[0]
+    src = torch.as_tensor(np.sort(np.random.default_rng(96).choice(live, k, replace=False)).astype(np.int32),
+                          device="cuda")
+    print(f"[halved] nnz={g.nnz} sources={k} T={T} {halved}", flush=True)
+    fast, slow = _query(ops, csr, src, src, T, ALPHA, True)[0], _query(ops, csr, src, src, T, ALPHA, False)[0]
+    assert torch.equal(fast, slow) != halved
+    assert ((fast - slow).norm() / slow.norm()).item() <= 1e-6  # the routes' bar
