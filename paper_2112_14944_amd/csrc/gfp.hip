@@ -49,16 +49,21 @@ namespace pprviz {
 namespace {
 
 constexpr int kGfpChunk = 2048;  // leaves per block of the aggregation
-constexpr int kGfpInfo = 4;      // [0] bad leaf lists, [1] largest leaf set, [2] wide rows
+// [0] bad leaf lists, [1] largest leaf set, rows over [2] kGfpWideDeg, [3] kGfpWideDegSmall arcs
+constexpr int kGfpInfo = 4;
 // Rows with more arcs than this are gathered by a whole wave (8 lane groups
 // on one row) instead of one 8-lane group: the longest row then takes 64
 // arcs per pass instead of 8, which keeps it from outlasting the rest of a
-// round.  On a grid that is resident at once a round lasts as long as its
-// longest row, 8 arcs per load latency, and the limit is lower (20000 nodes,
-// 4e5 arcs: 26.5 us per round at 256 arcs, 12 us at 32); on larger grids
-// whole waves on short rows would leave lanes idle.
+// round.  On a small grid a round lasts as long as its longest row, 8 arcs per
+// load latency, and the limit is lower, as long as the grid it gives has at most
+// kGfpSmallBlocks blocks; on larger grids whole waves on short rows leave lanes
+// idle.  20000 nodes, 4e5 arcs, 256 and 32 arcs: 26.5 and 12 us per round.  Whole
+// calls at 32 arcs over those at 256: 70000 nodes, 30 arcs per node (5300 blocks)
+// 0.89; 100000 nodes, 30 (7500) 0.95; 230000 nodes, 12 (9700) 0.9; 255000 nodes, 30
+// (19500) 1.05; 262000 nodes, 30 (20000) 1.09.
 constexpr int kGfpWideDeg = 256;
 constexpr int kGfpWideDegSmall = 32;
+constexpr int64_t kGfpSmallBlocks = 11264;
 static_assert(kGfpWideDeg + 2 <= kDegKeys, "wide rows must have degree classes of their own");
 // A block whose pushing rows hold more arcs than this, or more than half of
 // the block's arcs, in a round is over the mark cap: it writes no receive
@@ -68,10 +73,12 @@ constexpr int kGfpMarkArcs = 2048;
 // own row's arcs 256 at a time).
 constexpr int kGfpMarkArcsWide = 8192;
 // Rounds write and use receive marks only when their grid holds more than
-// this many blocks (4 x the 2048 blocks of 256 threads that 256 CUs keep
-// resident): a round whose blocks all fit at once is bound by one block's
-// latency, which the marks lengthen, and its flag scan is short anyway.
-constexpr int64_t kGfpMarkMinBlocks = 8192;
+// this many blocks (256 CUs keep 2048 of 256 threads resident): a round whose
+// blocks all fit at once is bound by one block's latency, which the marks
+// lengthen, and its flag scan is short anyway.  Whole calls with marks from 8192
+// blocks on over those with marks from here: 130000 nodes, 12 arcs per node (5500
+// blocks) 1.1; 255000 nodes, 12 (8200 at 256 arcs) 1.2.
+constexpr int64_t kGfpMarkMinBlocks = 4608;
 
 struct GfpWs {
     RowEnt* rows;
@@ -159,12 +166,12 @@ __global__ void gfp_check_idx_kernel(const int32_t* __restrict__ leaf_idx, int64
     }
 }
 
-// Rows with more than wide_deg arcs: after the scatter of the degree order,
+// Rows with more arcs than either limit: after the scatter of the degree order,
 // hist[c] is the end of class c (classes run from the largest degree down), so
-// the end of the class of degree wide_deg + 1 counts them.
-__global__ void gfp_wide_count_kernel(const int32_t* __restrict__ hist, int32_t wide_deg,
-                                      int32_t* __restrict__ info) {
-    info[2] = hist[kDegKeys - 2 - wide_deg];
+// the end of the class of a limit plus 1 counts them.
+__global__ void gfp_wide_count_kernel(const int32_t* __restrict__ hist, int32_t* __restrict__ info) {
+    info[2] = hist[kDegKeys - 2 - kGfpWideDeg];
+    info[3] = hist[kDegKeys - 2 - kGfpWideDegSmall];
 }
 
 // Initial residues of column c, supernode i = col_set[c] (c itself when
@@ -671,7 +678,7 @@ ppr_status gfp_validate(const GfpArgs& A, size_t ws_bytes, void* ws, GfpWs* w) {
 
 // Checks the leaf lists (and the backward targets, when given), builds the
 // degrees and the degree row order, and reads back the check results, the
-// largest leaf set and the count of wide rows.  Nothing else is enqueued.
+// largest leaf set and the counts of wide rows.  Nothing else is enqueued.
 ppr_status gfp_prepare(const GfpArgs& A, const GfpWs& w, const int32_t* targets, const float* rb_max,
                        int32_t n_targets, int32_t info[kGfpInfo], hipStream_t s) {
     const int32_t n = A.g->n;
@@ -685,12 +692,11 @@ ppr_status gfp_prepare(const GfpArgs& A, const GfpWs& w, const int32_t* targets,
         hipLaunchKernelGGL(gbp_columns_kernel, dim3((unsigned)((n_targets + 255) / 256)), dim3(256), 0, s, targets,
                            rb_max, n_targets, A.k, w.col_set, w.th_col, w.info);
     }
-    // Row order by degree; the wide rows come first, and their count is read back with the check results.
+    // Row order by degree; the wide rows come first, and their counts are read back
+    // with the check results.
     launch_degree(A.g->row_ptr, A.g->weight, n, w.deg, w.invd, s);
     stream_row_order(A.g->row_ptr, n, w.hist, w.rows, s);
-    const bool small = (int64_t)n / kStreamRowsPerBlock * (gfp_ld(A.k) / kSlab) <= kGfpMarkMinBlocks;
-    hipLaunchKernelGGL(gfp_wide_count_kernel, dim3(1), dim3(1), 0, s, w.hist,
-                       small ? kGfpWideDegSmall : kGfpWideDeg, w.info);
+    hipLaunchKernelGGL(gfp_wide_count_kernel, dim3(1), dim3(1), 0, s, w.hist, w.info);
     ppr_status st = launch_status();
     if (st != PPR_OK) return st;
     if ((st = read_i32(w.info, info, kGfpInfo, s)) != PPR_OK) return st;
@@ -708,12 +714,14 @@ ppr_status gfp_run(const GfpArgs& A, const GfpWs& w, const int32_t info[kGfpInfo
     const int32_t n = A.g->n;
     const int32_t k = A.k;
     const int64_t ld = gfp_ld(ncols);
-    const int32_t wide = info[2];
+    const StreamGrid fine = gfp_grid(n, info[3], ld);
+    const bool small = (int64_t)fine.row_blocks * fine.slabs <= kGfpSmallBlocks;
+    const int32_t wide = small ? info[3] : info[2];
     ppr_status st;
     fill<float>(w.resid, 0.f, n * ld, s);
     fill<float>(w.est, 0.f, n * ld, s);
     fill<int32_t>(w.active, 0, A.max_rounds, s);
-    const StreamGrid grid = gfp_grid(n, wide, ld);
+    const StreamGrid grid = small ? fine : gfp_grid(n, wide, ld);
     const bool marks = (int64_t)grid.row_blocks * grid.slabs > kGfpMarkMinBlocks;
     if (marks) {
         fill<int32_t>(w.over, 0, A.max_rounds, s);

@@ -479,3 +479,34 @@ def test_receive_marks_keep_residue_and_stopping_rule(ops):
         assert np.abs(mass - want_mass).max() <= 1e-5 * want_mass.max(), rounds
         agg = np.stack([E[:, F].sum(axis=1) / len(F) for F in leaves], axis=1)
         assert np.abs(out.double().cpu().numpy() - agg).max() <= 1e-6 * np.abs(agg).max()
+
+
+@pytest.mark.parametrize("n", [2000, 362000])
+def test_rows_around_the_whole_wave_limits(ops, n):
+    # rows from 33 arcs on take a whole wave on small grids, from 257 on on large
+    # ones (362000 nodes: more than 11264 blocks of 32 rows): rows of as many arcs
+    # as either limit and one less and more, on a ring, a few rounds of every push
+    want = [31, 32, 33, 34, 64, 65, 255, 256, 257, 300]
+    rng = np.random.default_rng(n)
+    pick = rng.permutation(np.arange(20, n - 1))
+    eu, ev, at = [np.arange(n)], [(np.arange(n) + 1) % n], 0
+    for i, m in enumerate(want):  # node i: the ring's two arcs and m - 2 of its own
+        hub = 2 * i
+        other = pick[at:at + m - 2] if n > 5000 else rng.choice(np.arange(40, n - 1), m - 2, replace=False)
+        at += m - 2
+        eu.append(np.full(m - 2, hub))
+        ev.append(other)
+    g = synth.build_graph(n, np.concatenate(eu), np.concatenate(ev))
+    assert [int(np.diff(g.row_ptr)[2 * i]) for i in range(len(want))] == want
+    leaves = [np.array([0, 2, 4]), np.array([12]), np.array([14, 16, 18, 6]), np.arange(0, n, max(1, n // 50))]
+    W = O.weight_matrix(g.n, g.eu, g.ev, g.weight)
+    csr = ops.Csr.from_graph(g, "cuda")
+    for T in (1, 3, 6):
+        print(f"[gfp limits] n={n} T={T}", flush=True)
+        out, est, resid, rounds, _ = ops.gfp_level_dppr(csr, leaves, ALPHA, 0.0, T, want_est=True, want_resid=True,
+                                                         allow_noconv=True)
+        assert rounds == T
+        e_o, R_o, ne_o, _, _ = O.group_forward_push_rounds(W, leaves, ALPHA, 0.0, T)
+        _within_rel(np.abs(out.double().cpu().numpy() - e_o).max(), np.abs(e_o).max())
+        _within_rel(np.abs(est.double().cpu().numpy() - ne_o).max(), np.abs(ne_o).max())
+        _within_rel(np.abs(resid.double().cpu().numpy() - R_o).max(), np.abs(R_o).max())
