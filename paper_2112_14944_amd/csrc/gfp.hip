@@ -64,6 +64,7 @@ constexpr int kGfpInfo = 4;
 constexpr int kGfpWideDeg = 256;
 constexpr int kGfpWideDegSmall = 32;
 constexpr int64_t kGfpSmallBlocks = 11264;
+constexpr int64_t kGfpResidentBlocks = 2048;  // 256 CUs, 8 blocks of 256 threads each
 static_assert(kGfpWideDeg + 2 <= kDegKeys, "wide rows must have degree classes of their own");
 // A block whose pushing rows hold more arcs than this, or more than half of
 // the block's arcs, in a round is over the mark cap: it writes no receive
@@ -763,10 +764,14 @@ ppr_status gfp_run(const GfpArgs& A, const GfpWs& w, const int32_t info[kGfpInfo
     // Rounds 1 .. max_rounds - 1 in growing batches; after each batch the
     // host reads which rounds pushed and stops when one did not.  A read leaves
     // the GPU idle for 40-80 us, a round launched past the end returns at once
-    // (4 us at 20000 nodes, 8 us at 10^6).
-    constexpr int32_t kFirst = 16, kSecond = 24, kMost = 64;
+    // (4 us at 20000 nodes, 8 us at 10^6), so the first batch is short: runs of 2
+    // to 5 rounds take 5 to 14% more time with one of 16.  Grids that are resident
+    // at once, whose rounds are cheapest, get the next one to 40 rounds.
+    constexpr int32_t kMost = 64;
+    const bool resident = (int64_t)grid.row_blocks * grid.slabs <= kGfpResidentBlocks;
+    const int32_t first = resident ? 12 : 8;
     bool capped = false;
-    int32_t seen = 0, launched = 1, batch = kFirst - 1, rounds = 0;
+    int32_t seen = 0, launched = 1, batch = first - 1, rounds = 0;
     while (true) {
         const int32_t end = std::min(A.max_rounds, launched + batch);
         for (int32_t t = launched; t < end; ++t) {
@@ -790,7 +795,7 @@ ppr_status gfp_run(const GfpArgs& A, const GfpWs& w, const int32_t info[kGfpInfo
         if (!capped) ++rounds;
         if (!capped || launched == A.max_rounds) break;
         seen = launched;
-        batch = launched == kFirst ? kSecond : (launched < 128 ? kFirst : kMost);
+        batch = launched == first && resident ? 40 - first : (launched < 128 ? 16 : kMost);
     }
     if (capped) {
         // deliver what the last round sent, so that the residues and the

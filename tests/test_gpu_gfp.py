@@ -510,3 +510,28 @@ def test_rows_around_the_whole_wave_limits(ops, n):
         _within_rel(np.abs(out.double().cpu().numpy() - e_o).max(), np.abs(e_o).max())
         _within_rel(np.abs(est.double().cpu().numpy() - ne_o).max(), np.abs(ne_o).max())
         _within_rel(np.abs(resid.double().cpu().numpy() - R_o).max(), np.abs(R_o).max())
+
+
+@pytest.mark.parametrize("n", [3000, 80000])
+def test_rounds_where_the_stop_flags_are_read(ops, n):
+    # the push flags of several rounds are read at once (after 12 and 40 rounds on a
+    # small grid, 8 and 24 on larger ones): caps on either side of the reads, each the
+    # uncapped run's rounds so far, and the run that ends by itself
+    g = synth.chung_lu(n, 2.5, 12, synth.BASE_SEED + 77)
+    csr = ops.Csr.from_graph(g, "cuda")
+    leaves = [np.arange(i, n, 5) for i in range(5)]
+    r_max = 1e-9
+    full, _, _, rounds, st = ops.gfp_level_dppr(csr, leaves, ALPHA, r_max, 10000)
+    assert st == 0 and rounds > 42
+    d = O.degrees(O.weight_matrix(g.n, g.eu, g.ev, g.weight))
+    for cap in (1, 7, 8, 9, 11, 12, 13, 24, 25, 39, 40, 41, rounds - 1, rounds, rounds + 1):
+        print(f"[gfp reads] n={n} cap={cap} of {rounds}", flush=True)
+        out, est, resid, r, st = ops.gfp_level_dppr(csr, leaves, ALPHA, r_max, cap, want_est=True, want_resid=True,
+                                                     allow_noconv=True)
+        assert r == min(cap, rounds) and (st == 0) == (cap >= rounds)
+        if cap >= rounds:
+            assert torch.equal(out, full)
+        # residue and estimate keep the seeds' mass
+        mass = (est.double().sum(1) + resid.double().sum(1)).cpu().numpy()
+        mean = np.array([d[F].mean() for F in leaves])
+        assert np.abs(mass - mean).max() <= REL * mean.max()
