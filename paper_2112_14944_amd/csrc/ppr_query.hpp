@@ -516,24 +516,29 @@ inline bool query_halves(int n, int64_t nnz, int n_src, int T) {
 }
 
 // Whether a query on a graph that fits LDS is faster here, by the time of
-// either route in microseconds.  Measured: a push here 5.5 us and 3.2e-7 us per
-// arc and column held (20000 nodes, 4e5 arcs, 48 sources: 14 us; 39000, 7.8e5,
-// 200: 63 us); the resident tile, 16 columns per block in a graph by itself, 2.5
-// us per push and 1.1e-5 us per arc and column (n = 2048, 1.3e5 arcs: 23 us); the mid-size kernel 4.4e-5
-// us per arc (6.9e-5 with 1 or 4 columns per block), and its preparation,
-// which one-block kernels dominate, 0.07 us per node.  48 sources of 20000
-// nodes, T = 86: 2.97 ms there, 1.25 ms here, 0.71 ms with halved pushes.
+// either route in microseconds, fitted to both routes' times over 150 to 40000
+// nodes, degrees 3 to 50, 1 to 256 sources and 8, 30 and 86 pushes (nine in ten
+// within 15 % of the fit).  A push here takes 6 us, 2.3e-6 us per row and column
+// held and 2.2e-7 us per arc and column held.  There, the preparation grows with
+// nodes and arcs; a push of the resident tile, 16 columns per block in a graph by
+// itself, takes 1.1 us, 1.56e-3 us per row and 1.4e-4 us per arc, one of the
+// mid-size kernel 3.6 us and 2.6e-5 us per arc (7.9e-5 with 1 column per block).  48
+// sources of 20000 nodes, T = 86: 2.97 ms there, 1.25 ms here, 0.71 ms with halved
+// pushes; 256 sources of 15000 nodes, T = 86: 1.36 ms there and 1.56 here at 9e4
+// arcs, 3.64 and 4.06 at 6e5.
 inline bool query_faster(int n, int64_t nnz, int n_src, int T, bool halved) {
     if (n_src > kQueryMaxSrc || n_src >= n) return false;
+    const double rows = (double)n, arcs = (double)nnz;
     const double steps = halved ? T / 2 + 1 : T;
-    const double here = 60.0 + steps * (5.5 + 3.2e-7 * (double)nnz * (double)query_ld(n_src));
+    const double here =
+        (halved ? 85.0 : 50.0) + steps * (6.0 + (double)query_ld(n_src) * (2.3e-6 * rows + 2.2e-7 * arcs));
     double there;
     if (res_cols_for(n) != 0) {
-        there = 40.0 + 0.1 * n + T * (2.5 + 1.1e-5 * (double)nnz * 16);
+        there = 44.0 + 0.059 * rows + 2.1e-3 * arcs + T * (1.1 + 1.56e-3 * rows + 1.4e-4 * arcs);
     } else {
         const int C = mid_cols_for(n);
         const int rounds = ((n_src + C - 1) / C + 255) / 256;
-        there = 100.0 + 0.07 * n + T * rounds * (C == 2 ? 4.4e-5 : 6.9e-5) * (double)nnz;
+        there = 100.0 + 0.025 * rows + 2.6e-3 * arcs + T * rounds * (3.6 + (C == 1 ? 7.9e-5 : 2.6e-5) * arcs);
     }
     return here < there;
 }

@@ -383,3 +383,23 @@ def test_few_sources_halved_where_faster(k, T, halved):
     fast, slow = _query(ops, csr, src, src, T, ALPHA, True)[0], _query(ops, csr, src, src, T, ALPHA, False)[0]
     assert torch.equal(fast, slow) != halved
     assert ((fast - slow).norm() / slow.norm()).item() <= 1e-6  # the routes' bar
+
+
+# Either side of the rule between the LDS kernels and the iterate in HBM: a push of
+# the iterate costs for its rows as well as for their arcs, and a few pushes of a
+# small graph less than the product's launches.
+@pytest.mark.parametrize("n,degree,k,T,among,hbm",
+                         [(15000, 6, 256, 86, False, False), (15000, 6, 48, 86, False, True),
+                          (300, 6, 1, 8, True, False), (20000, 6, 48, 86, True, True)])
+def test_few_sources_route(n, degree, k, T, among, hbm):
+    ops = get_ops()
+    g = synth.erdos_renyi(n, degree, 97)
+    csr = ops.Csr.from_graph(g, "cuda")
+    live = np.nonzero(np.diff(g.row_ptr))[0]
+    src = torch.as_tensor(np.sort(np.random.default_rng(98).choice(live, k, replace=False)).astype(np.int32),
+                          device="cuda")
+    tgt = src if among else None
+    print(f"[route] n={n} nnz={g.nnz} sources={k} T={T} {hbm}", flush=True)
+    fast, slow = _query(ops, csr, src, tgt, T, ALPHA, True)[0], _query(ops, csr, src, tgt, T, ALPHA, False)[0]
+    assert torch.equal(fast, slow) != hbm
+    assert ((fast - slow).norm() / slow.norm()).item() <= 1e-6  # the routes' bar
