@@ -277,10 +277,13 @@ def layout_step(delta, x, with_stress=False, out=None, ws=None):
 def layout(delta, x0, steps):
     """`steps` Jacobi sweeps from x0 (one call into the library)."""
     k = _check_layout(delta, x0)
+    steps = operator.index(steps)
+    if k == 0 or steps <= 0:
+        return x0.clone()
     out = torch.empty_like(x0)
     ws = _ws(L.lib().layout_run_workspace(k), x0.device)
-    L.check("layout_run", L.lib().layout_run(_ptr(delta), k, _ptr(x0), _ptr(out), max(operator.index(steps), 0),
-                                              _ptr(ws), ws.numel(), _stream(x0.device)))
+    L.check("layout_run", L.lib().layout_run(_ptr(delta), k, _ptr(x0), _ptr(out), steps, _ptr(ws), ws.numel(),
+                                              _stream(x0.device)))
     return out
 
 

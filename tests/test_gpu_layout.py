@@ -145,3 +145,13 @@ def test_layout_run(ops, k):
         want = nxt
     # the package's bar of one step (1e-5 of the layout's scale) for the few steps
     assert (got.double() - want).abs().max().item() <= STEP_REL * want.abs().max().item()
+
+
+# no node, no sweep or a negative number of them: the start, as a new tensor
+@pytest.mark.parametrize("k,steps", [(0, 3), (0, 0), (5, 0), (5, -1)])
+def test_layout_without_sweeps(ops, k, steps):
+    X = torch.rand((k, 2), device="cuda")
+    D = torch.full((k, k), 3.0, device="cuda")
+    got = ops.layout(D, X, steps)
+    assert got.shape == X.shape and torch.equal(got, X)
+    assert k == 0 or got.data_ptr() != X.data_ptr()
