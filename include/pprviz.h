@@ -402,6 +402,9 @@ size_t ppr_backward_workspace(const ppr_csr* g, int recompute);
  * edge hold the same value).  Requires col_idx sorted within each row.
  * ppr: the n x n all-pairs pi_hat (rows = sources) of the same T, or NULL to
  * recompute it inside the workspace.  grad_arc: float[nnz].
+ * grad_dppr must be finite: A may be taken as a dense product of pi_hat and Gb,
+ * where a NaN or infinity meets the zeros of pi_hat between components and
+ * reaches every component's arcs.
  * Only meaningful for graphs whose arcs each carry their own weight
  * parameter; unit-weight graphs (weight == NULL) are differentiated at w = 1.
  */

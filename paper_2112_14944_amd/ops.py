@@ -328,7 +328,8 @@ def stress_backward(delta, x, grad_scale=1.0, want_grad_x=True, want_grad_delta=
 
 def ppr_matrix_backward(g: Csr, alpha, T, ppr, grad_dppr):
     """dLoss/dw per arc (each arc carries the gradient of its undirected
-    edge's shared weight)."""
+    edge's shared weight).  grad_dppr must be finite: a NaN or infinity in it
+    may reach the arcs of every component."""
     dev = g.row_ptr.device
     cg = g.c()
     ws = _ws(L.lib().ppr_backward_workspace(C.byref(cg), 1 if ppr is None else 0), dev)
