@@ -57,6 +57,39 @@ def test_exact_step_matches_pseudo_inverse(ops, k):
     np.testing.assert_allclose(got.mean(axis=0), 0.0, atol=1e-5 * _scale(want))
 
 
+# Either side of the sizes up to which one block takes the whole solve (192) and
+# the update and direction of an iteration (8192), by the residual that the step
+# promises.
+@pytest.mark.parametrize("k", [192, 193, 8192, 8193])
+def test_exact_step_residual(ops, k):
+    tol = 1e-4
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    D = torch.rand((k, k), device="cuda", generator=gen) * 8 + 2
+    D = torch.triu(D, 1)
+    D = (D + D.T).contiguous()
+    Y = (torch.rand((k, 2), device="cuda", generator=gen) * 2 - 1).contiguous()
+    print(f"[guttman residual] k={k}", flush=True)
+    x, iters = ops.layout_step_exact(D, Y, cg_tol=tol)
+    assert 0 < iters < 100
+    X, Y64 = x.double(), Y.double()
+    b, r = torch.empty_like(Y64), torch.empty_like(Y64)
+    for a in range(0, k, 1024):
+        e = min(k, a + 1024)
+        d = D[a:e].double()
+        inv = torch.where(d > 0, 1.0 / d, 0.0)
+        dist = (Y64[a:e, None] - Y64[None]).norm(dim=2)
+        c = torch.where(dist > 0, inv / dist, 0.0)
+        b[a:e] = c.sum(1, keepdim=True) * Y64[a:e] - c @ Y64
+        r[a:e] = (inv * inv).sum(1, keepdim=True) * X[a:e] - (inv * inv) @ X - b[a:e]
+    # The recursion stops at tol.  Its residual and the true one part by the FP32
+    # row sums: 64 roundings of u = 2^-24 one after another at most (8192 columns
+    # over 64 lanes and 4 waves, then the tree), times ||L^w|| ||x|| / ||b|| <= 4
+    # (eigenvalues within a factor 4: the row sums of w are alike and its other
+    # eigenvalues small), over at most 6 iterations: below tol again.
+    assert (r.norm(dim=0) / b.norm(dim=0)).max().item() <= 2 * tol
+    assert X.mean(0).abs().max().item() <= 1e-5 * X.abs().max().item()
+
+
 def test_exact_steps_from_a_real_pdist_never_increase_stress(ops):
     # PDist of an ER graph (n = 500, mean degree 8) computed on the GPU, then
     # ten exact steps from a uniform start: the stress falls at every step.
