@@ -62,6 +62,35 @@ def test_weight_gradient_adjoint(n, T):
     assert ((got - want).norm() / want.norm()).item() <= 2e-5
 
 
+# One node past the graphs whose adjoint row is held in LDS, for a given pi: the
+# dense adjoint pi^T D G / alpha and its product with pi at the arcs.
+def test_weight_gradient_past_the_row_in_lds():
+    ops = get_ops()
+    n, T = 16385, 100
+    g = synth.erdos_renyi(n, 18, 51)
+    assert 2.0 * n**3 / 110e12 < (T - 1) * 4.0 * g.nnz * n / 11e12  # the dense adjoint
+    csr = ops.Csr.from_graph(g, "cuda")
+    pi = ops.ppr_matrix(csr, np.arange(n), alpha=ALPHA, tol=0.0, max_iter=T, want_dppr=False)[0]
+    G = torch.randn((n, n), device="cuda", generator=torch.Generator(device="cuda").manual_seed(n))
+    G = torch.triu(G, 1)
+    G = (G + G.T).contiguous()
+    print(f"[adjoint] n={n} nnz={g.nnz} T={T}", flush=True)
+    got = ops.ppr_matrix_backward(csr, ALPHA, T, pi, G).double()
+    rows = torch.repeat_interleave(torch.arange(n), torch.as_tensor(np.diff(g.row_ptr)).long()).cuda()
+    cols = torch.as_tensor(g.col_idx, device="cuda").long()
+    d = torch.as_tensor(np.diff(g.row_ptr), device="cuda").double()
+    pi64 = pi.double()
+    A = pi64.T.contiguous() @ (d[:, None] * G.double()) / ALPHA
+    dq = torch.cat([(A[rows[e:e + 8192]] * pi64[cols[e:e + 8192]]).sum(1) for e in range(0, g.nnz, 8192)])
+    row = torch.zeros(n, dtype=torch.float64, device="cuda").index_add_(0, rows, dq / d[rows])
+    arc = (1 - ALPHA) / d[rows] * (dq - row[rows]) + (G.double() * pi64).sum(1)[rows]
+    # the arc v -> u of u -> v: both lists are in row-major order
+    rev = torch.argsort(cols * n + rows)
+    want = arc + arc[rev]
+    # as above: an entry of A is a sum of n FP32 terms, the rest FP64
+    assert ((got - want).norm() / want.norm()).item() <= 2e-5
+
+
 # rows of 1 to n - 1 arcs, so that a block's 32 arcs are many rows, one, or a
 # part of one; 63, 64 and 513 around a wave's and eight waves' columns
 @pytest.mark.parametrize("n", [63, 64, 257, 513, 1000])
