@@ -453,19 +453,15 @@ __global__ __launch_bounds__(kPdistThreads) void batch_pdist_kernel(const int64_
     }
 }
 
-// Row kernels over (subgraph, 16 rows) items, grid-stride: pre is the
-// per-subgraph prefix of the item list and item_graph its subgraph map.
-// Used for the stress of the final layout, whose per-item partials are then
-// summed per subgraph in item order.
-template <int MODE>
-__global__ __launch_bounds__(256) void batch_layout_kernel(const int64_t* __restrict__ node_off,
-                                                           const int64_t* __restrict__ mat_off, int32_t G,
+// Stress of the final layout over (subgraph, 16 rows) items, grid-stride: pre is
+// the per-subgraph prefix of the item list and item_graph its subgraph map.  The
+// per-item partials are then summed per subgraph in item order.
+__global__ __launch_bounds__(256) void batch_stress_kernel(const int64_t* __restrict__ node_off, int32_t G,
                                                            const int64_t* __restrict__ pre,
                                                            const int32_t* __restrict__ item_graph,
                                                            const int64_t* __restrict__ iv_pre,
                                                            const float* __restrict__ inv,
-                                                           const float2* __restrict__ x, float2* __restrict__ xout,
-                                                           float* __restrict__ wsum, double* __restrict__ part) {
+                                                           const float2* __restrict__ x, double* __restrict__ part) {
     __shared__ double red[4];
     const int wave = threadIdx.x >> 6;
     const int64_t total = pre[G];
@@ -473,17 +469,12 @@ __global__ __launch_bounds__(256) void batch_layout_kernel(const int64_t* __rest
         const int g = item_graph[item];
         const int k = graph_n(node_off, g);
         const int64_t rb = item - pre[g];
-        const int64_t nb = node_off[g];
         const int row_begin = (int)(rb * kLayoutRowsPerBlock) + wave * kLayoutRowsPerWave;
-        const double st = layout_rows<MODE, true>(inv + iv_pre[g], inv_ld(k), k, x + nb, row_begin,
-                                                  xout ? xout + nb : nullptr, 1.f, nullptr, nullptr,
-                                                  wsum ? wsum + nb : nullptr);
-        if (MODE == kLayoutStress) {
-            if ((threadIdx.x & 63) == 0) red[wave] = st;
-            __syncthreads();
-            if (threadIdx.x == 0) part[item] = (red[0] + red[1]) + (red[2] + red[3]);
-            __syncthreads();
-        }
+        const double st = stress_rows(inv + iv_pre[g], inv_ld(k), k, x + node_off[g], row_begin);
+        if ((threadIdx.x & 63) == 0) red[wave] = st;
+        __syncthreads();
+        if (threadIdx.x == 0) part[item] = (red[0] + red[1]) + (red[2] + red[3]);
+        __syncthreads();
     }
 }
 
@@ -746,8 +737,8 @@ static ppr_status batch_enqueue(const ppr_batch* b, float alpha, int32_t T, int3
         next ^= 1;
     }
     if (stress_out) {
-        hipLaunchKernelGGL((batch_layout_kernel<kLayoutStress>), dim3(grid), dim3(256), 0, s, b->node_off, b->mat_off,
-                           G, w.plan.rb_pre, w.plan.rb_graph, w.plan.iv_pre, w.inv, cur, nullptr, nullptr, w.part);
+        hipLaunchKernelGGL(batch_stress_kernel, dim3(grid), dim3(256), 0, s, b->node_off, G, w.plan.rb_pre,
+                           w.plan.rb_graph, w.plan.iv_pre, w.inv, cur, w.part);
         hipLaunchKernelGGL(batch_stress_sum_kernel, dim3((G + 255) / 256), dim3(256), 0, s, w.plan.rb_pre, G, w.part,
                            stress_out);
     }

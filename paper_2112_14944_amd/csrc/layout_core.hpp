@@ -31,7 +31,6 @@ enum {
     kLayoutStress = 2,      // stress partials only
     kLayoutGradX = 3,       // dL/dX
     kLayoutGradBoth = 4,    // dL/dX (optional) and dL/dDelta
-    kLayoutWsum = 5,        // per-row sum_j Delta_ij^-2 (the diagonal of L^w)
 };
 
 // Added to every squared distance before the reciprocal square root, so that
@@ -45,19 +44,18 @@ constexpr int kLayoutRowsPerWave = 4;
 constexpr int kLayoutRowsPerBlock = 4 * kLayoutRowsPerWave;
 
 // Work of one pair (i, j), accumulated into the row's running sums (see
-// layout_rows for the formulas).
+// layout_split_kernel for the formulas).  INV: Dv is 1/Delta, 0 on the diagonal,
+// instead of Delta.
 template <int MODE, bool INV>
 __device__ __forceinline__ void layout_pair(float Dv, bool off, float2 xi, float2 xj, float& ax, float& ay,
                                             float& aw, float& as, float scale, float* gd_ij) {
     constexpr bool STEP = (MODE == kLayoutStep || MODE == kLayoutStepStress);
     constexpr bool STRESS = (MODE == kLayoutStepStress || MODE == kLayoutStress);
     constexpr bool GRAD = (MODE == kLayoutGradX || MODE == kLayoutGradBoth);
-    constexpr bool WSUM = (MODE == kLayoutWsum);
-    constexpr bool acc_w = WSUM || (STEP && !INV);
+    static_assert(!(INV && (STEP || GRAD)), "only the stress takes 1/Delta");
     const float inv = INV ? Dv : (off ? __builtin_amdgcn_rcpf(Dv) : 0.f);
     const float w = inv * inv;
-    if (acc_w) aw += w;
-    if (WSUM) return;
+    if (STEP) aw += w;
     const float dx = xi.x - xj.x;
     const float dy = xi.y - xj.y;
     const float r2 = fmaf(dx, dx, fmaf(dy, dy, kMinSq));
@@ -82,36 +80,14 @@ __device__ __forceinline__ void layout_pair(float Dv, bool off, float2 xi, float
     }
 }
 
-// Pairwise work of 4 consecutive rows i (one wave) against all j of a
-// k-node layout.  Lanes stride over j, so each row of Delta is read
-// coalesced and each X_j load serves 4 rows.
-//   step:   X+_i = (sum_j w X_j + c (X_i - X_j)) / sum_j w,
-//           w = Delta^-2, c = w Delta / d = Delta^-1 d^-1  (Jacobi sweep of
-//           L^w X = L^Y Y; a coincident pair adds only w X_j), taken as
-//           X_i + sum_j g (X_i - X_j) / sum_j w with g = c - w: a correction
-//           to X_i, whose rounding is that of the correction's size
-//   stress: sum_{j != i} (1 - d/Delta)^2, halved per unordered pair
-//   grad:   dL/dX_i = sum_j 2 w (d - Delta) (X_i - X_j)/d,
-//           dL/dDelta_ij = 2 (1 - d/Delta) d / Delta^2
-// INV: `delta` holds 1/Delta with a zero diagonal (precomputed once for many
-// sweeps) instead of Delta.  wsum: per-row sum_j w written by the kLayoutWsum
-// pass (same summation order); a step with INV reads it from there, a step
-// without INV accumulates it itself.
-// Full groups of 4 rows take a branch-free path that issues the loads of 4
-// columns (16 Delta values, 4 positions) before their arithmetic.
-// Returns this wave's stress contribution (lane 0 holds the wave total).
-template <int MODE, bool INV>
-__device__ __forceinline__ double layout_rows(const float* __restrict__ delta, int64_t ld, int32_t k,
-                                              const float2* __restrict__ x, int row_begin,
-                                              float2* __restrict__ xout, float scale,
-                                              float2* __restrict__ gx, float* __restrict__ gd,
-                                              float* __restrict__ wsum) {
+// Stress of 4 consecutive rows i (one wave) against all j of a k-node layout,
+// from `inv`, which holds 1/Delta with a zero diagonal.  Lanes stride over j, so
+// each row is read coalesced and each X_j load serves 4 rows.  Full groups of 4
+// rows take a branch-free path that issues the loads of 4 columns (16 values, 4
+// positions) before their arithmetic.  Lane 0 returns the wave's contribution.
+__device__ __forceinline__ double stress_rows(const float* __restrict__ inv, int64_t ld, int32_t k,
+                                              const float2* __restrict__ x, int row_begin) {
     constexpr int R = kLayoutRowsPerWave;
-    constexpr bool STEP = (MODE == kLayoutStep || MODE == kLayoutStepStress);
-    constexpr bool STRESS = (MODE == kLayoutStepStress || MODE == kLayoutStress);
-    constexpr bool GRAD = (MODE == kLayoutGradX || MODE == kLayoutGradBoth);
-    constexpr bool WSUM = (MODE == kLayoutWsum);
-    static_assert(!(INV && GRAD), "the gradient needs Delta itself");
     const int lane = threadIdx.x & 63;
     float2 xi[R];
     bool ok[R];
@@ -125,7 +101,7 @@ __device__ __forceinline__ double layout_rows(const float* __restrict__ delta, i
     }
     int j = lane;
     if (row_begin + R <= k) {
-        const float* __restrict__ drow = delta + (int64_t)row_begin * ld;
+        const float* __restrict__ drow = inv + (int64_t)row_begin * ld;
         for (; j + 3 * kWave < k; j += 4 * kWave) {
             float2 xv[4];
             float dv[4][R];
@@ -138,11 +114,9 @@ __device__ __forceinline__ double layout_rows(const float* __restrict__ delta, i
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int jj = j + u * kWave;
-                    layout_pair<MODE, INV>(dv[u][r], jj != row_begin + r, xi[r], xv[u], ax[r], ay[r], aw[r], as[r], scale,
-                                           GRAD ? gd + (int64_t)(row_begin + r) * ld + jj : nullptr);
-                }
+                for (int r = 0; r < R; ++r)
+                    layout_pair<kLayoutStress, true>(dv[u][r], j + u * kWave != row_begin + r, xi[r], xv[u], ax[r],
+                                                     ay[r], aw[r], as[r], 1.f, nullptr);
             }
         }
     }
@@ -152,38 +126,31 @@ __device__ __forceinline__ double layout_rows(const float* __restrict__ delta, i
         for (int r = 0; r < R; ++r) {
             if (!ok[r]) continue;
             const int i = row_begin + r;
-            layout_pair<MODE, INV>(delta[(int64_t)i * ld + j], j != i, xi[r], xj, ax[r], ay[r], aw[r], as[r],
-                                   scale, GRAD ? gd + (int64_t)i * ld + j : nullptr);
+            layout_pair<kLayoutStress, true>(inv[(int64_t)i * ld + j], j != i, xi[r], xj, ax[r], ay[r], aw[r], as[r],
+                                             1.f, nullptr);
         }
     }
     double st = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (!ok[r]) continue;  // wave-uniform
-        const int i = row_begin + r;
-        if (WSUM) {
-            const float sw = wave_sum(aw[r]);
-            if (lane == 0) wsum[i] = sw;
-        }
-        if (STEP || GRAD) {
-            const float sx = wave_sum(ax[r]);
-            const float sy = wave_sum(ay[r]);
-            if (STEP) {
-                const float sw = INV ? wsum[i] : wave_sum(aw[r]);
-                if (lane == 0) xout[i] = sw > 0.f ? make_float2(xi[r].x + sx / sw, xi[r].y + sy / sw) : xi[r];
-            } else if (gx && lane == 0) {
-                gx[i] = make_float2(scale * sx, scale * sy);
-            }
-        }
-        if (STRESS) st += wave_sum((double)as[r]);
+        st += wave_sum((double)as[r]);
     }
     return 0.5 * st;
 }
 
 // ---------------------------------------------------------------------------
-// Row sweep of one k-node layout (the formulas of layout_rows).  A row group
-// is 4 rows; S = 1 << sl of the block's 8 waves share it, each with every S-th
-// piece of U x 64 columns, and add their sums through LDS in wave order.
+// Row sweep of one k-node layout.
+//   step:   X+_i = (sum_j w X_j + c (X_i - X_j)) / sum_j w,
+//           w = Delta^-2, c = w Delta / d = Delta^-1 d^-1  (Jacobi sweep of
+//           L^w X = L^Y Y; a coincident pair adds only w X_j), taken as
+//           X_i + sum_j g (X_i - X_j) / sum_j w with g = c - w: a correction
+//           to X_i, whose rounding is that of the correction's size
+//   stress: sum_{j != i} (1 - d/Delta)^2, halved per unordered pair
+//   grad:   dL/dX_i = sum_j 2 w (d - Delta) (X_i - X_j)/d,
+//           dL/dDelta_ij = 2 (1 - d/Delta) d / Delta^2
+// A row group is 4 rows; S = 1 << sl of the block's 8 waves share it, each with
+// every S-th piece of U x 64 columns, and add their sums through LDS in wave order.
 //
 // Bound: latency below a few thousand nodes (Delta fits the caches, and a wave
 // that walks all columns alone waits for one load after another), the Delta
@@ -354,7 +321,7 @@ inline LayoutSplit layout_split(int32_t k, bool stress) {
 // ---------------------------------------------------------------------------
 // Strip Jacobi sweep of the batch.  Delta is symmetric, so each unordered
 // pair {i, j} is evaluated once and feeds both rows.  The sweep formula of
-// layout_rows, X+_i = (sum_j w X_j + c (X_i - X_j)) / sum_j w with
+// layout_split_kernel, X+_i = (sum_j w X_j + c (X_i - X_j)) / sum_j w with
 // w = Delta^-2 and c = 1 / (Delta d), is X_i + sum_j g (X_i - X_j) / sum_j w
 // with g = c - w, so a pair adds g (X_i - X_j) to row i and its negative to
 // row j, and the combine step adds X_i and divides by the precomputed weight
