@@ -396,8 +396,10 @@ __global__ __launch_bounds__(256) void query_block_out_kernel(
 // from the degrees (res_sort_kernel's groups; mid_split_kernel's parts and
 // mid_plan_kernel's slices).  Without such a row, which is the rule, it returns
 // after a look at the first rows of the degree order.  Classes from kDegKeys - 1
-// arcs on share the first class, so its rows are ranked here; deg_sorted
-// (n ints) takes the degrees, largest first.
+// arcs on share the first class, whose rows are ranked here as those kernels rank
+// them, by degree up to a limit and by id among rows beyond it (kDegKeys - 1 in the
+// resident tile, kMidKeys - 1 in the other); deg_sorted (n ints) takes the degrees
+// in that order.
 static __global__ __launch_bounds__(1024) void query_refuse_kernel(const RowEnt* __restrict__ rows,
                                                                    const int32_t* __restrict__ hist, int32_t n,
                                                                    int64_t nnz, int64_t cap_groups,
@@ -405,8 +407,10 @@ static __global__ __launch_bounds__(1024) void query_refuse_kernel(const RowEnt*
                                                                    int32_t* __restrict__ refuse) {
     __shared__ int long_row;
     const int tid = threadIdx.x;
+    const bool res = res_cols_for(n) != 0;
     if (tid == 0) long_row = 0;
     __syncthreads();
+    const int cap = (res ? kDegKeys : kMidKeys) - 1;
     const int c0 = hist[0];
     for (int i = tid; i < max(c0, 1); i += 1024)
         if (rows[i].re - rows[i].rs > n) long_row = 1;
@@ -421,8 +425,8 @@ static __global__ __launch_bounds__(1024) void query_refuse_kernel(const RowEnt*
         if (i < c0) {
             at = 0;
             for (int j = 0; j < c0; ++j) {
-                const int o = rows[j].re - rows[j].rs;
-                at += o > d || (o == d && j < i) ? 1 : 0;
+                const int o = min(rows[j].re - rows[j].rs, cap), k = min(d, cap);
+                at += o > k || (o == k && rows[j].rs < rows[i].rs) ? 1 : 0;
             }
         }
         deg_sorted[at] = d;
@@ -430,10 +434,14 @@ static __global__ __launch_bounds__(1024) void query_refuse_kernel(const RowEnt*
     __syncthreads();
     if (tid != 0) return;
     bool over;
-    if (res_cols_for(n) != 0) {
+    if (res) {
         const int GW = 256 / res_cols_for(n);
         int64_t words = 0;
-        for (int g = 0; g < n; g += GW) words += ((((int64_t)max(deg_sorted[g], 1) + 7) / 8 + 1) / 2) * 16 * GW;
+        for (int g = 0; g < n; g += GW) {
+            int64_t dmax = 1;
+            for (int p = g; p < min(n, g + GW); ++p) dmax = max(dmax, (int64_t)deg_sorted[p]);
+            words += ((dmax + 7) / 8 + 1) / 2 * 16 * GW;
+        }
         over = words > res_arc_words(nnz, n);
     } else {
         const int C = mid_cols_for(n);

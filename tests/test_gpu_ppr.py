@@ -182,6 +182,25 @@ def test_resident_repeated_arcs(ops):
     assert np.abs(resid - (1 - ALPHA) ** T).max() <= 2e-6 + rel
 
 
+def test_resident_repeated_arcs_refused_by_every_route(ops):
+    # n = 300, pairs (i, i + 4) of four rows each joined by 20000 and, every second
+    # one, 4200 parallel arcs: the tile keeps rows from 4095 arcs on in id order, so
+    # both groups of 4 rows are padded to 20000 arcs, beyond the arc copy's region
+    # (by degree they would fit).  One source and few pushes go elsewhere on such a
+    # graph when the workspace allows it, and are refused alike.
+    n, reps = 300, (20000, 4200, 20000, 4200)
+    row_ptr, col = np.zeros(n + 1, np.int32), []
+    for v in range(8):
+        row_ptr[v + 1] = reps[v % 4]
+        col.append(np.full(reps[v % 4], (v + 4) % 8))
+    g = ops.Csr(n, sum(map(len, col)), torch.as_tensor(np.cumsum(row_ptr).astype(np.int32), device="cuda"),
+                torch.as_tensor(np.concatenate(col).astype(np.int32), device="cuda"), None)
+    src = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ppr, _, _, _ = ops.ppr_matrix(g, src, tol=0.0, max_iter=86)
+    full, _, _, _ = ops.ppr_matrix(g, np.arange(n), tol=0.0, max_iter=4)
+    assert torch.isnan(full).all().item() and torch.isnan(ppr).all().item()
+
+
 def test_resident_repeated_arcs_flagged(ops):
     # with 5000 repeated arcs per row the padded first group would exceed the
     # reserved region: the layout reports it through NaN outputs
