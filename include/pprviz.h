@@ -18,7 +18,9 @@
  *    before anything is enqueued; a call that returns an error enqueues nothing.
  *  - Graphs are undirected: the CSR holds both arcs u->v and v->u of every
  *    edge, each arc carries the weight of its edge (weights must be finite and
- *    > 0), row_ptr/col_idx are int32, there are no self-loops or duplicate
+ *    > 0, and a node's sum of weights at most 1e36: the iterate is divided by it
+ *    and products of the divided iterates have to be held in FP32),
+ *    row_ptr/col_idx are int32, there are no self-loops or duplicate
  *    arcs.  A node without arcs behaves as if it had a self-loop, so each walk
  *    step stays stochastic (the paper leaves dangling nodes open; this only
  *    affects pi(v, v) of an isolated v).
