@@ -22,8 +22,8 @@
 // differences, 6.6e-8 so.
 //
 // Measured (MI355X): 512 block-model subgraphs of 32 to 2048 nodes (T = 86),
-// PPR stage 43.7 ms by pushes alone, 23.0 ms as 13.6 ms of pushes and 9.4 ms
-// of products; one graph of 2048 nodes, all pairs, 2.01 ms against 0.49 ms of
+// PPR stage 43.7 ms by pushes alone, 24.2 ms as 14.2 ms of pushes and 10.0 ms
+// of products; one graph of 2048 nodes, all pairs, 2.01 ms against 0.50 ms of
 // pushes and three products of 0.13.
 //
 // A 32x32 block on or above the diagonal is stored as computed, one below it
@@ -61,8 +61,8 @@ struct DensePlan {
 
 // Number of products: the k with the least time, in hundredths of a push of
 // one arc from one source.  Measured in the batch: pushes run at 23e12
-// additions/s, products at 100 TFLOP/s, so n^3 FLOP cost what 0.22 n^2 / nnz
-// pushes do; writing the three matrices and the extra push behind V cost about
+// additions/s, products at 90 to 100 TFLOP/s, so n^3 FLOP cost what 0.22 to 0.26
+// n^2 / nnz pushes do; writing the three matrices and the extra push behind V cost about
 // three pushes.  Integer arithmetic, so that host and device agree.
 __host__ __device__ inline DensePlan dense_plan(int n, int64_t nnz, int T) {
     DensePlan best{0, T, 0};
