@@ -61,9 +61,10 @@ struct DensePlan {
 
 // Number of products: the k with the least time, in hundredths of a push of
 // one arc from one source.  Measured in the batch: pushes run at 23e12
-// additions/s, products at 90 to 100 TFLOP/s, so n^3 FLOP cost what 0.22 to 0.26
-// n^2 / nnz pushes do; writing the three matrices and the extra push behind V cost about
-// three pushes.  Integer arithmetic, so that host and device agree.
+// additions/s and products at 89 to 100 TFLOP/s, so n^3 FLOP cost what 0.22 to
+// 0.26 n^2 / nnz pushes do (0.22 here); writing the three matrices and the extra
+// push behind V cost about three pushes.  Integer arithmetic, so that host and
+// device agree.
 __host__ __device__ inline DensePlan dense_plan(int n, int64_t nnz, int T) {
     DensePlan best{0, T, 0};
     if (n < kDenseMinN || n > Res<16>::NMAX || T < kDenseMinT || T > kDenseMaxT) return best;
