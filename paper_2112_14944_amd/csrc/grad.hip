@@ -284,6 +284,7 @@ ppr_status ppr_matrix_backward(const ppr_csr* g, float alpha, int32_t T, const f
         sa.invd = f.invd;
         sa.deg = f.deg;
         sa.n = n;
+        sa.nnz = g->nnz;
         sa.ncols = n;
         sa.ld = stream_ld(n);
         sa.alpha = alpha;

@@ -34,6 +34,7 @@ struct StreamArgs {
     const float* invd;
     const float* deg;
     int32_t n;
+    int64_t nnz;
     int32_t ncols;        // valid columns (right-hand sides)
     int64_t ld;           // columns held (multiple of 64)
     float alpha;
@@ -218,10 +219,11 @@ __device__ __forceinline__ float4 slab_load(__amdgpu_buffer_rsrc_t r, uint32_t o
 // AHEAD: the gathers of a pass go out before the pass ahead of it is summed,
 // so that a row waits for half a load latency per pass; it costs 32 registers
 // (streaming step at 10^6 nodes, 3e7 arcs, 64 columns: 1233 us per push
-// without, 1040 us with); it also shortens the Group Forward-Push rounds of
-// small grids, whose longest row sets their time.  The flagged rounds of large grids lose
-// more by the lower occupancy than they gain (late rounds 57-135 us without,
-// 100 us and more with), dense ones do not change.
+// without, 1040 us with; short rows lose, see stream_launch_step); it also
+// shortens the Group Forward-Push rounds of small grids, whose longest row sets
+// their time.  The flagged rounds of large grids lose more by the lower occupancy
+// than they gain (late rounds 57-135 us without, 100 us and more with), dense ones
+// do not change.
 template <bool WEIGHTED, bool FLAGGED, int STEP, bool AHEAD>
 __device__ __forceinline__ float4 slab_gather(__amdgpu_buffer_rsrc_t rin, const int32_t* __restrict__ col_idx,
                                               const float* __restrict__ weight, int rs, int dg, int lane,
@@ -308,7 +310,7 @@ __device__ __forceinline__ float4 slab_gather(__amdgpu_buffer_rsrc_t rin, const 
 // degree order side by side within one slab: lane = 8 * g + q, where g picks
 // the row and q 4 of the slab's 32 columns (one 16-byte load per arc, summed
 // by slab_gather).
-template <bool WEIGHTED, bool FINAL>
+template <bool WEIGHTED, bool FINAL, bool AHEAD>
 __global__ __launch_bounds__(256) void stream_step_kernel(
     const RowEnt* __restrict__ rows, const int32_t* __restrict__ col_idx,
     const float* __restrict__ weight, const float* __restrict__ invd, const float* __restrict__ deg,
@@ -333,7 +335,7 @@ __global__ __launch_bounds__(256) void stream_step_kernel(
         v = e.v;
     }
     const uint32_t qoff = (uint32_t)q * 16u;
-    float4 acc = slab_gather<WEIGHTED, false, kSlabVec, true>(rin, col_idx, weight, rs, dg, lane, qoff);
+    float4 acc = slab_gather<WEIGHTED, false, kSlabVec, AHEAD>(rin, col_idx, weight, rs, dg, lane, qoff);
     if (has_row && dg == 0) acc = slab_load(rin, ((uint32_t)v << 7) | qoff);
     if (!has_row) return;
     const int col0 = slab * kSlab + q * 4;
@@ -371,7 +373,11 @@ static __global__ void stream_resid_kernel(const double* __restrict__ part, int6
     resid[s] = 1.0 - t;
 }
 
-template <bool FINAL>
+// Gathers go out a pass ahead from a mean of 20 arcs per row on: shorter rows are
+// one to three passes and wait less than the lower occupancy costs.  A step with and
+// without, weights: 12000 nodes, 4, 12, 20 and 80 arcs 582, 842, 1047 and 2658 us and
+// 557, 815, 1055 and 2691; 36000 nodes, 40 arcs 18.1 and 18.8 ms.
+template <bool FINAL, bool AHEAD>
 inline void stream_launch_step(const StreamArgs& a, const float* yin, float* yout, hipStream_t s) {
     StreamGrid g;
     g.row_blocks = (a.n + kStreamRowsPerBlock - 1) / kStreamRowsPerBlock;
@@ -379,10 +385,10 @@ inline void stream_launch_step(const StreamArgs& a, const float* yin, float* you
     g.full_rounds = ((int64_t)a.n * kSlab * 4 <= kStreamSlabBudget) ? g.slabs / kXcds : 0;
     const dim3 grid((unsigned)((int64_t)g.row_blocks * g.slabs));
     if (a.weight)
-        hipLaunchKernelGGL((stream_step_kernel<true, FINAL>), grid, dim3(256), 0, s, a.rows, a.col_idx, a.weight,
+        hipLaunchKernelGGL((stream_step_kernel<true, FINAL, AHEAD>), grid, dim3(256), 0, s, a.rows, a.col_idx, a.weight,
                            a.invd, a.deg, a.forcing, a.ld_forcing, a.n, a.ncols, a.alpha, g, yin, yout);
     else
-        hipLaunchKernelGGL((stream_step_kernel<false, FINAL>), grid, dim3(256), 0, s, a.rows, a.col_idx, a.weight,
+        hipLaunchKernelGGL((stream_step_kernel<false, FINAL, AHEAD>), grid, dim3(256), 0, s, a.rows, a.col_idx, a.weight,
                            a.invd, a.deg, a.forcing, a.ld_forcing, a.n, a.ncols, a.alpha, g, yin, yout);
 }
 
@@ -395,9 +401,15 @@ inline const float* stream_adjoint(const StreamArgs& a, int T, float* ya, float*
                        a.ncols, a.ld, a.alpha, T == 1 ? 1 : 0, ya);
     float* in = ya;
     float* out = yb;
+    const bool ahead = a.nnz >= 20 * (int64_t)a.n;
     for (int it = 1; it < T; ++it) {
-        if (it == T - 1) stream_launch_step<true>(a, in, out, s);
-        else stream_launch_step<false>(a, in, out, s);
+        if (it == T - 1) {
+            if (ahead) stream_launch_step<true, true>(a, in, out, s);
+            else stream_launch_step<true, false>(a, in, out, s);
+        } else {
+            if (ahead) stream_launch_step<false, true>(a, in, out, s);
+            else stream_launch_step<false, false>(a, in, out, s);
+        }
         float* t = in;
         in = out;
         out = t;

@@ -62,6 +62,40 @@ def test_weight_gradient_adjoint(n, T):
     assert ((got - want).norm() / want.norm()).item() <= 2e-5
 
 
+# Streaming adjoint steps (T = 3) on rows below and from 20 arcs on average, which
+# gather a pass ahead or not: equal rows around the limit, and a few hubs.
+@pytest.mark.parametrize("degree,hubs", [(6, 0), (18, 0), (20, 0), (40, 0), (6, 3)])
+def test_weight_gradient_streaming_rows(degree, hubs):
+    ops = get_ops()
+    n, T = 2500, 3
+    ring = np.concatenate([np.stack([np.arange(n), (np.arange(n) + k) % n], 1) for k in range(1, degree // 2 + 1)] +
+                          [np.stack([np.full(n, h), np.arange(n)], 1) for h in range(hubs)])
+    e = np.unique(np.sort(ring[ring[:, 0] != ring[:, 1]], 1), axis=0)
+    g = synth.build_graph(n, e[:, 0], e[:, 1],
+                          (0.5 + np.random.default_rng(degree).random(len(e))).astype(np.float32))
+    csr = ops.Csr.from_graph(g, "cuda")
+    G = torch.randn((n, n), device="cuda", generator=torch.Generator(device="cuda").manual_seed(n))
+    G = (torch.triu(G, 1) + torch.triu(G, 1).T).contiguous()
+    print(f"[streaming rows] nnz={g.nnz} degree={degree} hubs={hubs}", flush=True)
+    # streamed, not dense
+    assert (T - 1) * (4.0 * g.nnz * n / 11e12 + 6e-6) <= 2.0 * n**3 / 110e12 + 10e-6
+    got = ops.ppr_matrix_backward(csr, ALPHA, T, None, G).double()
+    W, d, Q, rows, cols = _walk64(g)
+    pi = torch.zeros_like(Q)
+    A = torch.zeros_like(Q)
+    for _ in range(T):
+        pi = ALPHA * torch.eye(n, dtype=torch.float64, device="cuda") + pi @ Q
+        A = d[:, None] * G.double() + Q.T.contiguous() @ A
+    dq = (A @ pi.T.contiguous())[rows, cols]
+    row = torch.zeros(n, dtype=torch.float64, device="cuda").index_add_(0, rows, W[rows, cols] / d[rows] * dq)
+    both = torch.zeros_like(Q)
+    both[rows, cols] = (1 - ALPHA) / d[rows] * (dq - row[rows]) + (G.double() * pi).sum(1)[rows]
+    want = (both + both.T)[rows, cols]
+    # T steps of rows of at most n terms, summed by 8 arcs a pass: fewer roundings
+    # than the dense products' 320, whose bar this is
+    assert ((got - want).norm() / want.norm()).item() <= 2e-5
+
+
 # One node past the graphs whose adjoint row is held in LDS, for a given pi: the
 # dense adjoint pi^T D G / alpha and its product with pi at the arcs.
 def test_weight_gradient_past_the_row_in_lds():
